@@ -15,10 +15,11 @@
 // C x C matrix per retained frequency.
 //
 // Every contraction -- the truncated DFTs axis by axis, the per-frequency
-// channel mixing, the pointwise channel maps and all their adjoints -- is one
-// batched strided GEMM on the matrix cores: v_mfma_f32_16x16x16_bf16, operands
-// rounded to bfloat16 as they are loaded (weights and activations), products
-// accumulated in FP32.  Complex products are four real GEMMs on planar
+// channel mixing, the pointwise channel maps and all their adjoints -- runs on
+// the matrix cores: v_mfma_f32_16x16x16_bf16, operands rounded to bfloat16 as
+// they are loaded (weights and activations), products accumulated in FP32;
+// through the fused passes of rpm_fno_layer.h, or for wider networks than they
+// hold as batched strided GEMMs.  Complex products are four real GEMMs on planar
 // real/imaginary arrays.  Elementwise work (bias, GELU and its derivative,
 // loss, Adam) runs in small FP32 kernels.
 #include <hip/hip_runtime.h>
@@ -29,9 +30,16 @@
 #include <cstring>
 #include <vector>
 
+#include "rpm_fno_layer.h"
 #include "rpmfno.h"
 
 namespace {
+
+using fno::bf16x4;
+using fno::f32x4;
+using fno::gelu;
+using fno::gelu_grad;
+using fno::to_bf16;
 
 // ---------------------------------------------------------------------------
 // Batched strided GEMM on the matrix cores
@@ -48,17 +56,6 @@ struct GemmDesc {
     long long sAb, sAi, sAk, sBb, sBk, sBj, sCb, sCi, sCj;
     float alpha, beta;
 };
-
-typedef short bf16x4 __attribute__((ext_vector_type(4)));
-typedef float f32x4 __attribute__((ext_vector_type(4)));
-
-__device__ __forceinline__ short to_bf16(float f)
-{
-    uint32_t u = __float_as_uint(f);
-    if ((u & 0x7f800000u) == 0x7f800000u) return (short)(u >> 16);  // inf / nan kept
-    u += 0x7fffu + ((u >> 16) & 1u);
-    return (short)(u >> 16);
-}
 
 // 256 threads = 4 waves; a block owns a 32 x 32 tile of C[b] (waves in 2 x 2
 // tiles of 16 x 16), b = blockIdx.y.  Per 16-deep step lane l loads
@@ -138,17 +135,6 @@ GemmDesc gd(const float* A, long long sAb, long long sAi, long long sAk, const f
 // ---------------------------------------------------------------------------
 // Elementwise kernels
 // ---------------------------------------------------------------------------
-__device__ __forceinline__ float gelu(float x)
-{
-    return 0.5f * x * (1.f + erff(x * 0.70710678118654752f));
-}
-__device__ __forceinline__ float gelu_grad(float x)
-{
-    const float cdf = 0.5f * (1.f + erff(x * 0.70710678118654752f));
-    const float pdf = 0.39894228040143268f * expf(-0.5f * x * x);
-    return cdf + x * pdf;
-}
-
 // pre = acc + bias[c]; out = gelu(pre) (act) or pre; layout [B][C][N]
 __global__ void k_bias_act(float* __restrict__ acc, const float* __restrict__ bias, float* __restrict__ out, int C,
                            long long N, long long total, int act)
@@ -331,6 +317,8 @@ struct FWs {
     long long y;                      // output [B][cout][N]
     long long feat;                   // input features of a warm start [cin][N]
     long long part;                   // loss partial sums (double, 1024)
+    long long tab[3];                 // bfloat16 twiddle tables of the fused passes
+    long long wg;                     // partial sums of the fused weight gradients
     long long total;
     long long N;
     int n[3];
@@ -369,6 +357,8 @@ FWs make_fws(const Net& net, const int32_t n[3], int B)
     w.y = take((long long)B * net.cout * N);
     w.feat = take((long long)net.cin * N);
     w.part = take(2 * 1024);
+    for (int a = 0; a < 3; ++a) w.tab[a] = take(2 * fno::kModeSlots * ((n[a] + 15) / 16 * 16));
+    w.wg = take((long long)fno::kWgradBlocks * 4 * 16 * (16 * 4 + 1));
     w.total = off;
     return w;
 }
@@ -379,6 +369,8 @@ struct Fno {
     float* ws;
     hipStream_t s;
     int B;
+    bool fused;  // the passes of rpm_fno_layer.h serve this network and grid
+    fno::AxTab ax[3];
     bool ok = true;
     float* at(long long off) { return ws + off; }
     void G(const GemmDesc& d, int batch)
@@ -533,7 +525,7 @@ void pointwise_wgrad(Fno& f, const float* d, int co, const float* in, int ci, fl
             1);
 }
 
-void forward(Fno& f, const float* P, const float* x)
+void forward(Fno& f, const float* P, const float* x, float* y)
 {
     const Net& net = f.net;
     const long long N = f.w.N, B = f.B, C = net.C;
@@ -557,8 +549,8 @@ void forward(Fno& f, const float* P, const float* x)
     }
     // projection
     const long long outn = B * net.cout * N;
-    pointwise(f, P + net.proj_w, net.cout, (int)C, h0 + net.L * act, f.at(f.w.y), 1.f, 0.f, 0);
-    k_bias_act<<<blocks(outn), 256, 0, f.s>>>(f.at(f.w.y), P + net.proj_b, f.at(f.w.y), net.cout, N, outn, 0);
+    pointwise(f, P + net.proj_w, net.cout, (int)C, h0 + net.L * act, y, 1.f, 0.f, 0);
+    k_bias_act<<<blocks(outn), 256, 0, f.s>>>(y, P + net.proj_b, y, net.cout, N, outn, 0);
 }
 
 // gradient of the parameters (and of the input, dx nullable) for the output
@@ -626,6 +618,198 @@ bool valid_grid(const int32_t n[3])
     return true;
 }
 
+// ---------------------------------------------------------------------------
+// The same network through the fused passes (rpm_fno_layer.h)
+// ---------------------------------------------------------------------------
+// They hold all modes of an axis in one MFMA tile, the channels of a voxel in at
+// most four, and a row of 16-bit DFT operands per mode in LDS: up to 16 modes,
+// 64 channels and extents of 512.  Wider networks take the batched GEMMs.
+bool fused_fits(const Net& net, const int* n)
+{
+    return net.m <= fno::kModeSlots && net.C <= 64 && net.cin <= 64 && net.cout <= 64 && n[0] <= 512 &&
+           n[1] <= 512 && n[2] <= 512;
+}
+
+bool aligned16(const void* p) { return (reinterpret_cast<uintptr_t>(p) & 15) == 0; }
+
+void make_tables(Fno& f)
+{
+    int np = 0;
+    for (int a = 0; a < 3; ++a) {
+        fno::AxTab& t = f.ax[a];
+        t.n = f.w.n[a];
+        t.np = (t.n + 15) / 16 * 16;
+        t.fc = reinterpret_cast<short*>(f.at(f.w.tab[a]));
+        t.fs = t.fc + fno::kModeSlots * t.np;
+        t.ic = t.fs + fno::kModeSlots * t.np;
+        t.is = t.ic + fno::kModeSlots * t.np;
+        np = std::max(np, t.np);
+    }
+    fno::k_tables<<<dim3((unsigned)(fno::kModeSlots * np / 256), 3), 256, 0, f.s>>>(f.ax[0], f.ax[1], f.ax[2],
+                                                                                  f.net.m);
+}
+
+void fused_dft(Fno& f, const float* v, float* X, long long xplane)
+{
+    const fno::AxTab *a = f.ax;
+    const int m = f.net.m, ct = (m * m + 15) / 16;
+    const long long P = (long long)f.B * f.net.C, plane = P * a[2].n * m * m;
+    float* T2 = f.at(f.w.s2);
+    const int nt = 64 * std::min(4, std::max(2, a[1].np / 16));
+    const size_t lds = (size_t)2 * fno::kModeSlots * (a[1].np + 4) * sizeof(short);
+    if (a[0].n % 4 == 0 && aligned16(v))
+        fno::k_dft_xy<true><<<(unsigned)(P * a[2].n), nt, lds, f.s>>>(v, T2, plane, m, a[0], a[1]);
+    else
+        fno::k_dft_xy<false><<<(unsigned)(P * a[2].n), nt, lds, f.s>>>(v, T2, plane, m, a[0], a[1]);
+    fno::k_dft_z<<<(unsigned)(P * ct), 128, 0, f.s>>>(T2, plane, X, xplane, m, ct, a[2]);
+}
+
+void fused_idft_z(Fno& f, const float* Y, long long xplane, float* U, long long uplane)
+{
+    const int m = f.net.m, ct = (m * m + 15) / 16;
+    const long long P = (long long)f.B * f.net.C;
+    fno::k_idft_z<<<(unsigned)(P * ct), 256, 0, f.s>>>(Y, xplane, U, uplane, m, ct, f.ax[2]);
+}
+
+template <int CT>
+void fused_mix(Fno& f, const float* Rre, const float* Rim, const float* X, float* Y, long long plane, bool conj)
+{
+    const int C = f.net.C, m3 = f.net.m3;
+    const unsigned g = (unsigned)((m3 + 3) / 4);
+    if (conj)
+        fno::k_mix<CT, true, false><<<g, 256, 0, f.s>>>(Rre, Rim, X, plane, Y, plane, C, f.B, m3);
+    else if (C % 4 == 0 && aligned16(Rre) && aligned16(Rim))
+        fno::k_mix<CT, false, true><<<g, 256, 0, f.s>>>(Rre, Rim, X, plane, Y, plane, C, f.B, m3);
+    else
+        fno::k_mix<CT, false, false><<<g, 256, 0, f.s>>>(Rre, Rim, X, plane, Y, plane, C, f.B, m3);
+}
+
+template <int CT, int MODE>
+void fused_layer_out(Fno& f, const float* U, long long uplane, const float* h, const float* W, const float* bias,
+                     const float* aux, float* pre, float* out)
+{
+    const fno::AxTab* a = f.ax;
+    const unsigned g = (unsigned)((long long)f.B * a[2].n * (a[1].np / 16));
+    const size_t lds = (size_t)2 * 16 * fno::layer_vs(CT) * sizeof(short);
+    fno::k_layer_out<CT, MODE><<<g, 1024, lds, f.s>>>(U, uplane, h, W, MODE == fno::LAYER_FWD ? 0 : 1, bias, aux, pre,
+                                                     out, f.net.C, a[2].n, f.net.m, 1.f / (float)f.w.N, a[0], a[1]);
+}
+
+// out = W in (W^T in with trans), + bias[o] or * gelu'(aux)
+void fused_pointwise(Fno& f, const float* W, int co, int ci, int trans, const float* in, float* out,
+                     const float* bias, const float* aux)
+{
+    const int M = trans ? ci : co, K = trans ? co : ci, kt = (K + 15) / 16;
+    const long long tpb = (f.w.N + 31) / 32, nt = tpb * f.B;
+    const unsigned g = (unsigned)std::min<long long>((nt + 3) / 4, 2048);
+#define FNO_PW(T) fno::k_pointwise<T><<<g, 256, 0, f.s>>>(W, trans, in, out, bias, aux, M, K, f.w.N, nt, tpb)
+    if (kt == 1) FNO_PW(1);
+    else if (kt == 2) FNO_PW(2);
+    else if (kt == 3) FNO_PW(3);
+    else FNO_PW(4);
+#undef FNO_PW
+}
+
+// dW[o][i] = sum_{b, v} d in, db[o] = sum_{b, v} d
+void fused_wgrad(Fno& f, const float* d, int co, const float* in, int ci, float* dW, float* db)
+{
+    const long long N = f.w.N, upb = (N + 63) / 64, units = upb * f.B;
+    const int mt = (co + 15) / 16, nt = (ci + 15) / 16;
+    const int G = (int)std::min<long long>(fno::kWgradBlocks, (units + 3) / 4);
+    float* part = f.at(f.w.wg);
+    const bool vec = N % 4 == 0 && aligned16(d) && aligned16(in);
+#define FNO_WG(T)                                                                                                      if (vec) fno::k_wgrad<T, true><<<dim3((unsigned)G, (unsigned)mt), 256, 0, f.s>>>(d, in, part, co, ci, N, units, upb);     else fno::k_wgrad<T, false><<<dim3((unsigned)G, (unsigned)mt), 256, 0, f.s>>>(d, in, part, co, ci, N, units, upb)
+    if (nt == 1) { FNO_WG(1); }
+    else if (nt == 2) { FNO_WG(2); }
+    else if (nt == 3) { FNO_WG(3); }
+    else { FNO_WG(4); }
+#undef FNO_WG
+    fno::k_wgrad_reduce<<<(co * (ci + 1) + 3) / 4, 256, 0, f.s>>>(part, G, mt, nt, co, ci, dW, db);
+}
+
+// forward pass; keep_pre: the pre-activations stay for a backward pass
+template <int CT>
+void fused_forward(Fno& f, const float* P, const float* x, float* y, bool keep_pre)
+{
+    const Net& net = f.net;
+    const long long act = (long long)f.B * net.C * f.w.N, xplane = (long long)f.B * net.C * net.m3;
+    const long long uplane = (long long)f.B * net.C * f.w.n[2] * net.m * net.m;
+    float* h0 = f.at(f.w.h);
+    float *Y = f.at(f.w.s1), *U = f.at(f.w.s3);
+    fused_pointwise(f, P + net.lift_w, net.C, net.cin, 0, x, h0, P + net.lift_b, nullptr);
+    for (int l = 0; l < net.L; ++l) {
+        const float* h = h0 + l * act;
+        float* X = f.at(f.w.xhat) + 2 * l * xplane;
+        fused_dft(f, h, X, xplane);
+        fused_mix<CT>(f, P + net.r_re[l], P + net.r_im[l], X, Y, xplane, false);
+        fused_idft_z(f, Y, xplane, U, uplane);
+        fused_layer_out<CT, fno::LAYER_FWD>(f, U, uplane, h, P + net.pw_w[l], P + net.pw_b[l], nullptr,
+                                            keep_pre ? f.at(f.w.pre) + l * act : nullptr, h0 + (l + 1) * act);
+    }
+    fused_pointwise(f, P + net.proj_w, net.cout, net.C, 0, h0 + net.L * act, y, P + net.proj_b, nullptr);
+}
+
+template <int CT>
+void fused_backward(Fno& f, const float* P, const float* x, const float* dy, float* g, float* dx)
+{
+    const Net& net = f.net;
+    const int C = net.C, L = net.L;
+    const long long act = (long long)f.B * C * f.w.N, xplane = (long long)f.B * C * net.m3;
+    const long long uplane = (long long)f.B * C * f.w.n[2] * net.m * net.m;
+    const float invN = 1.f / (float)f.w.N;
+    float *h0 = f.at(f.w.h), *pre = f.at(f.w.pre);
+    float *d = f.at(f.w.dpre), *dn = f.at(f.w.dh2);  // gradient of a layer's pre-activations, of the next lower one's
+    float *D = f.at(f.w.s3), *RD = f.at(f.w.s1), *U = f.at(f.w.s4);
+    fused_wgrad(f, dy, net.cout, h0 + L * act, C, g + net.proj_w, g + net.proj_b);
+    fused_pointwise(f, P + net.proj_w, net.cout, C, 1, dy, d, nullptr, L > 0 ? pre + (L - 1) * act : nullptr);
+    for (int l = L - 1; l >= 0; --l) {
+        const float* X = f.at(f.w.xhat) + 2 * l * xplane;
+        fused_wgrad(f, d, C, h0 + l * act, C, g + net.pw_w[l], g + net.pw_b[l]);
+        // D = F dpre; dR(k) = (1/N) sum_b D X^H; dh = W^T dpre + (1/N) Re F^H R^H D
+        fused_dft(f, d, D, xplane);
+        fno::k_spec_wgrad<CT><<<(unsigned)((net.m3 + 3) / 4), 256, 0, f.s>>>(
+            D, X, xplane, g + net.r_re[l], g + net.r_im[l], C, f.B, net.m3, invN);
+        fused_mix<CT>(f, P + net.r_re[l], P + net.r_im[l], D, RD, xplane, true);
+        fused_idft_z(f, RD, xplane, U, uplane);
+        if (l > 0)
+            fused_layer_out<CT, fno::LAYER_BWD>(f, U, uplane, d, P + net.pw_w[l], nullptr, pre + (l - 1) * act,
+                                                nullptr, dn);
+        else
+            fused_layer_out<CT, fno::LAYER_PLAIN>(f, U, uplane, d, P + net.pw_w[l], nullptr, nullptr, nullptr, dn);
+        std::swap(d, dn);
+    }
+    fused_wgrad(f, d, C, x, net.cin, g + net.lift_w, g + net.lift_b);
+    if (dx) fused_pointwise(f, P + net.lift_w, C, net.cin, 1, d, dx, nullptr, nullptr);
+}
+
+void net_forward(Fno& f, const float* P, const float* x, float* y, bool keep_pre)
+{
+    if (!f.fused) {
+        forward(f, P, x, y);
+        return;
+    }
+    switch ((f.net.C + 15) / 16) {
+        case 1: fused_forward<1>(f, P, x, y, keep_pre); break;
+        case 2: fused_forward<2>(f, P, x, y, keep_pre); break;
+        case 3: fused_forward<3>(f, P, x, y, keep_pre); break;
+        default: fused_forward<4>(f, P, x, y, keep_pre); break;
+    }
+}
+
+void net_backward(Fno& f, const float* P, const float* x, const float* dy, float* g, float* dx)
+{
+    if (!f.fused) {
+        backward(f, P, x, dy, g, dx);
+        return;
+    }
+    switch ((f.net.C + 15) / 16) {
+        case 1: fused_backward<1>(f, P, x, dy, g, dx); break;
+        case 2: fused_backward<2>(f, P, x, dy, g, dx); break;
+        case 3: fused_backward<3>(f, P, x, dy, g, dx); break;
+        default: fused_backward<4>(f, P, x, dy, g, dx); break;
+    }
+}
+
 rpm_status fno_open(Fno& f, const rpm_fno_config* cfg, const int32_t n[3], int32_t batch, void* ws, size_t ws_bytes,
                     void* stream)
 {
@@ -636,7 +820,9 @@ rpm_status fno_open(Fno& f, const rpm_fno_config* cfg, const int32_t n[3], int32
     f.ws = (float*)ws;
     f.s = (hipStream_t)stream;
     f.B = batch;
-    if (!upload_twiddles(f)) return RPM_E_HIP;
+    f.fused = fused_fits(f.net, f.w.n);
+    if (f.fused) make_tables(f);
+    else if (!upload_twiddles(f)) return RPM_E_HIP;
     return RPM_OK;
 }
 
@@ -714,10 +900,7 @@ rpm_status rpm_fno_forward(const rpm_fno_config* cfg, const float* params, const
     Fno f;
     rpm_status rs = fno_open(f, cfg, n, batch, workspace, ws_bytes, hip_stream);
     if (rs != RPM_OK) return rs;
-    forward(f, params, x);
-    if (y && hipMemcpyAsync(y, f.at(f.w.y), sizeof(float) * (size_t)batch * f.net.cout * f.w.N,
-                            hipMemcpyDeviceToDevice, f.s) != hipSuccess)
-        return RPM_E_HIP;
+    net_forward(f, params, x, y ? y : f.at(f.w.y), true);
     if (!f.ok || hipGetLastError() != hipSuccess || hipStreamSynchronize(f.s) != hipSuccess) return RPM_E_HIP;
     return RPM_OK;
 }
@@ -730,7 +913,7 @@ rpm_status rpm_fno_backward(const rpm_fno_config* cfg, const float* params, cons
     Fno f;
     rpm_status rs = fno_open(f, cfg, n, batch, workspace, ws_bytes, hip_stream);
     if (rs != RPM_OK) return rs;
-    backward(f, params, x, dy, grad, dx);
+    net_backward(f, params, x, dy, grad, dx);
     if (!f.ok || hipGetLastError() != hipSuccess || hipStreamSynchronize(f.s) != hipSuccess) return RPM_E_HIP;
     return RPM_OK;
 }
@@ -743,14 +926,14 @@ rpm_status rpm_fno_train_step(const rpm_fno_config* cfg, float* params, float* g
     Fno f;
     rpm_status rs = fno_open(f, cfg, n, batch, workspace, ws_bytes, hip_stream);
     if (rs != RPM_OK) return rs;
-    forward(f, params, x);
+    net_forward(f, params, x, f.at(f.w.y), true);
     const long long ny = (long long)batch * f.net.cout * f.w.N;
     // the output gradient in the accumulator slot (backward does not use it)
     float* dy = f.at(f.w.acc);
     const int nb = (int)std::min<long long>(1024, (ny + 255) / 256);
     double* part = reinterpret_cast<double*>(f.at(f.w.part));
     k_mse<<<nb, 256, 0, f.s>>>(f.at(f.w.y), target, x, f.net.cin, f.net.cout, f.w.N, dy, part, ny);
-    backward(f, params, x, dy, grad, nullptr);
+    net_backward(f, params, x, dy, grad, nullptr);
     const float b1 = 0.9f, b2 = 0.999f, eps = 1e-8f;
     const float c1 = 1.f - std::pow(b1, (float)step), c2 = 1.f - std::pow(b2, (float)step);
     k_adam<<<blocks(f.net.total), 256, 0, f.s>>>(params, grad, adam_m, adam_v, f.net.total, lr, b1, b2, eps, c1, c2);
@@ -818,7 +1001,7 @@ rpm_status rpm_fno_warm_start(const rpm_fno_config* cfg, const float* params, co
     if (rs != RPM_OK) return rs;
     const long long N = f.w.N;
     k_features<<<blocks(N), 256, 0, f.s>>>(pr->phase, t, f.at(f.w.feat), N);
-    forward(f, params, f.at(f.w.feat));
+    net_forward(f, params, f.at(f.w.feat), f.at(f.w.y), false);
     E6 e;
     for (int i = 0; i < 6; ++i) e.e[i] = E[i];
     if (precision == RPM_FP64) k_assemble<double><<<blocks(N), 256, 0, f.s>>>(f.at(f.w.y), e, (double*)eps0, N);
