@@ -84,8 +84,10 @@ __host__ __device__ __forceinline__ long long zix(long long e, int j, int P)
     return ((e / kZTile) * (long long)P + j) * kZTile + (e % kZTile);
 }
 
-// Device-resident solver state (one per workspace).
-struct DevState {
+// Device-resident solver state (one per workspace).  The scalars come first:
+// they are all a call reads back at its end.
+constexpr int kSumBlocks = 256;  // blocks of the phase-map checksum
+struct DevHead {
     int magic;         // kStateMagic once the workspace has been initialised
     int cfg[6];        // nx, ny, nz, precision, p_max, map the basis was built for
     int done;          // 1 once the iteration stopped (any reason)
@@ -106,8 +108,12 @@ struct DevState {
     double best_err;   // lowest error below 0.9 x the previous lowest (stall test)
     int best_it;       // iteration at which best_err was reached
     int stall_window;  // stop (status 4) after this many iterations without a new best_err; 0 = off
-    double medium[8];  // lambda0, mu0, alpha, beta, a hash of the phase table and a checksum of the phase map
-                       // the basis was built for
+    double medium[6];  // lambda0, mu0, alpha, beta and a hash of the phase table the basis was built for
+};
+struct DevState : DevHead {
+    // checksums of phase maps (partial sums): [0] of the one the basis was built
+    // for (written before its first column), [1] of a call that asks for the basis
+    unsigned long long key[2][kSumBlocks];
     double z[kMaxP], zeta[kMaxP], d[kMaxP];
     double zeta_ring[4][kMaxP];
     double H[kMaxP * kMaxP];
@@ -117,7 +123,7 @@ struct DevState {
     int piv[kMaxP];
 };
 
-constexpr int kStateMagic = 0x52504d31;
+constexpr int kStateMagic = 0x52504d32;
 
 enum { DC_MEAN = 0, DC_ZERO = 1 };   // t_hat(0) = N(<eps> - E) or 0
 enum { OUT_XI = 0, OUT_T = 1 };      // xinv writes eps - t or t
@@ -1683,28 +1689,178 @@ __global__ __launch_bounds__(kThreads) void k_step_end(DevState* __restrict__ st
     }
 }
 
-// Checksum of the phase map (part of the basis reuse key): per-block wrapping
-// sums of (phase + 1) * splitmix64(voxel index); integer sums, so the order
-// does not matter.
+// Checksum of the phase map (part of the basis reuse key): wrapping sums over
+// 8-voxel words of splitmix64(word index + c (word + 1)), missing voxels zero;
+// integer sums, so the order does not matter.  Streams the map with 16-byte
+// loads (an unaligned map byte by byte): 64 blocks of byte loads took 62 us at
+// 128^3 and 414 us at 256^3.
+__device__ __forceinline__ unsigned long long splitmix64(unsigned long long z)
+{
+    z = (z ^ (z >> 30)) * 0xbf58476d1ce4e5b9ull;
+    z = (z ^ (z >> 27)) * 0x94d049bb133111ebull;
+    return z ^ (z >> 31);
+}
+
 __global__ __launch_bounds__(kThreads) void k_phase_sum(const uint8_t* __restrict__ phase, long long N,
                                                         unsigned long long* __restrict__ part)
 {
-    __shared__ unsigned long long red[kThreads];
+    __shared__ unsigned long long red[kWaves];
     unsigned long long s = 0;
-    for (long long v = (long long)blockIdx.x * kThreads + threadIdx.x; v < N; v += (long long)gridDim.x * kThreads) {
-        unsigned long long z = (unsigned long long)v + 0x9e3779b97f4a7c15ull;
-        z = (z ^ (z >> 30)) * 0xbf58476d1ce4e5b9ull;
-        z = (z ^ (z >> 27)) * 0x94d049bb133111ebull;
-        z ^= z >> 31;
-        s += (unsigned long long)(phase[v] + 1) * z;
+    auto word = [&](long long w, unsigned long long v) {
+        s += splitmix64((unsigned long long)w + 0x9e3779b97f4a7c15ull * (v + 1));
+    };
+    auto bytes = [&](long long w) {
+        unsigned long long v = 0;
+        for (int q = 0; q < 8; ++q)
+            if (8 * w + q < N) v |= (unsigned long long)phase[8 * w + q] << (8 * q);
+        return v;
+    };
+    const long long t = (long long)blockIdx.x * kThreads + threadIdx.x, stride = (long long)gridDim.x * kThreads;
+    const bool al = (reinterpret_cast<uintptr_t>(phase) & 15) == 0;
+    const long long n16 = al ? N / 16 : 0;
+    for (long long i = t; i < n16; i += stride) {
+        const ulonglong2 v = reinterpret_cast<const ulonglong2*>(phase)[i];
+        word(2 * i, v.x);
+        word(2 * i + 1, v.y);
     }
-    red[threadIdx.x] = s;
+    for (long long w = 2 * n16 + t; w < (N + 7) / 8; w += stride) word(w, bytes(w));
+#pragma unroll
+    for (int off = 32; off > 0; off >>= 1) s += __shfl_down(s, off, 64);
+    if ((threadIdx.x & 63) == 0) red[threadIdx.x >> 6] = s;
     __syncthreads();
-    for (int w = kThreads / 2; w > 0; w >>= 1) {
-        if ((int)threadIdx.x < w) red[threadIdx.x] += red[threadIdx.x + w];
-        __syncthreads();
+    if (threadIdx.x == 0) part[blockIdx.x] = (red[0] + red[1]) + (red[2] + red[3]);
+}
+
+// cos and sin of 2 pi r / n (0 <= r < n) rounded from about 2^-66 absolute:
+// quadrant and octant in integers, then the Taylor series on [0, pi/4] with the
+// leading terms in double-double arithmetic.
+struct dd {
+    double h, l;
+};
+__device__ __forceinline__ dd two_sum(double a, double b)
+{
+#pragma clang fp contract(off)
+    const double s = a + b, t = s - a;
+    return {s, (a - (s - t)) + (b - t)};
+}
+__device__ __forceinline__ dd dd_mul(dd a, dd b)
+{
+#pragma clang fp contract(off)
+    const double p = a.h * b.h;
+    return {p, fma(a.h, b.h, -p) + (a.h * b.l + a.l * b.h)};
+}
+__device__ __forceinline__ dd dd_add(dd a, dd b)
+{
+#pragma clang fp contract(off)
+    const dd s = two_sum(a.h, b.h);
+    return two_sum(s.h, s.l + a.l + b.l);
+}
+__device__ inline void cos_sin_turn(int r, int n, double* c, double* s)
+{
+#pragma clang fp contract(off)
+    const int quad = (int)(4ll * r / n);
+    int rem = 4 * r - quad * n;  // quarter turn: angle (pi / 2) rem / n
+    const bool swap = 2 * rem > n;
+    if (swap) rem = n - rem;
+    const double qh = (double)rem / n;
+    const dd q = {qh, fma(-qh, (double)n, (double)rem) / n};
+    const dd x = dd_mul(dd{1.5707963267948966, 6.123233995736766e-17}, q), y = dd_mul(x, x);
+    // remaining terms: relative to the series below 2^-12 of its value
+    const double ps = 1.0 / 362880 - y.h * (1.0 / 39916800 - y.h * (1.0 / 6227020800.0 -
+                      y.h * (1.0 / 1307674368000.0 - y.h * (1.0 / 355687428096000.0))));
+    const double pc = 1.0 / 40320 - y.h * (1.0 / 3628800 - y.h * (1.0 / 479001600 -
+                      y.h * (1.0 / 87178291200.0 - y.h * (1.0 / 20922789888000.0))));
+    // 1/3!, 1/5!, 1/7! and 1/2!, 1/4!, 1/6! as double-doubles
+    const dd s3 = {-0.16666666666666666, -9.25185853854297e-18}, s5 = {0.008333333333333333, 1.1564823173178714e-19},
+             s7 = {-0.0001984126984126984, -1.7209558293420705e-22};
+    const dd c4 = {0.041666666666666664, 2.3129646346357427e-18}, c6 = {-0.001388888888888889, 5.300543954373577e-20};
+    const dd yp = {y.h * ps, 0.0}, yc = {y.h * pc, 0.0};
+    dd a = dd_add(s7, yp);
+    a = dd_add(s5, dd_mul(y, a));
+    a = dd_add(s3, dd_mul(y, a));
+    a = dd_add(x, dd_mul(x, dd_mul(y, a)));
+    dd b = dd_add(c6, yc);
+    b = dd_add(c4, dd_mul(y, b));
+    b = dd_add(dd{-0.5, 0.0}, dd_mul(y, b));
+    b = dd_add(dd{1.0, 0.0}, dd_mul(y, b));
+    const double sn = swap ? b.h : a.h, cs = swap ? a.h : b.h;
+    *c = quad == 0 ? cs : quad == 1 ? -sn : quad == 2 ? -cs : sn;
+    *s = quad == 0 ? sn : quad == 1 ? cs : quad == 2 ? -sn : -cs;
+}
+
+// Start of a call: the state's scalars, the phase table and the twiddle tables
+// exp(-2 pi i e / n) of the three axes, all from the kernel's arguments (as
+// copies from host memory they were five transfers and three synchronisations
+// per call).  keep: the basis in the workspace stays.
+constexpr int kInitPhases = 64;  // larger phase tables are copied
+struct InitArgs {
+    int cfg[6];
+    int keep, max_iter, stall, n_lame, n[3];
+    double tol, gnorm, medium[6], E[6], lame[2 * kInitPhases];
+};
+template <typename T>
+__global__ __launch_bounds__(kThreads) void k_init(DevState* __restrict__ st, double* __restrict__ lame,
+                                                   cx<T>* __restrict__ tx, cx<T>* __restrict__ ty,
+                                                   cx<T>* __restrict__ tr, InitArgs a)
+{
+    const int t = threadIdx.x;
+    if (blockIdx.x > 0) {
+        int e = (blockIdx.x - 1) * kThreads + t;
+        cx<T>* tab = tx;
+        int n = a.n[0];
+        if (e >= n) {
+            e -= n;
+            n = a.n[1];
+            tab = ty;
+            if (e >= n) {
+                e -= n;
+                n = a.n[2];
+                tab = tr;
+            }
+        }
+        if (e < n) {
+            double c, s;
+            cos_sin_turn(e, n, &c, &s);
+            tab[e] = cx<T>{(T)c, (T)-s};
+        }
+        return;
     }
-    if (threadIdx.x == 0) part[blockIdx.x] = red[0];
+    for (int i = t; i < 512; i += kThreads) lame[i] = i < a.n_lame ? a.lame[i] : 0.0;
+    if (!a.keep) {
+        for (int i = t; i < kMaxP; i += kThreads) {
+            st->z[i] = st->zeta[i] = st->d[i] = 0.0;
+            for (int q = 0; q < 4; ++q) st->zeta_ring[q][i] = 0.0;
+        }
+    }
+    if (t < 6) {
+        st->cfg[t] = a.cfg[t];
+        st->medium[t] = a.medium[t];
+        st->E[t] = a.E[t];
+        st->Ezero[t] = 0.0;
+    }
+    if (t == 0) {
+        st->magic = kStateMagic;
+        st->done = 0;
+        st->status = 1;
+        st->iters = 0;
+        st->max_iter = a.max_iter;
+        if (!a.keep) {
+            st->p = 0;
+            st->singular = 0;
+        }
+        st->tol = a.tol;
+        st->gnorm = a.gnorm;
+        st->err0 = 0.0;
+        st->err = 0.0;
+        st->best_err = 1e300;
+        st->best_it = 0;
+        st->stall_window = a.stall;
+    }
+}
+
+__global__ void k_set_E(DevState* __restrict__ st, InitArgs a)
+{
+    if (threadIdx.x < 6) st->E[threadIdx.x] = a.E[threadIdx.x];
 }
 
 // Clear the stop flags and the step counter (a fresh map evaluation).

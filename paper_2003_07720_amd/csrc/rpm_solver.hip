@@ -456,6 +456,9 @@ struct Ctx {
     double alpha = 2.0, beta = 2.0;
     Prof prof;
     bool hip_error = false;
+    bool resident = false;  // prepared by an earlier stage of this call: its basis (p_resident columns) is this call's
+    int p_resident = 0;
+    bool keyed = false;     // the workspace holds the checksum of this phase map
     // FP32 fields: the FP64 pipeline in the same workspace, which evaluates
     // the Jacobian-vector products of H and the compatible projection of new
     // basis columns (null for FP64 fields)
@@ -759,15 +762,24 @@ void reduce_cols(Ctx<T>& c, const double* part, int G, long long bs, long long c
     k_reduce_cols<<<m, kThreads, 0, c.s>>>(part, G, bs, cs, out);
 }
 
-// Initialise or re-validate the workspace header; uploads the tables.
+// Checksum of the phase map for the reuse key of the basis, before its first column.
+template <typename T>
+void store_key(Ctx<T>& c)
+{
+    if (c.keyed) return;
+    k_phase_sum<<<kSumBlocks, kThreads, 0, c.s>>>(c.phase, c.sh.g.N, c.st->key[0]);
+    c.keyed = true;
+}
+
+// Initialise or re-validate the workspace header for mean strain E; writes the
+// tables.  Only a call that asks for a basis left by an earlier call reads the
+// header back (and waits); everything else is enqueued.
 template <typename T>
 rpm_status prepare(Ctx<T>& c, const rpm_problem* pr, const rpm_options* o, bool want_reuse, int* p_io,
-                   double tol, double gnorm = 1.0, int stall = 0)
+                   double tol, const double* E, double gnorm = 1.0, int stall = 0)
 {
     const Geo& g = c.sh.g;
-    DevState hs;
-    if (hipMemcpyAsync(&hs, c.st, sizeof(DevState), hipMemcpyDeviceToHost, c.s) != hipSuccess) return RPM_E_HIP;
-    if (hipStreamSynchronize(c.s) != hipSuccess) return RPM_E_HIP;
+    InitArgs a;
     const int cfg[6] = {g.nx, g.ny, g.nz, o->precision, c.pmax, o->map};
     // the basis holds the linear part of the map: it depends on the reference
     // medium, the polarization parameters and the phase table (FNV-1a over
@@ -782,70 +794,67 @@ rpm_status prepare(Ctx<T>& c, const rpm_problem* pr, const rpm_options* o, bool 
         }
     }
     const bool pol = o->map == RPM_MAP_POLARIZATION;
-    // and on the phase map: a device checksum (wrapping integer sums)
-    constexpr int kSumBlocks = 64;
-    unsigned long long* psum = reinterpret_cast<unsigned long long*>(c.pg());
-    k_phase_sum<<<kSumBlocks, kThreads, 0, c.s>>>(c.phase, g.N, psum);
-    unsigned long long parts[kSumBlocks];
-    if (hipMemcpyAsync(parts, psum, sizeof(parts), hipMemcpyDeviceToHost, c.s) != hipSuccess) return RPM_E_HIP;
-    if (hipStreamSynchronize(c.s) != hipSuccess) return RPM_E_HIP;
-    unsigned long long pk = 0;
-    for (int b = 0; b < kSumBlocks; ++b) pk += parts[b];
-    const double medium[8] = {c.lam0, c.mu0, pol ? o->alpha : 0.0, pol ? o->beta : 0.0,
-                              (double)(uint32_t)(h >> 32), (double)(uint32_t)h, (double)(uint32_t)(pk >> 32),
-                              (double)(uint32_t)pk};
-    bool same = hs.magic == kStateMagic && std::memcmp(hs.cfg, cfg, sizeof(cfg)) == 0 &&
-                std::memcmp(hs.medium, medium, sizeof(medium)) == 0;
-    if (!(same && want_reuse)) {
-        std::memset(&hs, 0, sizeof(hs));
-        hs.magic = kStateMagic;
-        std::memcpy(hs.cfg, cfg, sizeof(cfg));
-        std::memcpy(hs.medium, medium, sizeof(medium));
-        hs.p = 0;
+    const double medium[6] = {c.lam0, c.mu0, pol ? o->alpha : 0.0, pol ? o->beta : 0.0,
+                              (double)(uint32_t)(h >> 32), (double)(uint32_t)h};
+    int p = 0;
+    bool keep = false;
+    if (want_reuse && c.resident) {
+        // a later stage of the same call: the basis it left
+        p = c.p_resident;
+        keep = true;
+    } else if (want_reuse && c.pmax > 0) {
+        // and on the phase map: a device checksum (wrapping integer sums)
+        k_phase_sum<<<kSumBlocks, kThreads, 0, c.s>>>(c.phase, g.N, c.st->key[1]);
+        DevHead hs;
+        unsigned long long key[2][kSumBlocks];
+        if (hipMemcpyAsync(&hs, c.st, sizeof(DevHead), hipMemcpyDeviceToHost, c.s) != hipSuccess) return RPM_E_HIP;
+        if (hipMemcpyAsync(key, &c.st->key[0][0], sizeof(key), hipMemcpyDeviceToHost, c.s) != hipSuccess) return RPM_E_HIP;
+        if (hipStreamSynchronize(c.s) != hipSuccess) return RPM_E_HIP;
+        unsigned long long sum[2] = {0, 0};
+        for (int q = 0; q < 2; ++q)
+            for (int b = 0; b < kSumBlocks; ++b) sum[q] += key[q][b];
+        keep = hs.magic == kStateMagic && std::memcmp(hs.cfg, cfg, sizeof(cfg)) == 0 &&
+               std::memcmp(hs.medium, medium, sizeof(medium)) == 0 && hs.p > 0 && hs.p <= c.pmax &&
+               sum[0] == sum[1];
+        if (keep) p = hs.p;
     }
-    hs.done = 0;
-    hs.status = 1;
-    hs.iters = 0;
-    hs.max_iter = o->max_iter;
-    hs.tol = tol;
-    hs.gnorm = gnorm;
-    hs.err0 = 0.0;
-    hs.err = 0.0;
-    hs.best_err = 1e300;
-    hs.best_it = 0;
-    hs.stall_window = stall;
-    for (int i = 0; i < 6; ++i) hs.Ezero[i] = 0.0;
-    *p_io = hs.p;
-    // twiddles exp(-2 pi i e / n) computed in long double on the host; the
-    // host buffers stay alive until the stream synchronisation below
-    std::vector<cx<T>> tabs[3];
-    auto tw = [&](int slot, int n, size_t off) -> bool {
-        std::vector<cx<T>>& t = tabs[slot];
-        t.resize(n);
-        for (int e = 0; e < n; ++e) {
-            const long double ang = -2.0L * 3.141592653589793238462643383279502884L * (long double)e / (long double)n;
-            t[e] = cx<T>{(T)std::cos(ang), (T)std::sin(ang)};
-        }
-        return hipMemcpyAsync(c.ws + off, t.data(), sizeof(cx<T>) * n, hipMemcpyHostToDevice, c.s) == hipSuccess;
-    };
-    if (!tw(0, g.nx, c.L.twx) || !tw(1, g.ny, c.L.twy) || !tw(2, g.two_d ? g.ny : g.nz, c.L.twr)) return RPM_E_HIP;
-    std::vector<double> lt(512, 0.0);
-    for (int i = 0; i < pr->n_phases; ++i) {
-        lt[2 * i] = pr->lame[2 * i];
-        lt[2 * i + 1] = pr->lame[2 * i + 1];
+    c.keyed = keep;
+    c.resident = true;
+    c.p_resident = p;
+    *p_io = p;
+    std::memcpy(a.cfg, cfg, sizeof(cfg));
+    std::memcpy(a.medium, medium, sizeof(medium));
+    a.keep = keep ? 1 : 0;
+    a.max_iter = o->max_iter;
+    a.stall = stall;
+    a.tol = tol;
+    a.gnorm = gnorm;
+    a.n[0] = g.nx;
+    a.n[1] = g.ny;
+    a.n[2] = g.two_d ? g.ny : g.nz;
+    for (int i = 0; i < 6; ++i) a.E[i] = E ? E[i] : 0.0;
+    a.n_lame = 2 * std::min(pr->n_phases, kInitPhases);
+    std::memcpy(a.lame, pr->lame, sizeof(double) * a.n_lame);
+    const int entries = a.n[0] + a.n[1] + a.n[2];
+    k_init<T><<<1 + (entries + kThreads - 1) / kThreads, kThreads, 0, c.s>>>(c.st, c.lame(), c.twx(), c.twy(),
+                                                                           c.twr(), a);
+    if (pr->n_phases > kInitPhases) {
+        // the caller's table may go when the call returns early: wait for the copy
+        if (hipMemcpyAsync(c.lame(), pr->lame, sizeof(double) * 2 * pr->n_phases, hipMemcpyHostToDevice, c.s) !=
+                hipSuccess ||
+            hipStreamSynchronize(c.s) != hipSuccess)
+            return RPM_E_HIP;
     }
-    if (hipMemcpyAsync(c.lame(), lt.data(), sizeof(double) * 512, hipMemcpyHostToDevice, c.s) != hipSuccess)
-        return RPM_E_HIP;
-    if (hipMemcpyAsync(c.st, &hs, sizeof(DevState), hipMemcpyHostToDevice, c.s) != hipSuccess) return RPM_E_HIP;
-    if (hipStreamSynchronize(c.s) != hipSuccess) return RPM_E_HIP;
-    return RPM_OK;
+    c.check_launch();
+    return c.hip_error ? RPM_E_HIP : RPM_OK;
 }
 
 template <typename T>
 void set_E(Ctx<T>& c, const double E[6])
 {
-    hipMemcpyAsync(c.st->E, E, sizeof(double) * 6, hipMemcpyHostToDevice, c.s);
-    hipStreamSynchronize(c.s);
+    InitArgs a{};
+    std::memcpy(a.E, E, sizeof(a.E));
+    k_set_E<<<1, 64, 0, c.s>>>(c.st, a);
 }
 
 // Compatible projection of a T field in place: v <- Gamma0 * (C0 : v), k != 0.
@@ -1053,7 +1062,7 @@ int grow_basis(Ctx<T>& c, int it, int nq, int& p, const rpm_options* o, int grow
 }
 
 template <typename T>
-void stats_fill(Ctx<T>& c, rpm_stats* st, const DevState& hs, int jvps, int growth, int p, double secs,
+void stats_fill(Ctx<T>& c, rpm_stats* st, const DevHead& hs, int jvps, int growth, int p, double secs,
                 const std::vector<int>& decisions)
 {
     if (!st) return;
@@ -1108,7 +1117,7 @@ struct StepGraphs {
 template <typename T>
 struct SolveOut {
     const T* final_it = nullptr;  // the iterate whose error was evaluated last
-    DevState hs;
+    DevHead hs;
     int jvps = 0, growth = 0, p = 0;
     std::vector<int> decisions;
 };
@@ -1120,9 +1129,8 @@ rpm_status run_solve(Ctx<T>& c, const rpm_problem* pr, const rpm_options* o, con
     const Geo& g = c.sh.g;
     const long long N = g.N;
     int p = 0;
-    rpm_status rs = prepare(c, pr, o, sp.reuse, &p, sp.tol, sp.gnorm, sp.stall);
+    rpm_status rs = prepare(c, pr, o, sp.reuse, &p, sp.tol, sp.E, sp.gnorm, sp.stall);
     if (rs != RPM_OK) return rs;
-    set_E(c, sp.E);
     const bool rpm = o->scheme == RPM_SCHEME_RPM && c.pmax > 0;
     const int* done = &c.st->done;
     double* pinc = sp.err_mode == 1 ? c.template at<double>(c.L.pinc) : nullptr;
@@ -1155,6 +1163,7 @@ rpm_status run_solve(Ctx<T>& c, const rpm_problem* pr, const rpm_options* o, con
             if (at_growth) {
                 int want = 0;
                 const int p_before = p;
+                store_key(c);
                 const int added = grow_basis(c, it, nq, p, o, (int)so.decisions.size(), &want, &jvps);
                 if (added < 0) return RPM_E_HIP;
                 so.decisions.push_back(want);
@@ -1209,7 +1218,8 @@ rpm_status run_solve(Ctx<T>& c, const rpm_problem* pr, const rpm_options* o, con
         ++nu;
         ++nq;
     }
-    if (!sync_read(c, &so.hs, c.st, sizeof(DevState))) return RPM_E_HIP;
+    c.p_resident = p;
+    if (!sync_read(c, &so.hs, c.st, sizeof(DevHead))) return RPM_E_HIP;
     const int itf = std::max(so.hs.iters, 1);
     // the input of the last map application: eps while a basis recombined it,
     // the previous xi otherwise (the basis only grows between executed steps)
@@ -1246,12 +1256,12 @@ void sub64_init(Ctx<double>& c64, Ctx<float>& c, const rpm_options* o)
 }
 
 // FP64 map application on c64.eps(): xi64 in ring(1), error and sigma_hat(0) in hs.
-rpm_status eval64(Ctx<double>& c64, DevState& hs)
+rpm_status eval64(Ctx<double>& c64, DevHead& hs)
 {
     k_reset_state<<<1, 1, 0, c64.s>>>(c64.st);
     run_F<double>(c64, c64.eps(), 0, nullptr, c64.eps(), c64.ring(1), OUT_XI, 0, DC_MEAN, c64.st->E, nullptr);
     reduce_and_finalize(c64, 0, 1, 0, true, nullptr);
-    if (!sync_read(c64, &hs, c64.st, sizeof(DevState))) return RPM_E_HIP;
+    if (!sync_read(c64, &hs, c64.st, sizeof(DevHead))) return RPM_E_HIP;
     return RPM_OK;
 }
 
@@ -1271,14 +1281,12 @@ rpm_status finish_solve(Ctx<T>& c, Ctx<double>& c64, const rpm_problem* pr, cons
     const bool refine = sizeof(T) == 4 && o->refine > 0;
     const int stall = refine ? o->stall_window : 0;
     rpm_status rs = RPM_OK;
-    const DevState hs_main = so.hs;
+    const DevHead hs_main = so.hs;
     if (st && st->history && st->history_cap > 0) {  // before correction solves reuse the buffer
         const int n = std::min(st->history_cap, hs_main.iters);
-        if (n > 0) {
+        if (n > 0)
             hipMemcpyAsync(st->history, c.template at<double>(c.L.hist), sizeof(double) * n, hipMemcpyDeviceToHost,
                            c.s);
-            hipStreamSynchronize(c.s);
-        }
     }
     double sav[6];
     for (int i = 0; i < 6; ++i) sav[i] = so.hs.sig_hat0[i] / (double)N;
@@ -1288,7 +1296,7 @@ rpm_status finish_solve(Ctx<T>& c, Ctx<double>& c64, const rpm_problem* pr, cons
     bool rounded = false;  // outputs come from the FP64 field rounded to T
     if constexpr (sizeof(T) == 4) {
         k_convert<T, double><<<gb, 256, 0, c.s>>>(efin, c64.eps(), 1.0, nel);
-        DevState h64;
+        DevHead h64;
         if ((rs = eval64(c64, h64)) != RPM_OK) return rs;
         res64 = h64.err;
         for (int i = 0; i < 6; ++i) sav[i] = h64.sig_hat0[i] / (double)N;
@@ -1381,9 +1389,8 @@ rpm_status solve_full(Ctx<T>& c, const rpm_problem* pr, const double E[6], const
     if constexpr (sizeof(T) == 4) {
         sub64_init(c64, c, o);
         int p64 = 0;
-        rs = prepare(c64, pr, o, false, &p64, o->tol);
+        rs = prepare(c64, pr, o, false, &p64, o->tol, E);
         if (rs != RPM_OK) return rs;
-        set_E(c64, E);
         c.sub = &c64;
     }
     Spec<T> sp{E, eps0, false, nullptr, 0, stage_tol, 1.0, reuse, stall};
@@ -1490,12 +1497,11 @@ rpm_status apply_typed(const rpm_problem* pr, const double E[6], const rpm_optio
     rpm_status rs = ctx_init(c, pr, o, ws, ws_bytes, stream, map_only);
     if (rs != RPM_OK) return rs;
     int p = 0;
-    rs = prepare(c, pr, o, false, &p, o->tol);
+    rs = prepare(c, pr, o, false, &p, o->tol, E);
     if (rs != RPM_OK) return rs;
-    set_E(c, E);
     run_F<T>(c, (const T*)eps, 0, nullptr, (const T*)eps, (T*)xi, OUT_XI, 0, DC_MEAN, c.st->E, nullptr);
     reduce_and_finalize(c, 0, 1, 0, true, nullptr);
-    DevState hs;
+    DevHead hs;
     if (!sync_read(c, &hs, c.st, sizeof(hs))) return RPM_E_HIP;
     if (err) *err = hs.err;
     if (sig_avg)
@@ -1516,10 +1522,9 @@ rpm_status tune_typed(const rpm_problem* pr, const rpm_options* o, int reps, rpm
     rpm_status rs = ctx_init(c, pr, &ob, ws, ws_bytes, stream);
     if (rs != RPM_OK) return rs;
     int p = 0;
-    rs = prepare(c, pr, &ob, false, &p, ob.tol);
-    if (rs != RPM_OK) return rs;
     const double E[6] = {0.01, 0.0, 0.0, 0.0, 0.0, 0.0};
-    set_E(c, E);
+    rs = prepare(c, pr, &ob, false, &p, ob.tol, E);
+    if (rs != RPM_OK) return rs;
     const Geo& g0 = c.sh.g;
     k_fill_uniform<T><<<(int)((6 * g0.N + 255) / 256), 256, 0, c.s>>>(c.eps(), c.st->E, g0.N);
     hipEvent_t e0 = nullptr, e1 = nullptr;
@@ -1623,7 +1628,7 @@ rpm_status seed_typed(const rpm_problem* pr, const rpm_options* o, const void* V
     if (rs != RPM_OK) return rs;
     if (c.pmax == 0) return RPM_E_INVALID;
     int p = 0;
-    rs = prepare(c, pr, o, o->reuse_basis != 0, &p, o->tol);
+    rs = prepare(c, pr, o, o->reuse_basis != 0, &p, o->tol, nullptr);
     if (rs != RPM_OK) return rs;
     const long long N = c.sh.g.N;
     const long long nel = 6 * N;
@@ -1637,11 +1642,12 @@ rpm_status seed_typed(const rpm_problem* pr, const rpm_options* o, const void* V
     if constexpr (sizeof(T) == 4) {
         sub64_init(c64, c, o);
         int p64 = 0;
-        rs = prepare(c64, pr, o, false, &p64, o->tol);
+        rs = prepare(c64, pr, o, false, &p64, o->tol, nullptr);
         if (rs != RPM_OK) return rs;
         c.sub = &c64;
     }
     int added = 0, jvps = 0;
+    if (p0 > 0) store_key(c);
     for (int k = 0; k < p0 && p < c.pmax; ++k) {
         const T* v = reinterpret_cast<const T*>(V) + (long long)k * nel;
         k_convert<T, double><<<gb, 256, 0, c.s>>>(v, D1, 1.0, nel);
@@ -1752,8 +1758,8 @@ struct StateHead {
 template <typename T>
 bool read_head(Ctx<T>& c, StateHead& h)
 {
-    DevState hs;
-    const size_t n = offsetof(DevState, err) + sizeof(double);
+    DevHead hs;
+    const size_t n = offsetof(DevHead, err) + sizeof(double);
     if (hipMemcpyAsync(&hs, c.st, n, hipMemcpyDeviceToHost, c.s) != hipSuccess) return false;
     if (hipStreamSynchronize(c.s) != hipSuccess) return false;
     h.done = hs.done;
@@ -1800,7 +1806,7 @@ rpm_status eff_batched(const rpm_problem* pr, const rpm_options* o, double* C, r
     if constexpr (sizeof(T) == 4) {
         sub64_init(c64, c, o);
         int p64 = 0;
-        rs = prepare(c64, pr, o, false, &p64, o->tol);
+        rs = prepare(c64, pr, o, false, &p64, o->tol, nullptr);
         if (rs != RPM_OK) return rs;
         c.sub = &c64;
     }
@@ -1813,10 +1819,9 @@ rpm_status eff_batched(const rpm_problem* pr, const rpm_options* o, double* C, r
         for (int i = 0; i < 6; ++i) Ec[f][i] = 0.0;
         Ec[f][j] = j < 3 ? 1.0 : 0.5;
         int pf = 0;
-        rs = prepare(cx[f], pr, o, f == 0 && o->reuse_basis != 0, &pf, stage_tol, 1.0, stall);
+        rs = prepare(cx[f], pr, o, f == 0 && o->reuse_basis != 0, &pf, stage_tol, Ec[f], 1.0, stall);
         if (rs != RPM_OK) return rs;
         if (f == 0) p = pf;
-        set_E(cx[f], Ec[f]);
     }
     // a carried basis (case 0's state) serves every case
     for (int f = 1; f < nb && p > 0; ++f) k_copy_basis_state<<<1, kThreads, 0, c.s>>>(cx[f].st, cx[0].st);
@@ -1863,6 +1868,7 @@ rpm_status eff_batched(const rpm_problem* pr, const rpm_options* o, double* C, r
             if (all) break;
             if (at_growth) {
                 const int p_before = p;
+                store_key(cx[0]);  // the state a later call reads
                 // batch_cases 1: the differences of the case with the largest
                 // error; 2: of every case still iterating, largest error first
                 int order[kMaxCases], no = 0;
@@ -1941,7 +1947,8 @@ rpm_status eff_batched(const rpm_problem* pr, const rpm_options* o, double* C, r
     rpm_status worst = RPM_OK;
     for (int f = 0; f < nb; ++f) {
         SolveOut<T> so;
-        if (!sync_read(cx[f], &so.hs, cx[f].st, sizeof(DevState))) return RPM_E_HIP;
+        cx[f].p_resident = p;
+        if (!sync_read(cx[f], &so.hs, cx[f].st, sizeof(DevHead))) return RPM_E_HIP;
         const int itf = std::max(so.hs.iters, 1);
         so.final_it = (itf == 1 || p_end[f] > 0) ? cx[f].eps() : cx[f].ring(itf - 1);
         so.jvps = f == 0 ? jvps : 0;
@@ -2230,8 +2237,8 @@ rpm_status rpm_fft_solve_stress(const rpm_problem* pr, const double Sigma[6], co
 rpm_status rpm_workspace_basis_dim(const void* workspace, size_t ws_bytes, int32_t* p, void* hip_stream)
 {
     if (!workspace || !p || ws_bytes < sizeof(DevState)) return RPM_E_INVALID;
-    DevState hs;
-    if (hipMemcpyAsync(&hs, workspace, sizeof(DevState), hipMemcpyDeviceToHost, (hipStream_t)hip_stream) !=
+    DevHead hs;
+    if (hipMemcpyAsync(&hs, workspace, sizeof(DevHead), hipMemcpyDeviceToHost, (hipStream_t)hip_stream) !=
         hipSuccess)
         return RPM_E_HIP;
     if (hipStreamSynchronize((hipStream_t)hip_stream) != hipSuccess) return RPM_E_HIP;
