@@ -4,7 +4,11 @@ import subprocess
 
 HERE = os.path.dirname(os.path.abspath(__file__))
 ROOT = os.path.dirname(HERE)
-SRCS = [os.path.join(HERE, "csrc", "rpm_solver.hip"), os.path.join(HERE, "csrc", "rpm_fno.hip")]
+CSRC = os.path.join(HERE, "csrc")
+# (object, source, defines): the fixed-length pencil passes compile in groups
+# of lengths side by side
+JOBS = [("rpm_solver", "rpm_solver.hip", ["-DRPM_PENCIL_SEPARATE"]), ("rpm_fno", "rpm_fno.hip", [])] + [
+    (f"rpm_pencil{k}", "rpm_pencil.hip", [f"-DRPM_PENCIL_GROUP={k}"]) for k in range(6)]
 OUT = os.path.join(HERE, "librpmfft.so")
 
 HIPCC_FLAGS = [
@@ -17,10 +21,10 @@ HIPCC_FLAGS = [
 
 def build(verbose=False):
     inc = ["-I", os.path.join(ROOT, "include")]
-    objs = [os.path.join(HERE, "csrc", os.path.basename(s).replace(".hip", ".o")) for s in SRCS]
+    objs = [os.path.join(CSRC, name + ".o") for name, _, _ in JOBS]
     procs = []
-    for src, obj in zip(SRCS, objs):
-        cmd = ["hipcc"] + HIPCC_FLAGS + inc + ["-c", "-o", obj, src]
+    for (_, src, defs), obj in zip(JOBS, objs):
+        cmd = ["hipcc"] + HIPCC_FLAGS + defs + inc + ["-c", "-o", obj, os.path.join(CSRC, src)]
         if verbose:
             print(" ".join(cmd), flush=True)
         procs.append(subprocess.Popen(cmd, stdout=subprocess.PIPE, stderr=subprocess.PIPE, text=True))

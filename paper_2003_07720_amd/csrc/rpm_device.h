@@ -222,59 +222,13 @@ __device__ __forceinline__ void fft_stage(const cx<T>* __restrict__ src, cx<T>* 
     }
 }
 
-// The same stage with the length and the stage position fixed at compile time
-// (power-of-two lengths): index arithmetic reduces to shifts and masks.
-template <typename T, int R, int D, int N, int NS, int NT>
-__device__ __forceinline__ void fft_stage_ct(const cx<T>* __restrict__ src, cx<T>* __restrict__ dst, int nseq,
-                                             int ss, const cx<T>* __restrict__ tw, int tid)
-{
-    constexpr int nb = N / R;
-    constexpr int tws = N / (NS * R);
-    const int total = nb * nseq;
-    for (int g = tid; g < total; g += NT) {
-        const int s = g / nb;
-        const int j = g & (nb - 1);
-        const cx<T>* in = src + s * ss;
-        cx<T>* out = dst + s * ss;
-        cx<T> v[R];
-#pragma unroll
-        for (int q = 0; q < R; ++q) v[q] = in[lpad(j + q * nb)];
-        const int k = j & (NS - 1);
-        if constexpr (NS > 1) {
-#pragma unroll
-            for (int q = 1; q < R; ++q) {
-                cx<T> w = tw[q * k * tws];
-                if (D > 0) w.y = -w.y;
-                v[q] = cmul(v[q], w);
-            }
-        }
-        dftR<T, R, D>(v);
-        const int o = (j - k) * R + k;
-#pragma unroll
-        for (int q = 0; q < R; ++q) out[lpad(o + q * NS)] = v[q];
-    }
-}
-
 // Radix sequence of a power-of-two length: radix 16 while possible, then one
 // stage of 8, 4 or 2 (the host plan builds the same sequence).
 constexpr int ct_log2(int n) { return n <= 1 ? 0 : 1 + ct_log2(n / 2); }
 constexpr int ct_nst(int n) { return ct_log2(n) / 4 + (ct_log2(n) % 4 ? 1 : 0); }
 constexpr int ct_rad(int n, int st) { return st < ct_log2(n) / 4 ? 16 : (1 << (ct_log2(n) % 4)); }
 
-template <typename T, int D, int N, int ST, int NS, int NT>
-__device__ __forceinline__ cx<T>* ct_stages(cx<T>* src, cx<T>* dst, int nseq, int ss, const cx<T>* tw, int tid)
-{
-    if constexpr (ST == ct_nst(N)) {
-        return src;
-    } else {
-        constexpr int R = ct_rad(N, ST);
-        fft_stage_ct<T, R, D, N, NS, NT>(src, dst, nseq, ss, tw, tid);
-        __syncthreads();
-        return ct_stages<T, D, N, ST + 1, NS * R, NT>(dst, src, nseq, ss, tw, tid);
-    }
-}
-
-// In-place variant of the compile-time stages for at most one butterfly per
+// The stages of a power-of-two length N in place, at most one butterfly per
 // thread (nseq * N / R <= NT at every stage): each thread reads its inputs,
 // the block synchronises, then every thread writes its outputs into the same
 // rows.  Half the LDS of the ping-pong form (more resident blocks).
@@ -321,10 +275,8 @@ __device__ __forceinline__ void ct_stages_ip(cx<T>* buf, int nseq, int ss, const
 // Caller must __syncthreads() after filling a.  Returns the buffer that holds
 // the natural-order result; all threads are synchronised on return.
 template <typename T, int D, int NT = kThreads>
-__device__ cx<T>* lds_fft(cx<T>* a, cx<T>* b, const Plan& pl, int nseq, int ss, const cx<T>* tw,
-                         int tid = threadIdx.x)
+__device__ cx<T>* lds_fft(cx<T>* a, cx<T>* b, const Plan& pl, int nseq, int ss, const cx<T>* tw)
 {
-    if (pl.n == 128) return ct_stages<T, D, 128, 0, 1, NT>(a, b, nseq, ss, tw, tid);
     int Ns = 1;
     cx<T>* src = a;
     cx<T>* dst = b;

@@ -17,7 +17,8 @@
 // and, in an RPM iteration, two streams over the basis Z: the recombination
 // eps = xi_prev + Z d before the map (k_recombine_split for FP32 fields; for
 // FP64 fields on 128-point rows inside xfwd, else k_recombine) and the
-// projections Z^T xi after it (k_gdots_split / k_gdots, FP64 accumulation).
+// projections Z^T xi after it (k_gdots_split / k_gdots, FP64 accumulation).  The kernels of this file take any 2,3-smooth length;
+// rpm_pencil.h has the passes of the usual ones.
 //
 // In 2-D (nz == 1) the y passes are skipped and gamma runs along y on S1.
 // The k = 0 term of t is N(<eps> - E), so xi = eps - F^-1[Gamma sigma_hat]
@@ -44,21 +45,6 @@ __device__ __forceinline__ double2 nt_load(const double2* p)
     const nt_d2 t = __builtin_nontemporal_load(reinterpret_cast<const nt_d2*>(p));
     return make_double2(t.x, t.y);
 }
-
-// waves per SIMD the compiler budgets registers for: the in-place gamma pass
-// (five resident blocks per CU), and the x pass that recombines eps = xi + Z d
-// on the way in (four; with 8 basis columns in flight per lane it needs ~114
-// VGPRs, and 16 columns spill at four waves and drop to three); RC_GROUP is
-// the basis columns in flight per lane there
-#ifndef RPM_GIP_WPE
-#define RPM_GIP_WPE 5
-#endif
-#ifndef RPM_RC_GROUP
-#define RPM_RC_GROUP 8
-#endif
-#ifndef RPM_RC_WPE
-#define RPM_RC_WPE 4
-#endif
 
 struct Geo {
     int nx, ny, nz, nh;    // nh = nx/2 + 1 (half spectrum along x)
@@ -151,14 +137,14 @@ struct MaxV<double> { static constexpr int v = 4; };
 // x-forward: constitutive law + R2C FFT along x (two real components per
 // complex transform), per-block <eps> partial sums.  POL: eps is transformed
 // too (components 6..11 of S1), for the polarization iteration.
-// RC (RPM iterations, VEC only): the strain is recombined on the way in,
+// RC (RPM iterations, VEC and 128-point rows only): the strain is recombined on the way in,
 // eps = xin + sum_{j < p} d_j Z_j, in the order and rounding of k_recombine,
 // and stored to eps_out (the x-inverse pass reads it); the tile's basis
 // slices stream through eight columns at a time.
 // grid: nz * (ny / ty) blocks.  LDS: 2 * ty * lrow(nx) + nx complex + reduction.
 // ---------------------------------------------------------------------------
-template <typename T, bool VEC, bool POL, int NT, bool IP, bool RC = false>
-__global__ __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(sizeof(T) == 4 ? (RC ? RPM_RC_WPE : 4) : 2))) void k_xfwd(const T* __restrict__ xin, const uint8_t* __restrict__ phase,
+template <typename T, bool VEC, bool POL, bool RC = false>
+__global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(sizeof(T) == 4 ? 4 : 2))) void k_xfwd(const T* __restrict__ xin, const uint8_t* __restrict__ phase,
                                                    const double* __restrict__ lame, int use_ref, double lam0,
                                                    double mu0, cx<T>* __restrict__ S1,
                                                    double* __restrict__ part_mean, Geo g, Plan px,
@@ -170,13 +156,14 @@ __global__ __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(sizeof(T) ==
     static_assert(!RC || VEC, "recombination on the way in needs 16-byte runs");
     if (done && *done) return;
     extern __shared__ __align__(16) unsigned char smem[];
-    constexpr int MV = MaxV<T>::v * kThreads / NT;  // voxels per thread
+    constexpr int NT = kThreads, MV = MaxV<T>::v;  // voxels per thread
+    constexpr bool IP = RC;  // 128-point transforms in place, one LDS buffer
     const int nx = g.nx, ty = g.ty, ss = lrow(nx);
     cx<T>* A = reinterpret_cast<cx<T>*>(smem);
     cx<T>* B = A + ty * ss;
-    cx<T>* tw = IP ? B : B + ty * ss;  // IP: one buffer, transforms in place
+    cx<T>* tw = IP ? B : B + ty * ss;
     double* red = reinterpret_cast<double*>(tw + nx);
-    constexpr int RG = RPM_RC_GROUP;  // basis columns in flight per thread
+    constexpr int RG = 8;  // basis columns in flight per thread
     __shared__ T dj[RC ? kMaxP + RG : 1];
     if constexpr (RC) {
         for (int j = threadIdx.x; j < kMaxP + RG; j += NT) dj[j] = j < p ? (T)dco[j] : T(0);
@@ -365,8 +352,8 @@ __global__ __launch_bounds__(kThreads) void k_yfwd(const cx<T>* __restrict__ S1,
 // Software-pipelined y passes: a persistent grid walks the tiles; each thread
 // keeps its share of the next tile in registers (loads in flight during the
 // current tile's LDS transform and stores).  PT bounds tz * ny / kThreads.
-template <typename T, int D, int PT, bool IP>
-__global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(sizeof(T) == 4 ? (IP ? 5 : 4) : 2))) void k_ypipe(const cx<T>* __restrict__ Sin, cx<T>* __restrict__ Sout, Geo g,
+template <typename T, int D, int PT>
+__global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(sizeof(T) == 4 ? 4 : 2))) void k_ypipe(const cx<T>* __restrict__ Sin, cx<T>* __restrict__ Sout, Geo g,
                                                     Plan py, const cx<T>* __restrict__ twy, int ntiles,
                                                     const int* __restrict__ done)
 {
@@ -375,7 +362,7 @@ __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(sizeof
     const int ny = g.ny, tz = g.tz, ss = lrow(ny);
     cx<T>* A = reinterpret_cast<cx<T>*>(smem);
     cx<T>* B = A + tz * ss;
-    cx<T>* tw = IP ? B : B + tz * ss;  // IP: one buffer, transforms in place
+    cx<T>* tw = B + tz * ss;
     const int nzt = g.nz / tz;
     const int nel = tz * ny;
     for (int i = threadIdx.x; i < ny; i += kThreads) tw[i] = twy[i];
@@ -425,13 +412,7 @@ __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(sizeof
         __syncthreads();
         const int tn = t + gridDim.x;
         if (tn < ntiles) load(tn);  // next tile in flight during the transform
-        const cx<T>* R;
-        if constexpr (IP) {
-            ct_stages_ip<T, D, 128, 0, 1, kThreads>(A, tz, ss, tw, threadIdx.x);
-            R = A;
-        } else {
-            R = lds_fft<T, D>(A, B, py, tz, ss, tw);
-        }
+        const cx<T>* R = lds_fft<T, D>(A, B, py, tz, ss, tw);
         int b = t;
         const int zt = b % nzt;
         b /= nzt;
@@ -663,25 +644,24 @@ __device__ __forceinline__ void wave_vector(int kx, int ky, int kz, const Geo& g
 // 3-D: rows along z of S2 (pencil = ky * nh + kx).  2-D: rows along y of S1
 // (pencil = kx, kz = 0).  grid: ceil(npencils / np).
 // ---------------------------------------------------------------------------
-// Green operator at one frequency of a gamma tile: component c of the pencil
-// sits in row c * nrs + r of R (element i).  Overwrites components 0..5 with
-// t_hat (the k = 0 entry as described above) and returns the frequency's share
-// of the equilibrium error.
+// Green operator at one frequency of a gamma tile: component c sits at
+// R[c * cs].  Overwrites components 0..5 with t_hat (the k = 0 entry as
+// described above) and returns the frequency's share of the equilibrium error.
 template <typename T, bool POL>
-__device__ __forceinline__ double gamma_point(cx<T>* R, int ss, int nrs, int r, int i, int kx, int ky, int kz,
-                                              const Geo& g, double lam0, double mu0, double alpha, double beta,
-                                              int dc_mode, const double* __restrict__ E, const double* dc_mean,
-                                              DevState* __restrict__ st)
+__device__ __forceinline__ double gamma_point_at(cx<T>* R, int cs, int kx, int ky, int kz, const Geo& g,
+                                                 double lam0, double mu0, double alpha, double beta, int dc_mode,
+                                                 const double* __restrict__ E, const double* dc_mean,
+                                                 DevState* __restrict__ st)
 {
     cx<T> s[6];
 #pragma unroll
-    for (int c = 0; c < 6; ++c) s[c] = R[(c * nrs + r) * ss + lpad(i)];
+    for (int c = 0; c < 6; ++c) s[c] = R[c * cs];
     // the field the Green operator acts on: sigma_hat, or s_b (POL)
     cx<T> sg[6];
     if constexpr (POL) {
         cx<T> e[6];
 #pragma unroll
-        for (int c = 0; c < 6; ++c) e[c] = R[((6 + c) * nrs + r) * ss + lpad(i)];
+        for (int c = 0; c < 6; ++c) e[c] = R[(6 + c) * cs];
         const cx<T> tr = cadd(cadd(e[0], e[1]), e[2]);
         const T al = (T)alpha, bl = (T)(beta * lam0), b2m = (T)(2.0 * beta * mu0);
 #pragma unroll
@@ -748,8 +728,19 @@ __device__ __forceinline__ double gamma_point(cx<T>* R, int ss, int nrs, int r, 
         o[5] = csub(cadd(cscale(sy, hm * n0), cscale(sx, hm * n1)), cscale(a, cc * n0 * n1));
     }
 #pragma unroll
-    for (int c = 0; c < 6; ++c) R[(c * nrs + r) * ss + lpad(i)] = o[c];
+    for (int c = 0; c < 6; ++c) R[c * cs] = o[c];
     return esum;
+}
+
+// The same for component c of a pencil in row c * nrs + r of R, element i.
+template <typename T, bool POL>
+__device__ __forceinline__ double gamma_point(cx<T>* R, int ss, int nrs, int r, int i, int kx, int ky, int kz,
+                                              const Geo& g, double lam0, double mu0, double alpha, double beta,
+                                              int dc_mode, const double* __restrict__ E, const double* dc_mean,
+                                              DevState* __restrict__ st)
+{
+    return gamma_point_at<T, POL>(R + r * ss + lpad(i), nrs * ss, kx, ky, kz, g, lam0, mu0, alpha, beta, dc_mode, E,
+                                  dc_mean, st);
 }
 
 // Frequency indices of element i of gamma pencil pen.
@@ -846,8 +837,8 @@ __global__ __launch_bounds__(kThreads) void k_gamma(cx<T>* __restrict__ S, Geo g
 // tile in registers, in flight while the current tile is transformed,
 // filtered and stored.  Pencils past the last one are zero and never stored.
 // part_err gets one sum per block.
-template <typename T, bool POL, bool IP>
-__global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(sizeof(T) == 4 && IP && !POL ? RPM_GIP_WPE : 1))) void k_gpipe(cx<T>* __restrict__ S, Geo g, Plan pr,
+template <typename T, bool POL>
+__global__ __launch_bounds__(kThreads) void k_gpipe(cx<T>* __restrict__ S, Geo g, Plan pr,
                                                     const cx<T>* __restrict__ twr, double lam0, double mu0,
                                                     double alpha, double beta, int dc_mode,
                                                     const double* __restrict__ E,
@@ -864,7 +855,7 @@ __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(sizeof
     const int ss = lrow(nrow);
     cx<T>* A0 = reinterpret_cast<cx<T>*>(smem);
     cx<T>* B0 = A0 + NC * np * ss;
-    cx<T>* tw0 = IP ? B0 : B0 + NC * np * ss;  // IP: one buffer, transforms in place
+    cx<T>* tw0 = B0 + NC * np * ss;
     double* red = reinterpret_cast<double*>(tw0 + nrow);
 
     for (int i = threadIdx.x; i < nrow; i += kThreads) tw0[i] = twr[i];
@@ -898,13 +889,7 @@ __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(sizeof
         __syncthreads();
         const int tn = t + gridDim.x;
         if (tn < ntiles) load(tn);  // next tile in flight during this one
-        cx<T>* R;
-        if constexpr (IP) {
-            ct_stages_ip<T, -1, 128, 0, 1, kThreads>(A, NC * np, ss, tw, threadIdx.x + opq);
-            R = A;
-        } else {
-            R = lds_fft<T, -1>(A, B, pr, NC * np, ss, tw, threadIdx.x + opq);
-        }
+        cx<T>* R = lds_fft<T, -1>(A, B, pr, NC * np, ss, tw);
         const long long o = (long long)t * kThreads + threadIdx.x;
         const bool in = o < nlast;
         if (in) {
@@ -914,13 +899,7 @@ __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(sizeof
                                         dc_mean, st);
         }
         __syncthreads();
-        const cx<T>* Q;
-        if constexpr (IP) {
-            ct_stages_ip<T, +1, 128, 0, 1, kThreads>(A, 6 * np, ss, tw, threadIdx.x + opq);
-            Q = A;
-        } else {
-            Q = lds_fft<T, +1>(R, R == A ? B : A, pr, 6 * np, ss, tw, threadIdx.x + opq);
-        }
+        const cx<T>* Q = lds_fft<T, +1>(R, R == A ? B : A, pr, 6 * np, ss, tw);
         if (in) {
 #pragma unroll
             for (int c = 0; c < 6; ++c) S[c * g.nspec + o] = Q[c * np * ss + la];
@@ -938,8 +917,8 @@ __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(sizeof
 // are back.
 // grid: nz * (ny / ty).
 // ---------------------------------------------------------------------------
-template <typename T, bool POL, int NT, bool IP>
-__global__ __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(sizeof(T) == 4 ? 4 : 2))) void k_xinv(const cx<T>* __restrict__ S1, const T* __restrict__ eps,
+template <typename T, bool POL>
+__global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(sizeof(T) == 4 ? 4 : 2))) void k_xinv(const cx<T>* __restrict__ S1, const T* __restrict__ eps,
                                                    T* __restrict__ out, int out_mode, const T* __restrict__ shift,
                                                    double* __restrict__ part_inc, Geo g, Plan px,
                                                    const cx<T>* __restrict__ twx, const uint8_t* __restrict__ phase,
@@ -948,11 +927,11 @@ __global__ __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(sizeof(T) ==
 {
     if (done && *done) return;
     extern __shared__ __align__(16) unsigned char smem[];
-    constexpr int MV = MaxV<T>::v * kThreads / NT;  // voxels per thread
+    constexpr int NT = kThreads, MV = MaxV<T>::v;  // voxels per thread
     const int nx = g.nx, ty = g.ty, ss = lrow(nx), nh = g.nh;
     cx<T>* A = reinterpret_cast<cx<T>*>(smem);
     cx<T>* B = A + ty * ss;
-    cx<T>* tw = IP ? B : B + ty * ss;  // IP: one buffer, transforms in place
+    cx<T>* tw = B + ty * ss;
     const int nyt = g.ny / ty;
     const int z = blockIdx.x / nyt;
     const int y0 = (blockIdx.x - z * nyt) * ty;
@@ -1024,13 +1003,7 @@ __global__ __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(sizeof(T) ==
                 }
             }
         }
-        const cx<T>* R;
-        if constexpr (IP) {
-            ct_stages_ip<T, +1, 128, 0, 1, NT>(A, ty, ss, tw, threadIdx.x);
-            R = A;
-        } else {
-            R = lds_fft<T, +1, NT>(A, B, px, ty, ss, tw);
-        }
+        const cx<T>* R = lds_fft<T, +1, NT>(A, B, px, ty, ss, tw);
 #pragma unroll
         for (int i = 0; i < MV; ++i) {
             const int v = threadIdx.x + i * NT;
@@ -1520,7 +1493,7 @@ __global__ __launch_bounds__(kThreads) void k_tdots(TA* __restrict__ a0, TA* __r
 // Reductions of per-block partial sums (fixed order: deterministic).
 // ---------------------------------------------------------------------------
 // out[j] = sum_b part[b * bs + j * cs], j < m.  grid: m.
-__global__ __launch_bounds__(kThreads) void k_reduce_cols(const double* __restrict__ part, int G, long long bs,
+static __global__ __launch_bounds__(kThreads) void k_reduce_cols(const double* __restrict__ part, int G, long long bs,
                                                           long long cs, double* __restrict__ out)
 {
     __shared__ double red[kWaves];
@@ -1540,7 +1513,7 @@ __global__ __launch_bounds__(kThreads) void k_reduce_cols(const double* __restri
 // per column: zeta_j at column j and, nf = 2, z_j at column ld + j).  Fixed
 // order: deterministic.
 // ---------------------------------------------------------------------------
-__global__ __launch_bounds__(kThreads) void k_reduce_main(const double* __restrict__ part_err, int G_err,
+static __global__ __launch_bounds__(kThreads) void k_reduce_main(const double* __restrict__ part_err, int G_err,
                                                           const double* __restrict__ part_dots, int G_dots, int ld,
                                                           int p, double* __restrict__ out,
                                                           const int* __restrict__ done)
@@ -1576,7 +1549,7 @@ __global__ __launch_bounds__(kThreads) void k_reduce_main(const double* __restri
 // (the same numbers without a second pass over the basis).
 // newton_only: skip the error bookkeeping (used after basis growth).
 // ---------------------------------------------------------------------------
-__global__ __launch_bounds__(kThreads) void k_step_end(DevState* __restrict__ st, const double* __restrict__ sums,
+static __global__ __launch_bounds__(kThreads) void k_step_end(DevState* __restrict__ st, const double* __restrict__ sums,
                                                        int p, int slot, int two_d, int newton_only, int err_mode,
                                                        int direct, double* __restrict__ hist, int hist_cap)
 {
@@ -1701,7 +1674,7 @@ __device__ __forceinline__ unsigned long long splitmix64(unsigned long long z)
     return z ^ (z >> 31);
 }
 
-__global__ __launch_bounds__(kThreads) void k_phase_sum(const uint8_t* __restrict__ phase, long long N,
+static __global__ __launch_bounds__(kThreads) void k_phase_sum(const uint8_t* __restrict__ phase, long long N,
                                                         unsigned long long* __restrict__ part)
 {
     __shared__ unsigned long long red[kWaves];
@@ -1858,13 +1831,13 @@ __global__ __launch_bounds__(kThreads) void k_init(DevState* __restrict__ st, do
     }
 }
 
-__global__ void k_set_E(DevState* __restrict__ st, InitArgs a)
+static __global__ void k_set_E(DevState* __restrict__ st, InitArgs a)
 {
     if (threadIdx.x < 6) st->E[threadIdx.x] = a.E[threadIdx.x];
 }
 
 // Clear the stop flags and the step counter (a fresh map evaluation).
-__global__ void k_reset_state(DevState* __restrict__ st)
+static __global__ void k_reset_state(DevState* __restrict__ st)
 {
     if (threadIdx.x == 0) {
         st->done = 0;
@@ -1875,7 +1848,7 @@ __global__ void k_reset_state(DevState* __restrict__ st)
 
 // H gains row and column p: H[i][p] = col[i] (i <= p), H[p][j] = row[j] (j < p);
 // the Gram matrix gains gram[j] = <Z_p, Z_j> (j <= p) in row and column p.
-__global__ void k_border(DevState* __restrict__ st, const double* __restrict__ col, const double* __restrict__ row,
+static __global__ void k_border(DevState* __restrict__ st, const double* __restrict__ col, const double* __restrict__ row,
                          const double* __restrict__ gram, int p)
 {
     if (threadIdx.x != 0) return;
@@ -1890,7 +1863,7 @@ __global__ void k_border(DevState* __restrict__ st, const double* __restrict__ c
 // LU factorisation with partial pivoting of I - H, one wave of 64 threads on
 // an LDS copy (row stride kMaxP + 1 keeps the row-parallel updates free of
 // bank conflicts).  Thread t eliminates row c + 1 + t at step c.
-__global__ __launch_bounds__(64) void k_factor(DevState* __restrict__ st, int p)
+static __global__ __launch_bounds__(64) void k_factor(DevState* __restrict__ st, int p)
 {
     constexpr int LD = kMaxP + 1;
     __shared__ double A[kMaxP * LD];
@@ -2267,7 +2240,7 @@ __global__ __launch_bounds__(kThreads) void k_recombine_multi(CasePtrs<T> cp, co
 // The basis part of the solver state (p, H, its factorisation and inverse, the
 // Gram matrix) copied from one load case's state to another's after the
 // shared basis grew.
-__global__ __launch_bounds__(kThreads) void k_copy_basis_state(DevState* __restrict__ dst,
+static __global__ __launch_bounds__(kThreads) void k_copy_basis_state(DevState* __restrict__ dst,
                                                                const DevState* __restrict__ src)
 {
     for (int e = threadIdx.x; e < kMaxP * kMaxP; e += kThreads) {

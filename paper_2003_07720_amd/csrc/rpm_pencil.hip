@@ -1,0 +1,82 @@
+// Instantiations of the fixed-length pencil passes (rpm_pencil.h): every length
+// of RPM_PENCIL_LENGTHS, or those of one group (the build compiles the groups
+// side by side).
+#include "rpm_pencil.h"
+
+namespace rpm {
+
+template <typename T, int N>
+void Pencil<T, N>::y_pass(int dir, int comps, const cx<T>* in, cx<T>* out, const Geo& g, const cx<T>* tw,
+                          const int* done, hipStream_t s)
+{
+    const int nzt = (g.nz + rows() - 1) / rows(), grid = comps * g.nh * nzt;
+    constexpr int NT = tile_threads<T, N>();
+    if (dir < 0) k_py<T, N, -1><<<grid, NT, 0, s>>>(in, out, g, nzt, tw, done);
+    else k_py<T, N, +1><<<grid, NT, 0, s>>>(in, out, g, nzt, tw, done);
+}
+
+template <typename T, int N>
+void Pencil<T, N>::x_forward(bool pol, const T* xin, const uint8_t* phase, const double* lame, int use_ref,
+                             double lam0, double mu0, cx<T>* S1, double* part_mean, const Geo& g, const cx<T>* tw,
+                             const int* done, hipStream_t s)
+{
+    const int nyt = (g.ny + rows() - 1) / rows(), nt = g.nz * nyt;
+    constexpr int NT = tile_threads<T, N>();
+    if (pol)
+        k_pxf<T, N, 6><<<x_grid(nt, 6), NT, 0, s>>>(xin, phase, lame, use_ref, lam0, mu0, S1, part_mean, g, nt, nyt,
+                                                    tw, done);
+    else
+        k_pxf<T, N, 3><<<x_grid(nt, 3), NT, 0, s>>>(xin, phase, lame, use_ref, lam0, mu0, S1, part_mean, g, nt, nyt,
+                                                    tw, done);
+}
+
+template <typename T, int N>
+void Pencil<T, N>::x_inverse(bool pol, const cx<T>* S1, const T* eps, T* out, int out_mode, const T* shift,
+                             double* part_inc, const Geo& g, const cx<T>* tw, const uint8_t* phase,
+                             const double* lame, double lam0, double mu0, double beta, const int* done,
+                             hipStream_t s)
+{
+    const int nyt = (g.ny + rows() - 1) / rows(), nt = g.nz * nyt;
+    constexpr int NT = tile_threads<T, N>();
+    if (pol)
+        k_pxi_pol<T, N><<<nt, pol_groups<T, N>() * NT, 0, s>>>(S1, eps, out, shift, part_inc, g, nyt, tw, phase, lame,
+                                                               lam0, mu0, beta, done);
+    else
+        k_pxi<T, N><<<x_grid(nt, 3), NT, 0, s>>>(S1, eps, out, out_mode, shift, part_inc, g, nt, nyt, tw, done);
+}
+
+template <typename T, int N>
+void Pencil<T, N>::gamma(bool pol, cx<T>* S, const Geo& g, const cx<T>* tw, double lam0, double mu0, double alpha,
+                         double beta, int dc_mode, const double* E, const double* part_mean, int n_mean,
+                         double* part_err, DevState* st, const int* done, hipStream_t s)
+{
+    const int grid = gamma_blocks(pol, g.two_d ? g.nh : g.ny * g.nh);
+    if (pol)
+        k_pg<T, N, true><<<grid, GCfg<T, N, true>::NT, 0, s>>>(S, g, tw, lam0, mu0, alpha, beta, dc_mode, E, part_mean, n_mean,
+                                             part_err, st, done);
+    else
+        k_pg<T, N, false><<<grid, GCfg<T, N, false>::NT, 0, s>>>(S, g, tw, lam0, mu0, alpha, beta, dc_mode, E, part_mean, n_mean,
+                                              part_err, st, done);
+}
+
+#define RPM_INST(N)              \
+    template struct Pencil<float, N>; \
+    template struct Pencil<double, N>;
+
+#if !defined(RPM_PENCIL_GROUP)
+RPM_PENCIL_LENGTHS(RPM_INST)
+#elif RPM_PENCIL_GROUP == 0
+RPM_INST(16) RPM_INST(64) RPM_INST(256)
+#elif RPM_PENCIL_GROUP == 1
+RPM_INST(18) RPM_INST(72) RPM_INST(128)
+#elif RPM_PENCIL_GROUP == 2
+RPM_INST(24) RPM_INST(81) RPM_INST(192)
+#elif RPM_PENCIL_GROUP == 3
+RPM_INST(27) RPM_INST(48) RPM_INST(162)
+#elif RPM_PENCIL_GROUP == 4
+RPM_INST(32) RPM_INST(54) RPM_INST(144)
+#else
+RPM_INST(36) RPM_INST(96) RPM_INST(108)
+#endif
+
+}  // namespace rpm

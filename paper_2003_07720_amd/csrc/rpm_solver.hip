@@ -19,7 +19,11 @@
 #include <vector>
 
 #include "rpm_kernels.h"
+#include "rpm_pencil.h"
 #include "rpmfft.h"
+#ifndef RPM_PENCIL_SEPARATE  // the build compiles the instantiations side by side
+#include "rpm_pencil.hip"
+#endif
 
 using namespace rpm;
 
@@ -36,16 +40,8 @@ constexpr double kFp32Stage = 1e-5;  // FP32 stage target before FP64 refinement
 #define RPM_YPIPE_BLOCKS 1024
 #endif
 constexpr bool kYPipe = RPM_YPIPE != 0;        // software-pipelined y passes
-#ifndef RPM_Y_INPLACE
-#define RPM_Y_INPLACE 1
-#endif
-#ifndef RPM_YIP_BLOCKS
-#define RPM_YIP_BLOCKS 1280
-#endif
-constexpr bool kYInPlace = RPM_Y_INPLACE != 0;  // in-place y transforms (half the LDS)
-// persistent grid of the pipelined y passes (four, or with in-place transforms five, resident blocks per CU)
+// persistent grid of the pipelined y passes (four resident blocks per CU)
 constexpr int kYPipeBlocks = RPM_YPIPE_BLOCKS;
-constexpr int kYipBlocks = RPM_YIP_BLOCKS;
 #ifndef RPM_TDOTS_BLOCKS
 #define RPM_TDOTS_BLOCKS 1024
 #endif
@@ -57,43 +53,18 @@ constexpr int kTdotsBlocks = RPM_TDOTS_BLOCKS;  // grid cap of the basis product
 #define RPM_GPIPE_BLOCKS 1280
 #endif
 constexpr bool kGPipe = RPM_GPIPE != 0;        // software-pipelined gamma pass
-#ifndef RPM_G_INPLACE
-#define RPM_G_INPLACE 1
-#endif
-#ifndef RPM_GIP_BLOCKS
-#define RPM_GIP_BLOCKS 1280
-#endif
-constexpr bool kGInPlace = RPM_G_INPLACE != 0;  // in-place gamma transforms
-#ifndef RPM_X_INPLACE
-#define RPM_X_INPLACE 1
-#endif
-constexpr bool kXInPlace = RPM_X_INPLACE != 0;  // in-place x transforms
-#ifndef RPM_FUSE_RECOMBINE
-#define RPM_FUSE_RECOMBINE 1
-#endif
-// RPM recombination inside the x-forward pass (in-place 128-point x
-// transforms, not the polarization map; FP64 fields, or FP32 ones when the
-// split-column pass below is switched off)
-constexpr bool kFuseRecombine = RPM_FUSE_RECOMBINE != 0;
 #ifndef RPM_SPLIT_RECOMBINE
 #define RPM_SPLIT_RECOMBINE 1
 #endif
-// FP32 recombination as its own pass with the basis columns split over the
-// waves of a block (k_recombine_split) instead of inside the x-forward pass
+// FP32 recombination with the basis columns split over the waves of a block
+// (k_recombine_split)
 constexpr bool kSplitRecombine = RPM_SPLIT_RECOMBINE != 0;
 #ifndef RPM_SPLIT_DOTS
 #define RPM_SPLIT_DOTS 1
 #endif
 // per-step basis products with two or four columns per wave (k_gdots_split)
 constexpr bool kSplitDots = RPM_SPLIT_DOTS != 0;
-constexpr int kGipBlocks = RPM_GIP_BLOCKS;      // persistent grid with in-place transforms
 constexpr int kGPipeBlocks = RPM_GPIPE_BLOCKS;  // its persistent grid
-#ifndef RPM_X_NT
-#define RPM_X_NT 256
-#endif
-// threads of an FP32 x-pass block (the tile size does not change with it)
-template <typename T>
-constexpr int x_threads() { return sizeof(T) == 4 ? RPM_X_NT : kThreads; }
 
 size_t align_up(size_t x) { return (x + kAlign - 1) / kAlign * kAlign; }
 
@@ -140,6 +111,21 @@ int largest_divisor_leq(int n, int cap)
     return 1;
 }
 
+// f(Pencil<T, n>) where the pencil passes have length n at compile time; false elsewhere
+template <typename T, typename F>
+bool with_length(int n, F f)
+{
+    switch (n) {
+#define RPM_CASE(N)          \
+    case N:                  \
+        f(Pencil<T, N>());   \
+        return true;
+        RPM_PENCIL_LENGTHS(RPM_CASE)
+#undef RPM_CASE
+    }
+    return false;
+}
+
 // Tile shapes and LDS bytes of each pass for element type T.
 template <typename T>
 struct Shapes {
@@ -149,13 +135,18 @@ struct Shapes {
     int G1, Gy, Gyf, G3, Gg, Gp, Gq;  // Gyf: forward y-pass tiles (all spectral components)
     int Gt;                           // gamma tiles
     bool gpipe;                       // pipelined gamma pass (tiles of kThreads elements per component)
-    bool yip;                         // y passes transform in place (one LDS buffer)
-    bool gip;                         // gamma pass transforms in place
-    bool xip;                         // x passes transform in place
     int Yb;                           // workgroups of the persistent y passes
     bool ok;
     bool tune_ok;                     // the launch-shape overrides (rpm_tuning) apply to this grid
     bool yregs;                       // y transforms in registers (k_ywave)
+    // passes with their length at compile time (rpm_pencil.h) along x, y and the
+    // last axis, the tiles of such an x pass, its increment partial sums and the
+    // blocks of such a gamma pass
+    bool fx, fy, fg;
+    int Gx, Gxi, Gpg;
+    int g1() const { return fx ? Gx : G1; }      // <eps> partial sums of an x-forward pass
+    int ginc() const { return fx ? Gxi : G1; }   // increment partial sums of an x-inverse pass
+    int g3() const { return fg ? Gpg : G3; }     // error partial sums of a gamma pass
 };
 
 template <typename T>
@@ -182,19 +173,10 @@ Shapes<T> make_shapes(const int32_t n[3], int ncomp, const rpm_tuning* tn = null
     while (g.ty > 1 && (size_t)(2 * g.ty * lrow(g.nx) + g.nx) * wsz + 80 * 8 > (size_t)kLdsCap)
         g.ty = largest_divisor_leq(g.ny, g.ty - 1);
     s.lds_x = (size_t)(2 * g.ty * lrow(g.nx) + g.nx) * wsz + 80 * 8;
-    // 128-point x transforms of at most one butterfly per thread run in place
-    s.xip = kXInPlace && g.nx == 128 && g.ty * 128 / 8 <= kThreads;
-    if (s.xip) s.lds_x = (size_t)(g.ty * lrow(g.nx) + g.nx) * wsz + 80 * 8;
-    // y passes: tz columns of ny (128-byte segments; FP64 128-point rows,
-    // transformed in place in one LDS buffer, take 16: 92 / 66 us against
-    // 98 / 71 us for the forward / inverse pass at 128^3)
+    // y passes: tz columns of ny (128-byte segments)
     g.tz = largest_divisor_leq(g.nz, 128 / wsz);
     while (g.tz > 1 && (size_t)(2 * g.tz * lrow(g.ny) + g.ny) * wsz > (size_t)kLdsCap)
         g.tz = largest_divisor_leq(g.nz, g.tz - 1);
-    if (wsz == 16 && kYInPlace && g.ny == 128) {
-        const int t = largest_divisor_leq(g.nz, 16);
-        if ((size_t)(t * lrow(g.ny) + g.ny) * wsz <= (size_t)kLdsCap) g.tz = t;
-    }
     if (tn && tn->y_cols > 0) {
         const int t = tn->y_cols;
         if (g.nz % t != 0 || t > 128 / wsz || t * g.ny > 8 * kThreads ||
@@ -203,9 +185,7 @@ Shapes<T> make_shapes(const int32_t n[3], int ncomp, const rpm_tuning* tn = null
         else
             g.tz = t;
     }
-    // 128-point y transforms of at most one butterfly per thread run in place
-    s.yip = kYInPlace && g.ny == 128 && g.tz * 128 / 8 <= kThreads;
-    s.lds_y = (size_t)((s.yip ? 1 : 2) * g.tz * lrow(g.ny) + g.ny) * wsz;
+    s.lds_y = (size_t)(2 * g.tz * lrow(g.ny) + g.ny) * wsz;
     // gamma pass: np pencils x ncomp components along the last axis
     const int nrow = g.two_d ? g.ny : g.nz;
     const int npen = g.two_d ? g.nh : g.ny * g.nh;
@@ -235,16 +215,19 @@ Shapes<T> make_shapes(const int32_t n[3], int ncomp, const rpm_tuning* tn = null
     s.Gyf = ncomp * g.nh * (g.nz / g.tz);
     s.Gt = (npen + g.np - 1) / g.np;
     s.gpipe = kGPipe && g.np * nrow == kThreads;
-    // 128-point gamma transforms of at most one butterfly per thread run in place
-    s.gip = s.gpipe && kGInPlace && nrow == 128 && ncomp * g.np * 128 / 8 <= kThreads;
-    if (s.gip) s.lds_g = (size_t)(ncomp * np * lrow(nrow) + nrow) * wsz + 80 * 8;
-    s.G3 = s.gpipe ? std::min(s.Gt, s.gip ? kGipBlocks : kGPipeBlocks) : s.Gt;  // gamma blocks (one error partial each)
-    s.Yb = s.yip ? kYipBlocks : kYPipeBlocks;
+    s.G3 = s.gpipe ? std::min(s.Gt, kGPipeBlocks) : s.Gt;  // gamma blocks (one error partial each)
+    s.Yb = kYPipeBlocks;
     if (tn && tn->y_blocks > 0) s.Yb = tn->y_blocks;
     s.yregs = tn && tn->y_regs > 0;
     if (s.yregs && !(sizeof(T) == 4 && !g.two_d && g.ny == 128 && g.tz == 16 && tn->y_blocks == 0))
         s.tune_ok = false;
     if (tn && tn->gamma_blocks > 0 && s.gpipe) s.G3 = std::min(s.Gt, tn->gamma_blocks);
+    s.fx = with_length<T>(g.nx, [&](auto pc) {
+        s.Gx = g.nz * ((g.ny + pc.rows() - 1) / pc.rows());
+        s.Gxi = ncomp == 12 ? s.Gx : 3 * s.Gx;
+    });
+    s.fy = !g.two_d && with_length<T>(g.ny, [](auto) {});
+    s.fg = with_length<T>(nrow, [&](auto pc) { s.Gpg = pc.gamma_blocks(ncomp == 12, npen); });
     s.Gg = (int)((g.N + kChunk - 1) / kChunk);
     s.Gp = (int)((6 * g.N + kVecBlock - 1) / kVecBlock);
     const long long ntile = (6 * g.N + kZTile - 1) / kZTile;
@@ -309,9 +292,11 @@ Layout make_layout(const Shapes<T>& s, const rpm_options* o, bool map_only)
     L.twy = take(sizeof(cx<T>) * kMaxN);
     L.twr = take(sizeof(cx<T>) * kMaxN);
     L.lame = take(sizeof(double) * 512);
-    L.pmean = take(sizeof(double) * 6 * s.G1);
-    L.perr = take(sizeof(double) * std::max(s.G3, s.Gt));  // any gamma grid (tuned or not) fits
-    L.pinc = take(sizeof(double) * s.G1);
+    const int gm = std::max(s.G1, s.Gx), gi = std::max(s.G1, s.Gxi);
+    const int ge = std::max(std::max(s.G3, s.Gt), s.Gpg);  // any gamma grid (tuned or not) fits
+    L.pmean = take(sizeof(double) * 6 * gm);
+    L.perr = take(sizeof(double) * ge);
+    L.pinc = take(sizeof(double) * gi);
     L.pdots = take(sizeof(double) * 2 * L.ld * std::max(std::max(s.G1, s.Gp), s.Gq));
     const long long Gd = (6 * g.N + 4 * kThreads - 1) / (4 * kThreads);  // k_growth_diff blocks (3 partials each)
     L.pg = take(sizeof(double) * std::max((size_t)(4 * kMaxP + 4) * std::max(std::max(s.Gg, s.Gp), s.Gq),
@@ -350,9 +335,9 @@ Layout make_layout(const Shapes<T>& s, const rpm_options* o, bool map_only)
         for (int f = 1; f < L.nb; ++f) {
             CaseOff& c = L.cs[f];
             c.st = take(sizeof(DevState));
-            c.pmean = take(sizeof(double) * 6 * s.G1);
-            c.perr = take(sizeof(double) * std::max(s.G3, s.Gt));
-            c.pinc = take(sizeof(double) * s.G1);
+            c.pmean = take(sizeof(double) * 6 * gm);
+            c.perr = take(sizeof(double) * ge);
+            c.pinc = take(sizeof(double) * gi);
             c.pdots = take(sizeof(double) * 2 * L.ld * std::max(std::max(s.G1, s.Gp), s.Gq));
             c.sums = take(sizeof(double) * (2 * kMaxP + 8));
             c.gsum = take(sizeof(double) * (kMaxP + 8));
@@ -536,21 +521,23 @@ void run_F(Ctx<T>& c, const T* xin, int p_corr, T* eps_store, const T* eps_for_i
     hipEvent_t ev;
     const bool pol = c.pol && out_mode == OUT_XI;
     const bool vec = g.nx % (16 / (int)sizeof(T)) == 0;
-    constexpr int XT = x_threads<T>();
     const double cf = (double)g.ncomp / 6.0;  // spectral components carried forward, over 6
     const double bx = fieldB + (use_ref ? 0.0 : (double)g.N) + cf * specB;
-    // FP32 with whole basis tiles: the split-column streaming pass plus the
-    // plain x pass beat the fused pass (its one resident round of blocks
-    // cannot overlap their transforms with the stream)
+    // FP32 with whole basis tiles: the split-column streaming pass
     const bool split = sizeof(T) == 4 && kSplitRecombine && (6 * g.N) % kZTile == 0;
-    const bool fuse = eps_store && kFuseRecombine && sh.xip && vec && !pol && !split;
-    if (fuse) {
-        // eps = xin + Z d recombined inside the x pass (stored for the x-inverse)
-        c.mark_begin(RPM_K_XFWD, ev);
-        k_xfwd<T, true, false, XT, true, true><<<sh.G1, XT, sh.lds_x, c.s>>>(
-            xin, c.phase, c.lame(), use_ref, c.lam0, c.mu0, S1, pmean, g, sh.px, c.twx(), done, c.Zb(), p_corr,
-            c.pmax, c.st->d, eps_store);
-        c.mark_end(RPM_K_XFWD, ev, bx + fieldB * (1 + p_corr));
+    // FP64 on 128-point rows: eps = xin + Z d recombined inside the x pass, which
+    // stores it for the x-inverse (128^3, p = 32: 610 us, as the two passes)
+    constexpr bool can_fuse = sizeof(T) == 8;
+    const bool fuse = can_fuse && eps_store && g.nx == 128 && !pol;
+    if constexpr (can_fuse) {
+        if (fuse) {
+            const size_t lds = (size_t)(g.ty * lrow(128) + 128) * sizeof(cx<T>) + 80 * 8;
+            c.mark_begin(RPM_K_XFWD, ev);
+            k_xfwd<T, true, false, true><<<sh.G1, kThreads, lds, c.s>>>(xin, c.phase, c.lame(), use_ref, c.lam0, c.mu0, S1,
+                                                                 pmean, g, sh.px, c.twx(), done, c.Zb(), p_corr,
+                                                                 c.pmax, c.st->d, eps_store);
+            c.mark_end(RPM_K_XFWD, ev, bx + fieldB * (1 + p_corr));
+        }
     }
     if (eps_store && !fuse) {
         // eps = xin + Z d (a copy while p = 0) as its own streaming pass; the x
@@ -580,27 +567,22 @@ void run_F(Ctx<T>& c, const T* xin, int p_corr, T* eps_store, const T* eps_for_i
         c.mark_end(RPM_K_RECOMBINE, ev, fieldB * (2 + p_corr));
         xin = eps_store;
     }
+    const int n_mean = fuse ? sh.G1 : sh.g1();
     if (!fuse) c.mark_begin(RPM_K_XFWD, ev);
-#define RPM_XFWD(V, P, I)                                                                                      \
-    k_xfwd<T, V, P, XT, I><<<sh.G1, XT, sh.lds_x, c.s>>>(xin, c.phase, c.lame(), use_ref, c.lam0, c.mu0, S1, pmean, \
-                                                         g, sh.px, c.twx(), done)
+#define RPM_XFWD(V, P)                                                                                        \
+    k_xfwd<T, V, P><<<sh.G1, kThreads, sh.lds_x, c.s>>>(xin, c.phase, c.lame(), use_ref, c.lam0, c.mu0, S1, pmean, \
+                                                        g, sh.px, c.twx(), done)
     if (fuse) {
-    } else if (sh.xip) {
-        if (pol) {
-            if (vec) RPM_XFWD(true, true, true);
-            else RPM_XFWD(false, true, true);
-        } else {
-            if (vec) RPM_XFWD(true, false, true);
-            else RPM_XFWD(false, false, true);
-        }
+    } else if (sh.fx) {
+        with_length<T>(g.nx, [&](auto pc) {
+            pc.x_forward(pol, xin, c.phase, c.lame(), use_ref, c.lam0, c.mu0, S1, pmean, g, c.twx(), done, c.s);
+        });
+    } else if (pol) {
+        if (vec) RPM_XFWD(true, true);
+        else RPM_XFWD(false, true);
     } else {
-        if (pol) {
-            if (vec) RPM_XFWD(true, true, false);
-            else RPM_XFWD(false, true, false);
-        } else {
-            if (vec) RPM_XFWD(true, false, false);
-            else RPM_XFWD(false, false, false);
-        }
+        if (vec) RPM_XFWD(true, false);
+        else RPM_XFWD(false, false);
     }
 #undef RPM_XFWD
     if (!fuse) c.mark_end(RPM_K_XFWD, ev, bx);
@@ -609,11 +591,10 @@ void run_F(Ctx<T>& c, const T* xin, int p_corr, T* eps_store, const T* eps_for_i
         c.mark_begin(RPM_K_YFWD, ev);
         if (sh.yregs)
             launch_ywave<T, -1>(c.s, tiles, S1, S2, g, c.twy(), done);
-        else if (kYPipe && sh.yip)
-            k_ypipe<T, -1, 8, true><<<std::min(tiles, sh.Yb), kThreads, sh.lds_y, c.s>>>(S1, S2, g, sh.py,
-                                                                                             c.twy(), tiles, done);
+        else if (sh.fy)
+            with_length<T>(g.ny, [&](auto pc) { pc.y_pass(-1, pol ? g.ncomp : 6, S1, S2, g, c.twy(), done, c.s); });
         else if (kYPipe && g.tz * g.ny <= 8 * kThreads)
-            k_ypipe<T, -1, 8, false><<<std::min(tiles, sh.Yb), kThreads, sh.lds_y, c.s>>>(S1, S2, g, sh.py,
+            k_ypipe<T, -1, 8><<<std::min(tiles, sh.Yb), kThreads, sh.lds_y, c.s>>>(S1, S2, g, sh.py,
                                                                                                 c.twy(), tiles, done);
         else
             k_yfwd<T><<<tiles, kThreads, sh.lds_y, c.s>>>(S1, S2, g, sh.py, c.twy(), done);
@@ -622,13 +603,15 @@ void run_F(Ctx<T>& c, const T* xin, int p_corr, T* eps_store, const T* eps_for_i
     c.mark_begin(RPM_K_GAMMA, ev);
     cx<T>* Sg = g.two_d ? S1 : S2;
 #define RPM_GAMMA_ARGS                                                                                    \
-    Sg, g, sh.pr, c.twr(), c.lam0, c.mu0, c.alpha, c.beta, dc_mode, Edev, pmean, sh.G1, perr, c.st
-    if (sh.gip) {
-        if (pol) k_gpipe<T, true, true><<<sh.G3, kThreads, sh.lds_g, c.s>>>(RPM_GAMMA_ARGS, sh.Gt, done);
-        else k_gpipe<T, false, true><<<sh.G3, kThreads, sh.lds_g, c.s>>>(RPM_GAMMA_ARGS, sh.Gt, done);
+    Sg, g, sh.pr, c.twr(), c.lam0, c.mu0, c.alpha, c.beta, dc_mode, Edev, pmean, n_mean, perr, c.st
+    if (sh.fg) {
+        with_length<T>(g.two_d ? g.ny : g.nz, [&](auto pc) {
+            pc.gamma(pol, Sg, g, c.twr(), c.lam0, c.mu0, c.alpha, c.beta, dc_mode, Edev, pmean, n_mean, perr, c.st,
+                     done, c.s);
+        });
     } else if (sh.gpipe) {
-        if (pol) k_gpipe<T, true, false><<<sh.G3, kThreads, sh.lds_g, c.s>>>(RPM_GAMMA_ARGS, sh.Gt, done);
-        else k_gpipe<T, false, false><<<sh.G3, kThreads, sh.lds_g, c.s>>>(RPM_GAMMA_ARGS, sh.Gt, done);
+        if (pol) k_gpipe<T, true><<<sh.G3, kThreads, sh.lds_g, c.s>>>(RPM_GAMMA_ARGS, sh.Gt, done);
+        else k_gpipe<T, false><<<sh.G3, kThreads, sh.lds_g, c.s>>>(RPM_GAMMA_ARGS, sh.Gt, done);
     } else {
         if (pol) k_gamma<T, true><<<sh.G3, kThreads, sh.lds_g, c.s>>>(RPM_GAMMA_ARGS, done);
         else k_gamma<T, false><<<sh.G3, kThreads, sh.lds_g, c.s>>>(RPM_GAMMA_ARGS, done);
@@ -639,26 +622,28 @@ void run_F(Ctx<T>& c, const T* xin, int p_corr, T* eps_store, const T* eps_for_i
         c.mark_begin(RPM_K_YINV, ev);
         if (sh.yregs)
             launch_ywave<T, 1>(c.s, sh.Gy, S2, S1, g, c.twy(), done);
-        else if (kYPipe && sh.yip)
-            k_ypipe<T, 1, 8, true><<<std::min(sh.Gy, sh.Yb), kThreads, sh.lds_y, c.s>>>(S2, S1, g, sh.py,
-                                                                                            c.twy(), sh.Gy, done);
+        else if (sh.fy)
+            with_length<T>(g.ny, [&](auto pc) { pc.y_pass(+1, 6, S2, S1, g, c.twy(), done, c.s); });
         else if (kYPipe && g.tz * g.ny <= 8 * kThreads)
-            k_ypipe<T, 1, 8, false><<<std::min(sh.Gy, sh.Yb), kThreads, sh.lds_y, c.s>>>(S2, S1, g, sh.py,
+            k_ypipe<T, 1, 8><<<std::min(sh.Gy, sh.Yb), kThreads, sh.lds_y, c.s>>>(S2, S1, g, sh.py,
                                                                                                c.twy(), sh.Gy, done);
         else
             k_yinv<T><<<sh.Gy, kThreads, sh.lds_y, c.s>>>(S2, S1, g, sh.py, c.twy(), done);
         c.mark_end(RPM_K_YINV, ev, 2.0 * specB);
     }
     c.mark_begin(RPM_K_XINV, ev);
-#define RPM_XINV(P, I)                                                                                         \
-    k_xinv<T, P, XT, I><<<sh.G1, XT, sh.lds_x, c.s>>>(S1, eps_for_inv, out, out_mode, shift, part_inc, g, sh.px,     \
-                                                      c.twx(), c.phase, c.lame(), c.lam0, c.mu0, c.beta, done)
-    if (sh.xip) {
-        if (pol) RPM_XINV(true, true);
-        else RPM_XINV(false, true);
+#define RPM_XINV(P)                                                                                            \
+    k_xinv<T, P><<<sh.G1, kThreads, sh.lds_x, c.s>>>(S1, eps_for_inv, out, out_mode, shift, part_inc, g, sh.px,  \
+                                                     c.twx(), c.phase, c.lame(), c.lam0, c.mu0, c.beta, done)
+    if (sh.fx) {
+        with_length<T>(g.nx, [&](auto pc) {
+            pc.x_inverse(pol, S1, eps_for_inv, out, out_mode, shift, part_inc, g, c.twx(), c.phase, c.lame(), c.lam0,
+                         c.mu0, c.beta, done, c.s);
+        });
+    } else if (pol) {
+        RPM_XINV(true);
     } else {
-        if (pol) RPM_XINV(true, false);
-        else RPM_XINV(false, false);
+        RPM_XINV(false);
     }
 #undef RPM_XINV
     c.mark_end(RPM_K_XINV, ev, bi + (pol ? (double)g.N : 0.0));
@@ -737,7 +722,7 @@ void reduce_and_finalize(Ctx<T>& c, int p, int slot, int newton_only, bool direc
                                      : (err_mode == 0 ? c.template at<double>(c.L.perr)
                                                       : c.template at<double>(c.L.pinc));
     const int nf = direct ? 2 : 1;
-    k_reduce_main<<<1 + nf * p, kThreads, 0, c.s>>>(perr, err_mode == 0 ? c.sh.G3 : c.sh.G1, c.pdots(), c.sh.Gq,
+    k_reduce_main<<<1 + nf * p, kThreads, 0, c.s>>>(perr, err_mode == 0 ? c.sh.g3() : c.sh.ginc(), c.pdots(), c.sh.Gq,
                                                     c.L.ld, p, c.sums(), done);
     c.mark_end(RPM_K_REDUCE, ev);
     c.mark_begin(RPM_K_FINAL, ev);
@@ -1568,8 +1553,9 @@ rpm_status tune_typed(const rpm_problem* pr, const rpm_options* o, int reps, rpm
             }
         }
     }
-    // y_cols: admissible divisors of nz, largest first (3-D only)
-    if (!g.two_d) {
+    // y_cols: admissible divisors of nz, largest first (3-D only; passes with
+    // their length at compile time have one shape)
+    if (!g.two_d && !base.fy) {
         int tried = 0;
         for (int t = std::min(g.nz, 64); t >= 1 && tried < 4 && hip_ok; --t) {
             if (g.nz % t != 0 || t == g.tz) continue;
@@ -1588,7 +1574,8 @@ rpm_status tune_typed(const rpm_problem* pr, const rpm_options* o, int reps, rpm
     const int mult[7] = {1, 2, 3, 4, 5, 6, 8};
     // y_blocks, then gamma_blocks: 256 x mult, below the tile counts
     for (int coord = 0; coord < 2 && hip_ok; ++coord) {
-        if (coord == 0 && g.two_d) continue;
+        if (coord == 0 && (g.two_d || base.fy)) continue;
+        if (coord == 1 && base.fg) continue;
         const Shapes<T> sh0 = make_shapes<T>(pr->n, spectral_comps(&ob), &cur);
         if (coord == 1 && !sh0.gpipe) continue;  // one tile per workgroup: nothing to tune
         const int tiles = coord == 0 ? sh0.Gy : sh0.Gt;
@@ -1932,7 +1919,7 @@ rpm_status eff_batched(const rpm_problem* pr, const rpm_options* o, double* C, r
         }
         for (int f = 0; f < nb; ++f) {
             const double* bpd = c.template at<double>(c.L.bpd) + (long long)f * kMaxP * c.sh.Gq;
-            k_reduce_main<<<1 + p, kThreads, 0, c.s>>>(cx[f].template at<double>(cx[f].L.perr), c.sh.G3, bpd,
+            k_reduce_main<<<1 + p, kThreads, 0, c.s>>>(cx[f].template at<double>(cx[f].L.perr), c.sh.g3(), bpd,
                                                        c.sh.Gq, kMaxP, p, cx[f].sums(), done[f]);
             k_step_end<<<1, kThreads, 0, c.s>>>(cx[f].st, cx[f].sums(), p, it & 3, g.two_d, 0, 0, 0,
                                                 cx[f].template at<double>(cx[f].L.hist), (int)c.L.hist_cap);
