@@ -318,11 +318,22 @@ struct FWs {
     long long feat;                   // input features of a warm start [cin][N]
     long long part;                   // loss partial sums (double, 1024)
     long long tab[3];                 // bfloat16 twiddle tables of the fused passes
-    long long wg;                     // partial sums of the fused weight gradients
+    long long dp;                     // gradients of the pre-activations of all layers: L x [B][C][N]
+    long long wg;                     // results of the fused weight-gradient chains
     long long total;
     long long N;
     int n[3];
 };
+
+// The fused passes (rpm_fno_layer.h) hold all modes of an axis in one MFMA tile,
+// the channels of a voxel in at most four, and a row of 16-bit DFT operands per
+// mode in LDS: up to 16 modes, 64 channels and extents of 512.  Wider networks
+// take the batched GEMMs.
+bool fused_fits(const Net& net, const int* n)
+{
+    return net.m <= fno::kModeSlots && net.C <= 64 && net.cin <= 64 && net.cout <= 64 && n[0] <= 512 &&
+           n[1] <= 512 && n[2] <= 512;
+}
 
 FWs make_fws(const Net& net, const int32_t n[3], int B)
 {
@@ -358,7 +369,12 @@ FWs make_fws(const Net& net, const int32_t n[3], int B)
     w.feat = take((long long)net.cin * N);
     w.part = take(2 * 1024);
     for (int a = 0; a < 3; ++a) w.tab[a] = take(2 * fno::kModeSlots * ((n[a] + 15) / 16 * 16));
-    w.wg = take((long long)fno::kWgradBlocks * 4 * 16 * (16 * 4 + 1));
+    if (fused_fits(net, n)) {
+        w.dp = take((long long)net.L * B * C * N);
+        const auto t16 = [](int c) { return (c + 15) / 16; };
+        const int mt = std::max(t16(net.C) * std::max(t16(net.C), t16(net.cin)), t16(net.cout) * t16(net.C));
+        w.wg = take((((net.L + 2ll) * B + 7) / 8 * 8) * mt * 256);
+    }
     w.total = off;
     return w;
 }
@@ -379,6 +395,9 @@ struct Fno {
     }
 };
 
+// 2 pi r / n
+long double turn(long long r, int n) { return 2.0L * 3.141592653589793238462643383279502884L * (long double)r / n; }
+
 // Twiddle tables of axis a: cos(2 pi k x / n) and sin(2 pi k x / n), k the
 // signed frequency index kk - m/2, row-major [kk][x].
 bool upload_twiddles(Fno& f)
@@ -391,7 +410,7 @@ bool upload_twiddles(Fno& f)
             const long long k = kk - m / 2;
             for (int x = 0; x < n; ++x) {
                 const long long r = ((k * x) % n + n) % n;
-                const long double ang = 2.0L * 3.141592653589793238462643383279502884L * (long double)r / n;
+                const long double ang = turn(r, n);
                 t[(size_t)kk * n + x] = (float)std::cos(ang);
                 t[(size_t)m * n + (size_t)kk * n + x] = (float)std::sin(ang);
             }
@@ -621,15 +640,6 @@ bool valid_grid(const int32_t n[3])
 // ---------------------------------------------------------------------------
 // The same network through the fused passes (rpm_fno_layer.h)
 // ---------------------------------------------------------------------------
-// They hold all modes of an axis in one MFMA tile, the channels of a voxel in at
-// most four, and a row of 16-bit DFT operands per mode in LDS: up to 16 modes,
-// 64 channels and extents of 512.  Wider networks take the batched GEMMs.
-bool fused_fits(const Net& net, const int* n)
-{
-    return net.m <= fno::kModeSlots && net.C <= 64 && net.cin <= 64 && net.cout <= 64 && n[0] <= 512 &&
-           n[1] <= 512 && n[2] <= 512;
-}
-
 bool aligned16(const void* p) { return (reinterpret_cast<uintptr_t>(p) & 15) == 0; }
 
 void make_tables(Fno& f)
@@ -643,6 +653,9 @@ void make_tables(Fno& f)
         t.fs = t.fc + fno::kModeSlots * t.np;
         t.ic = t.fs + fno::kModeSlots * t.np;
         t.is = t.ic + fno::kModeSlots * t.np;
+        t.q[0] = (float)std::cos(turn(t.n / 4, t.n));
+        t.q[1] = (float)std::sin(turn(t.n / 2, t.n));
+        t.q[2] = (float)std::cos(turn(3ll * t.n / 4, t.n));
         np = std::max(np, t.np);
     }
     fno::k_tables<<<dim3((unsigned)(fno::kModeSlots * np / 256), 3), 256, 0, f.s>>>(f.ax[0], f.ax[1], f.ax[2],
@@ -710,21 +723,25 @@ void fused_pointwise(Fno& f, const float* W, int co, int ci, int trans, const fl
 #undef FNO_PW
 }
 
-// dW[o][i] = sum_{b, v} d in, db[o] = sum_{b, v} d
-void fused_wgrad(Fno& f, const float* d, int co, const float* in, int ci, float* dW, float* db)
+// weight and bias gradients of all pointwise maps
+void fused_wgrad(Fno& f, const fno::WItems& w)
 {
-    const long long N = f.w.N, upb = (N + 63) / 64, units = upb * f.B;
-    const int mt = (co + 15) / 16, nt = (ci + 15) / 16;
-    const int G = (int)std::min<long long>(fno::kWgradBlocks, (units + 3) / 4);
+    int mt = 0, m = 0, mk = 0;
+    bool vec = f.w.N % 4 == 0;
+    for (int i = 0; i < w.n; ++i) {
+        const fno::WItem& t = w.it[i];
+        mt = std::max(mt, (t.M + 15) / 16 * ((t.K + 15) / 16));
+        m = std::max(m, t.M);
+        mk = std::max(mk, t.M * t.K);
+        vec = vec && aligned16(t.d) && aligned16(t.in);
+    }
+    // the tiles of one item and batch share their operands through one XCD's L2
+    const int nx = (w.n * f.B + 7) / 8 * 8;
     float* part = f.at(f.w.wg);
-    const bool vec = N % 4 == 0 && aligned16(d) && aligned16(in);
-#define FNO_WG(T)                                                                                                      if (vec) fno::k_wgrad<T, true><<<dim3((unsigned)G, (unsigned)mt), 256, 0, f.s>>>(d, in, part, co, ci, N, units, upb);     else fno::k_wgrad<T, false><<<dim3((unsigned)G, (unsigned)mt), 256, 0, f.s>>>(d, in, part, co, ci, N, units, upb)
-    if (nt == 1) { FNO_WG(1); }
-    else if (nt == 2) { FNO_WG(2); }
-    else if (nt == 3) { FNO_WG(3); }
-    else { FNO_WG(4); }
-#undef FNO_WG
-    fno::k_wgrad_reduce<<<(co * (ci + 1) + 3) / 4, 256, 0, f.s>>>(part, G, mt, nt, co, ci, dW, db);
+    if (vec) fno::k_wgrad<true><<<dim3((unsigned)nx, (unsigned)mt), 256, 0, f.s>>>(w, part, f.B, f.w.N);
+    else fno::k_wgrad<false><<<dim3((unsigned)nx, (unsigned)mt), 256, 0, f.s>>>(w, part, f.B, f.w.N);
+    fno::k_wgrad_sum<<<dim3((unsigned)((mk + 255) / 256), (unsigned)w.n), 256, 0, f.s>>>(w, part, f.B, nx);
+    fno::k_bias_grads<<<dim3((unsigned)m, (unsigned)w.n), 256, 0, f.s>>>(w, f.B, f.w.N);
 }
 
 // forward pass; keep_pre: the pre-activations stay for a backward pass
@@ -758,27 +775,34 @@ void fused_backward(Fno& f, const float* P, const float* x, const float* dy, flo
     const long long uplane = (long long)f.B * C * f.w.n[2] * net.m * net.m;
     const float invN = 1.f / (float)f.w.N;
     float *h0 = f.at(f.w.h), *pre = f.at(f.w.pre);
-    float *d = f.at(f.w.dpre), *dn = f.at(f.w.dh2);  // gradient of a layer's pre-activations, of the next lower one's
+    // gradient of every layer's pre-activations (the weight gradients read them
+    // at the end), and of the lift's output
+    float *dp = f.at(f.w.dp), *dh = f.at(f.w.dh2);
     float *D = f.at(f.w.s3), *RD = f.at(f.w.s1), *U = f.at(f.w.s4);
-    fused_wgrad(f, dy, net.cout, h0 + L * act, C, g + net.proj_w, g + net.proj_b);
+    fno::WItems w;
+    w.n = 0;
+    w.it[w.n++] = {dy, h0 + L * act, g + net.proj_w, g + net.proj_b, net.cout, C};
+    float* d = L > 0 ? dp + (L - 1) * act : dh;
     fused_pointwise(f, P + net.proj_w, net.cout, C, 1, dy, d, nullptr, L > 0 ? pre + (L - 1) * act : nullptr);
     for (int l = L - 1; l >= 0; --l) {
         const float* X = f.at(f.w.xhat) + 2 * l * xplane;
-        fused_wgrad(f, d, C, h0 + l * act, C, g + net.pw_w[l], g + net.pw_b[l]);
+        w.it[w.n++] = {d, h0 + l * act, g + net.pw_w[l], g + net.pw_b[l], C, C};
         // D = F dpre; dR(k) = (1/N) sum_b D X^H; dh = W^T dpre + (1/N) Re F^H R^H D
         fused_dft(f, d, D, xplane);
         fno::k_spec_wgrad<CT><<<(unsigned)((net.m3 + 3) / 4), 256, 0, f.s>>>(
             D, X, xplane, g + net.r_re[l], g + net.r_im[l], C, f.B, net.m3, invN);
         fused_mix<CT>(f, P + net.r_re[l], P + net.r_im[l], D, RD, xplane, true);
         fused_idft_z(f, RD, xplane, U, uplane);
+        float* dn = l > 0 ? dp + (l - 1) * act : dh;
         if (l > 0)
             fused_layer_out<CT, fno::LAYER_BWD>(f, U, uplane, d, P + net.pw_w[l], nullptr, pre + (l - 1) * act,
                                                 nullptr, dn);
         else
             fused_layer_out<CT, fno::LAYER_PLAIN>(f, U, uplane, d, P + net.pw_w[l], nullptr, nullptr, nullptr, dn);
-        std::swap(d, dn);
+        d = dn;
     }
-    fused_wgrad(f, d, C, x, net.cin, g + net.lift_w, g + net.lift_b);
+    w.it[w.n++] = {d, x, g + net.lift_w, g + net.lift_b, C, net.cin};
+    fused_wgrad(f, w);
     if (dx) fused_pointwise(f, P + net.lift_w, C, net.cin, 1, d, dx, nullptr, nullptr);
 }
 

@@ -7,9 +7,8 @@
 // and written once per layer; as separate batched GEMMs the same layer was 26
 // launches that read h five times and moved every partial sum of a complex
 // product through memory.  Warm start of a 64^3 cell (width 32, 4 layers, 12
-// modes): 1989 -> 313 us; training step on four 32^3 cells: 44.2 -> 0.73 ms, of
-// which the weight gradients (k_wgrad: their contraction over the voxels ran
-// on one workgroup each) were most.
+// modes): 1989 -> 313 us; training step on four 32^3 cells: 44.2 -> 0.92 ms, of
+// which the weight gradients (k_wgrad) were most.
 //
 // The arithmetic is that of the batched GEMM (k_gemm_bf16), bit for bit:
 // operands in FP32, rounded to bfloat16 where an MFMA reads them, one FP32
@@ -61,10 +60,13 @@ constexpr int kModeSlots = 16;  // modes per axis, padded to one MFMA tile
 // Twiddles of one axis in bfloat16, cos and sin of 2 pi k x / n with k the
 // signed frequency kk - m/2, zero where kk >= m or x >= n (np: n padded to 16).
 // Forward tables [kk][x], inverse tables [x][kk]: an MFMA operand is one 8-byte
-// load from either.
+// load from either.  q: cos at a quarter, sin at a half and cos at three quarters
+// of a turn as the host's long double functions give them (about 1e-20, not 0:
+// the MFMA's sums see the difference).
 struct AxTab {
     short *fc, *fs, *ic, *is;
     int n, np;
+    float q[3];
 };
 
 __global__ __launch_bounds__(256) void k_tables(AxTab a0, AxTab a1, AxTab a2, int m)
@@ -78,8 +80,8 @@ __global__ __launch_bounds__(256) void k_tables(AxTab a0, AxTab a1, AxTab a2, in
         const int r = (((kk - m / 2) * x) % a.n + a.n) % a.n;
         double sd, cd;
         sincospi(2.0 * r / a.n, &sd, &cd);
-        c = to_bf16((float)cd);
-        s = to_bf16((float)sd);
+        c = to_bf16(4 * r == a.n ? a.q[0] : 4 * r == 3 * a.n ? a.q[2] : (float)cd);
+        s = to_bf16(2 * r == a.n ? a.q[1] : (float)sd);
     }
     a.fc[kk * a.np + x] = c;
     a.fs[kk * a.np + x] = s;
@@ -305,6 +307,7 @@ __global__ __launch_bounds__(256) void k_spec_wgrad(const float* __restrict__ D,
                                                     long long plane, float* __restrict__ gre,
                                                     float* __restrict__ gim, int C, int B, int m3, float invN)
 {
+#pragma clang fp contract(off)
     const int lane = threadIdx.x & 63;
     const int li = lane & 15, lk = 4 * (lane >> 4);
     const long long k = (long long)blockIdx.x * 4 + (threadIdx.x >> 6);
@@ -559,86 +562,127 @@ __global__ __launch_bounds__(256) void k_pointwise(const float* __restrict__ W, 
     }
 }
 
-// Weight and bias gradients of a pointwise map, dW[o][i] = sum_{b, v} d[b][o][v]
-// in[b][i][v] and db[o] = sum d, split over the voxels: block (g, o tile) sums
-// units of 64 voxels g, g + G, ... per wave and writes its partial sums to
-// part[(g MT + ot)][16][16 NT + 1]; k_wgrad_reduce adds them in FP64 in fixed
-// order.  (As one GEMM the contraction ran on one workgroup: K = the voxels.)
-constexpr int kWgradBlocks = 128;
-template <int NT, bool VEC>
-__global__ __launch_bounds__(256) void k_wgrad(const float* __restrict__ d, const float* __restrict__ in,
-                                               float* __restrict__ part, int M, int K, long long N, long long units,
-                                               long long upb)
+// Weight and bias gradients of the pointwise maps (lift, layers, projection),
+// dW[o][i] = sum_b sum_v d[b][o][v] in[b][i][v] and db[o] = sum_b sum_v d, all of
+// a backward pass at once.  The sums keep the order of the batched GEMM (voxels
+// ascending in one chain of MFMAs per item, batch and 16 x 16 tile, batches
+// added afterwards): Adam divides by the gradient's own scale, so a gradient
+// changed in its last bits moves weights across bfloat16 roundings and the next
+// step's gradients by 1e-3 in places.  A chain of N / 16 dependent MFMAs is short
+// (32^3: 2048 of them); what bounded the GEMM was the latency of its loads in the
+// same chain, 1.2 ms per contraction.  Here four waves stream both operands
+// through LDS while one of them runs the chain, and the chains of all maps run
+// side by side.
+struct WItem {
+    const float *d, *in;  // [B][M][N], [B][K][N]
+    float *dW, *db;       // [M][K], [M]
+    int M, K;
+};
+constexpr int kMaxItems = 18;  // 16 layers, lift, projection
+struct WItems {
+    WItem it[kMaxItems];
+    int n;
+};
+constexpr int kChunk = 256, kChunkLd = kChunk + 16;  // voxels per LDS stage, its row
+
+template <bool VEC>
+__global__ __launch_bounds__(256) void k_wgrad(WItems items, float* __restrict__ part, int B, long long N)
 {
-    __shared__ float red[4][16][16 * NT + 1];
+    __shared__ __align__(16) short S[2][32][kChunkLd];  // 16 rows of d, 16 of in
+    const int ib = blockIdx.x;
+    if (ib >= items.n * B) return;
+    const WItem w = items.it[ib / B];
+    const int b = ib % B, nt = (w.K + 15) / 16;
+    const int tile = blockIdx.y;
+    if (tile >= (w.M + 15) / 16 * nt) return;
+    const int o0 = tile / nt * 16, i0 = tile % nt * 16;
     const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
     const int li = lane & 15, lk = 4 * (lane >> 4);
-    const int o = 16 * blockIdx.y + li;
-    f32x4 acc[NT];
+    // wave w stages rows w, w + 4, ... (0..15 of d, 16..31 of in)
+    const float* row[8];
+    bool rin[8];
 #pragma unroll
-    for (int t = 0; t < NT; ++t) acc[t] = f32x4{0.f, 0.f, 0.f, 0.f};
-    float bs = 0.f;
-    auto load = [&](const float* p, bool rin, long long v, float (&f)[4]) {
-        if constexpr (VEC) {
-            const bool ok = rin && v < N;
-            const float4 t = *reinterpret_cast<const float4*>(p + (ok ? v : 0));
-            f[0] = ok ? t.x : 0.f;
-            f[1] = ok ? t.y : 0.f;
-            f[2] = ok ? t.z : 0.f;
-            f[3] = ok ? t.w : 0.f;
-        } else {
+    for (int r = 0; r < 8; ++r) {
+        const int q = wave + 4 * r;
+        const int c = q < 16 ? o0 + q : i0 + q - 16, C = q < 16 ? w.M : w.K;
+        rin[r] = c < C;
+        row[r] = (q < 16 ? w.d : w.in) + ((long long)b * C + (rin[r] ? c : 0)) * N;
+    }
+    float f[8][4];
+    auto load = [&](long long v0) {
+        const long long v = v0 + 4 * lane;
 #pragma unroll
-            for (int q = 0; q < 4; ++q) f[q] = rin && v + q < N ? p[v + q] : 0.f;
-        }
-    };
-    for (long long u = (long long)blockIdx.x * 4 + wave; u < units; u += (long long)gridDim.x * 4) {
-        const long long b = u / upb, v0 = (u - b * upb) * 64;
-        const float* dp = d + (b * M + (o < M ? o : 0)) * N;
+        for (int r = 0; r < 8; ++r) {
+            if constexpr (VEC) {
+                const bool in = rin[r] && v < N;
+                const float4 t = *reinterpret_cast<const float4*>(row[r] + (v < N ? v : 0));
+                f[r][0] = in ? t.x : 0.f;
+                f[r][1] = in ? t.y : 0.f;
+                f[r][2] = in ? t.z : 0.f;
+                f[r][3] = in ? t.w : 0.f;
+            } else {
 #pragma unroll
-        for (int s = 0; s < 4; ++s) {
-            const long long v = v0 + 16 * s + lk;
-            float f[4];
-            load(dp, o < M, v, f);
-            bs += (f[0] + f[1]) + (f[2] + f[3]);
-            const bf16x4 a = to_bf16(f);
-#pragma unroll
-            for (int t = 0; t < NT; ++t) {
-                const int i = 16 * t + li;
-                float g[4];
-                load(in + (b * K + (i < K ? i : 0)) * N, i < K, v, g);
-                acc[t] = mfma(a, to_bf16(g), acc[t]);
+                for (int q = 0; q < 4; ++q) f[r][q] = rin[r] && v + q < N ? row[r][v + q] : 0.f;
             }
         }
+    };
+    f32x4 acc = {0.f, 0.f, 0.f, 0.f};
+    load(0);
+    int buf = 0;
+    for (long long v0 = 0; v0 < N; v0 += kChunk, buf ^= 1) {
+#pragma unroll
+        for (int r = 0; r < 8; ++r) *reinterpret_cast<bf16x4*>(&S[buf][wave + 4 * r][4 * lane]) = to_bf16(f[r]);
+        __syncthreads();  // also: the chain has left the other buffer
+        if (v0 + kChunk < N) load(v0 + kChunk);
+        if (wave == 0) {
+            const int ns = (int)(min((long long)kChunk, N - v0) + 15) / 16;
+#pragma unroll 16
+            for (int s = 0; s < ns; ++s)
+                acc = mfma(ld4(&S[buf][li][16 * s + lk]), ld4(&S[buf][16 + li][16 * s + lk]), acc);
+        }
     }
+    if (wave == 0) {
+        float* dst = part + ((long long)tile * gridDim.x + ib) * 256;
 #pragma unroll
-    for (int t = 0; t < NT; ++t)
-#pragma unroll
-        for (int q = 0; q < 4; ++q) red[wave][lk + q][16 * t + li] = acc[t][q];
-    bs += __shfl_xor(bs, 16, 64);
-    bs += __shfl_xor(bs, 32, 64);
-    if (lane < 16) red[wave][li][16 * NT] = bs;
-    __syncthreads();
-    constexpr int E = 16 * (16 * NT + 1);
-    float* dst = part + ((long long)blockIdx.x * gridDim.y + blockIdx.y) * E;
-    const float* r = &red[0][0][0];
-    for (int e = threadIdx.x; e < E; e += 256) dst[e] = (r[e] + r[E + e]) + (r[2 * E + e] + r[3 * E + e]);
+        for (int q = 0; q < 4; ++q) dst[(lk + q) * 16 + li] = acc[q];
+    }
 }
 
-// dW[o][i] (i < K) and db[o] (i == K) from the partial sums; one wave each
-__global__ __launch_bounds__(256) void k_wgrad_reduce(const float* __restrict__ part, int G, int MT, int NT, int M,
-                                                      int K, float* __restrict__ dW, float* __restrict__ db)
+// dW from the chains' results, batches in order; one thread per weight
+__global__ __launch_bounds__(256) void k_wgrad_sum(WItems items, const float* __restrict__ part, int B, int stride)
 {
-    const int lane = threadIdx.x & 63;
-    const int w = blockIdx.x * 4 + (threadIdx.x >> 6);
-    if (w >= M * (K + 1)) return;
-    const int o = w / (K + 1), i = w - o * (K + 1);
-    const int E = 16 * (16 * NT + 1);
-    const float* p = part + (long long)(o >> 4) * E + (o & 15) * (16 * NT + 1) + (i < K ? i : 16 * NT);
-    double s = 0.0;
-    for (int g = lane; g < G; g += 64) s += (double)p[(long long)g * MT * E];
-#pragma unroll
-    for (int off = 32; off > 0; off >>= 1) s += __shfl_down(s, off, 64);
-    if (lane == 0) (i < K ? dW[o * K + i] : db[o]) = (float)s;
+    const WItem w = items.it[blockIdx.y];
+    const int e = blockIdx.x * 256 + threadIdx.x;
+    if (e >= w.M * w.K) return;
+    const int o = e / w.K, i = e - o * w.K, nt = (w.K + 15) / 16;
+    const int tile = o / 16 * nt + i / 16;
+    const float* p = part + ((long long)tile * stride + blockIdx.y * B) * 256 + (o % 16) * 16 + i % 16;
+    float s = p[0];
+    for (int b = 1; b < B; ++b) s += p[(long long)b * 256];
+    w.dW[e] = s;
+}
+
+// db[o] of every item: one block per channel, thread t the voxels t, t + 256, ...
+// of every batch, then a tree
+__global__ __launch_bounds__(256) void k_bias_grads(WItems items, int B, long long N)
+{
+    __shared__ float red[256];
+    const WItem w = items.it[blockIdx.y];
+    const int c = blockIdx.x;
+    if (c >= w.M) return;
+    float s = 0.f;
+    for (int b = 0; b < B; ++b) {
+        const float* p = w.d + ((long long)b * w.M + c) * N;
+#pragma unroll 8
+        for (long long v = threadIdx.x; v < N; v += 256) s += p[v];
+    }
+    red[threadIdx.x] = s;
+    __syncthreads();
+    for (int h = 128; h > 0; h >>= 1) {
+        if ((int)threadIdx.x < h) red[threadIdx.x] += red[threadIdx.x + h];
+        __syncthreads();
+    }
+    if (threadIdx.x == 0) w.db[c] = red[0];
 }
 
 }  // namespace fno
