@@ -191,13 +191,19 @@ __global__ __launch_bounds__(256) void k_mse(const float* __restrict__ y, const 
                                              float* __restrict__ dy, double* __restrict__ part, long long n)
 {
     __shared__ double red[256];
+    // a thread takes all channels of a voxel: one weight per voxel
     double s = 0.0;
-    for (long long i = (long long)blockIdx.x * 256 + threadIdx.x; i < n; i += (long long)gridDim.x * 256) {
-        const long long v = i % N, b = i / (N * cout);
+    const long long nv = n / cout;  // voxels of all batches
+    for (long long i = (long long)blockIdx.x * 256 + threadIdx.x; i < nv; i += (long long)gridDim.x * 256) {
+        const long long b = i / N, v = i - b * N;
         const float w = x ? expf(6.90775527898f * x[b * cin * N + v]) : 1.f;
-        const float e = y[i] - t[i];
-        if (dy) dy[i] = 2.f * w * e / (float)n;
-        s += (double)w * e * e;
+#pragma unroll 18
+        for (int c = 0; c < cout; ++c) {
+            const long long o = (b * cout + c) * N + v;
+            const float e = y[o] - t[o];
+            if (dy) dy[o] = 2.f * w * e / (float)n;
+            s += (double)w * e * e;
+        }
     }
     red[threadIdx.x] = s;
     __syncthreads();
@@ -738,8 +744,8 @@ void fused_wgrad(Fno& f, const fno::WItems& w)
     // the tiles of one item and batch share their operands through one XCD's L2
     const int nx = (w.n * f.B + 7) / 8 * 8;
     float* part = f.at(f.w.wg);
-    if (vec) fno::k_wgrad<true><<<dim3((unsigned)nx, (unsigned)mt), 256, 0, f.s>>>(w, part, f.B, f.w.N);
-    else fno::k_wgrad<false><<<dim3((unsigned)nx, (unsigned)mt), 256, 0, f.s>>>(w, part, f.B, f.w.N);
+    if (vec) fno::k_wgrad<true><<<dim3((unsigned)nx, (unsigned)mt), fno::kWgradThreads, 0, f.s>>>(w, part, f.B, f.w.N);
+    else fno::k_wgrad<false><<<dim3((unsigned)nx, (unsigned)mt), fno::kWgradThreads, 0, f.s>>>(w, part, f.B, f.w.N);
     fno::k_wgrad_sum<<<dim3((unsigned)((mk + 255) / 256), (unsigned)w.n), 256, 0, f.s>>>(w, part, f.B, nx);
     fno::k_bias_grads<<<dim3((unsigned)m, (unsigned)w.n), 256, 0, f.s>>>(w, f.B, f.w.N);
 }
@@ -954,7 +960,7 @@ rpm_status rpm_fno_train_step(const rpm_fno_config* cfg, float* params, float* g
     const long long ny = (long long)batch * f.net.cout * f.w.N;
     // the output gradient in the accumulator slot (backward does not use it)
     float* dy = f.at(f.w.acc);
-    const int nb = (int)std::min<long long>(1024, (ny + 255) / 256);
+    const int nb = (int)std::min<long long>(1024, (batch * f.w.N + 255) / 256);
     double* part = reinterpret_cast<double*>(f.at(f.w.part));
     k_mse<<<nb, 256, 0, f.s>>>(f.at(f.w.y), target, x, f.net.cin, f.net.cout, f.w.N, dy, part, ny);
     net_backward(f, params, x, dy, grad, nullptr);

@@ -25,16 +25,12 @@ namespace fno {
 typedef short bf16x4 __attribute__((ext_vector_type(4)));
 typedef float f32x4 __attribute__((ext_vector_type(4)));
 
-__device__ __forceinline__ short to_bf16(float f)
-{
-    uint32_t u = __float_as_uint(f);
-    if ((u & 0x7f800000u) == 0x7f800000u) return (short)(u >> 16);  // inf / nan kept
-    u += 0x7fffu + ((u >> 16) & 1u);
-    return (short)(u >> 16);
-}
+// round to nearest even (v_cvt_pk_bf16_f32)
+__device__ __forceinline__ short to_bf16(float f) { return __builtin_bit_cast(short, (__bf16)f); }
 __device__ __forceinline__ bf16x4 to_bf16(const float (&f)[4])
 {
-    return bf16x4{to_bf16(f[0]), to_bf16(f[1]), to_bf16(f[2]), to_bf16(f[3])};
+    typedef __bf16 h4 __attribute__((ext_vector_type(4)));
+    return __builtin_bit_cast(bf16x4, __builtin_convertvector((f32x4{f[0], f[1], f[2], f[3]}), h4));
 }
 // v_mfma_f32_16x16x16_bf16: lane l holds A(l % 16, 4 (l / 16) + q) and
 // B(4 (l / 16) + q, l % 16), and receives C(4 (l / 16) + q, l % 16), q < 4
@@ -571,8 +567,8 @@ __global__ __launch_bounds__(256) void k_pointwise(const float* __restrict__ W, 
 // step's gradients by 1e-3 in places.  A chain of N / 16 dependent MFMAs is short
 // (32^3: 2048 of them); what bounded the GEMM was the latency of its loads in the
 // same chain, 1.2 ms per contraction.  Here four waves stream both operands
-// through LDS while one of them runs the chain, and the chains of all maps run
-// side by side.
+// through LDS while a fifth runs the chain, and the chains of all maps run side
+// by side.
 struct WItem {
     const float *d, *in;  // [B][M][N], [B][K][N]
     float *dW, *db;       // [M][K], [M]
@@ -585,8 +581,9 @@ struct WItems {
 };
 constexpr int kChunk = 256, kChunkLd = kChunk + 16;  // voxels per LDS stage, its row
 
+constexpr int kWgradThreads = 320;
 template <bool VEC>
-__global__ __launch_bounds__(256) void k_wgrad(WItems items, float* __restrict__ part, int B, long long N)
+__global__ __launch_bounds__(kWgradThreads) void k_wgrad(WItems items, float* __restrict__ part, int B, long long N)
 {
     __shared__ __align__(16) short S[2][32][kChunkLd];  // 16 rows of d, 16 of in
     const int ib = blockIdx.x;
@@ -598,47 +595,73 @@ __global__ __launch_bounds__(256) void k_wgrad(WItems items, float* __restrict__
     const int o0 = tile / nt * 16, i0 = tile % nt * 16;
     const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
     const int li = lane & 15, lk = 4 * (lane >> 4);
-    // wave w stages rows w, w + 4, ... (0..15 of d, 16..31 of in)
+    // wave 0 runs the chain; wave w > 0 stages rows w - 1, w + 3, ... (0..15 of d,
+    // 16..31 of in)
     const float* row[8];
     bool rin[8];
 #pragma unroll
     for (int r = 0; r < 8; ++r) {
-        const int q = wave + 4 * r;
+        const int q = max(wave - 1, 0) + 4 * r;
         const int c = q < 16 ? o0 + q : i0 + q - 16, C = q < 16 ? w.M : w.K;
         rin[r] = c < C;
         row[r] = (q < 16 ? w.d : w.in) + ((long long)b * C + (rin[r] ? c : 0)) * N;
     }
-    float f[8][4];
-    auto load = [&](long long v0) {
+    // loads of the next D stages in flight: one stage ahead, the loop waited on
+    // memory latency (2.1 us per stage of 0.2 us of work)
+    constexpr int D = 4;
+    float f[D][8][4];
+    auto load = [&](float (&g)[8][4], long long v0) {
         const long long v = v0 + 4 * lane;
 #pragma unroll
         for (int r = 0; r < 8; ++r) {
             if constexpr (VEC) {
                 const bool in = rin[r] && v < N;
                 const float4 t = *reinterpret_cast<const float4*>(row[r] + (v < N ? v : 0));
-                f[r][0] = in ? t.x : 0.f;
-                f[r][1] = in ? t.y : 0.f;
-                f[r][2] = in ? t.z : 0.f;
-                f[r][3] = in ? t.w : 0.f;
+                g[r][0] = in ? t.x : 0.f;
+                g[r][1] = in ? t.y : 0.f;
+                g[r][2] = in ? t.z : 0.f;
+                g[r][3] = in ? t.w : 0.f;
             } else {
 #pragma unroll
-                for (int q = 0; q < 4; ++q) f[r][q] = rin[r] && v + q < N ? row[r][v + q] : 0.f;
+                for (int q = 0; q < 4; ++q) g[r][q] = rin[r] && v + q < N ? row[r][v + q] : 0.f;
             }
         }
     };
     f32x4 acc = {0.f, 0.f, 0.f, 0.f};
-    load(0);
-    int buf = 0;
-    for (long long v0 = 0; v0 < N; v0 += kChunk, buf ^= 1) {
 #pragma unroll
-        for (int r = 0; r < 8; ++r) *reinterpret_cast<bf16x4*>(&S[buf][wave + 4 * r][4 * lane]) = to_bf16(f[r]);
-        __syncthreads();  // also: the chain has left the other buffer
-        if (v0 + kChunk < N) load(v0 + kChunk);
-        if (wave == 0) {
-            const int ns = (int)(min((long long)kChunk, N - v0) + 15) / 16;
-#pragma unroll 16
-            for (int s = 0; s < ns; ++s)
-                acc = mfma(ld4(&S[buf][li][16 * s + lk]), ld4(&S[buf][16 + li][16 * s + lk]), acc);
+    for (int u = 0; u < D; ++u)
+        if (wave > 0 && u * kChunk < N) load(f[u], u * kChunk);
+    for (long long base = 0; base < N; base += D * kChunk) {
+#pragma unroll
+        for (int u = 0; u < D; ++u) {
+            const long long v0 = base + u * kChunk;
+            if (v0 >= N) break;
+            const int buf = u & 1;
+            if (wave > 0)
+#pragma unroll
+                for (int r = 0; r < 8; ++r)
+                    *reinterpret_cast<bf16x4*>(&S[buf][wave - 1 + 4 * r][4 * lane]) = to_bf16(f[u][r]);
+            __syncthreads();  // also: the chain has left the other buffer
+            if (wave > 0) {
+                if (v0 + D * kChunk < N) load(f[u], v0 + D * kChunk);
+            } else {
+                const short* da = &S[buf][li][lk];
+                const short* db = &S[buf][16 + li][lk];
+                if (v0 + kChunk <= N) {
+                    // all operands first, then the chain
+                    bf16x4 a[kChunk / 16], c[kChunk / 16];
+#pragma unroll
+                    for (int s = 0; s < kChunk / 16; ++s) {
+                        a[s] = ld4(da + 16 * s);
+                        c[s] = ld4(db + 16 * s);
+                    }
+#pragma unroll
+                    for (int s = 0; s < kChunk / 16; ++s) acc = mfma(a[s], c[s], acc);
+                } else {
+                    for (int s = 0; s < (int)(N - v0 + 15) / 16; ++s)
+                        acc = mfma(ld4(da + 16 * s), ld4(db + 16 * s), acc);
+                }
+            }
         }
     }
     if (wave == 0) {
