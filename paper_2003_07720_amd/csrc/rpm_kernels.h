@@ -83,6 +83,7 @@ struct DevHead {
     int singular;      // LU of I - H hit a tiny pivot
     int max_iter;
     int pad1;
+    double gram[3];    // Gram entries of the differences that feed a basis growth
     double tol;
     double err0;       // error of the starting iterate
     double err;        // error of the latest iterate
@@ -1492,78 +1493,61 @@ __global__ __launch_bounds__(kThreads) void k_tdots(TA* __restrict__ a0, TA* __r
 // ---------------------------------------------------------------------------
 // Reductions of per-block partial sums (fixed order: deterministic).
 // ---------------------------------------------------------------------------
-// out[j] = sum_b part[b * bs + j * cs], j < m.  grid: m.
+// out[f * os + j] = sum_b part[f * fs + b * bs + j * cs].  grid: (j, f).
 static __global__ __launch_bounds__(kThreads) void k_reduce_cols(const double* __restrict__ part, int G, long long bs,
-                                                          long long cs, double* __restrict__ out)
+                                                                 long long cs, long long fs, int os,
+                                                                 double* __restrict__ out)
 {
     __shared__ double red[kWaves];
     __shared__ double tot[1];
-    const int j = blockIdx.x;
+    const int j = blockIdx.x, f = blockIdx.y;
     double acc = 0.0;
-    for (int b = threadIdx.x; b < G; b += kThreads) acc += part[(long long)b * bs + j * cs];
+    const double* src = part + f * fs + j * cs;
+    for (int b = threadIdx.x; b < G; b += kThreads) acc += src[(long long)b * bs];
     double v[1] = {acc};
     wg_sum_store<1>(v, tot, red);
-    if (threadIdx.x == 0) out[j] = tot[0];
+    if (threadIdx.x == 0) out[f * os + j] = tot[0];
 }
 
 // ---------------------------------------------------------------------------
-// Reductions at the end of a step, one block per output: out[0] = sum of the
-// error partials (part_err, G_err entries); out[1 + q] for q < nf * p = sum of
-// partial column map(q) of the basis products (column-major part_dots, G_dots
-// per column: zeta_j at column j and, nf = 2, z_j at column ld + j).  Fixed
-// order: deterministic.
-// ---------------------------------------------------------------------------
-static __global__ __launch_bounds__(kThreads) void k_reduce_main(const double* __restrict__ part_err, int G_err,
-                                                          const double* __restrict__ part_dots, int G_dots, int ld,
-                                                          int p, double* __restrict__ out,
-                                                          const int* __restrict__ done)
-{
-    if (done && *done) return;
-    __shared__ double red[kWaves];
-    __shared__ double tot[1];
-    const int o = blockIdx.x;
-    double acc = 0.0;
-    if (o == 0) {
-        if (part_err)
-            for (int b = threadIdx.x; b < G_err; b += kThreads) acc += part_err[b];
-    } else {
-        const int q = o - 1;
-        const double* src = part_dots + (long long)(q < p ? q : ld + (q - p)) * G_dots;
-        for (int b = threadIdx.x; b < G_dots; b += kThreads) acc += src[b];
-    }
-    double v[1] = {acc};
-    wg_sum_store<1>(v, tot, red);
-    if (threadIdx.x == 0) out[o] = tot[0];
-}
-
-// ---------------------------------------------------------------------------
-// End of a step (one block of kThreads) on the reduced sums: the equilibrium
-// error of the iterate that went through F, the convergence / divergence /
-// budget tests, and the Newton step on the unstable subspace
+// End of a step, one block of 16 waves: the sums of the per-block partials
+// (part_err: G_err of the error; column-major part_dots, G_dots per column:
+// zeta_j at column j and, direct, z_j at column ld + j), the equilibrium error
+// of the iterate that went through F, the convergence / divergence / budget
+// tests, and the Newton step on the unstable subspace
 // z' = z + (I - H)^{-1}(zeta - z), applied as a product with the inverse kept
 // by k_factor, giving the recombination coefficients d = z' - zeta for the
-// next iterate eps_next = xi + Z d.
-// direct: z = Z^T eps was reduced into sums (after a basis change or at the
+// next iterate eps_next = xi + Z d.  Fixed orders throughout: deterministic.
+// direct: z = Z^T eps comes from the partials (after a basis change or at the
 // start of a solve); otherwise eps = xi_prev + Z d_prev was built from the
 // stored pair, so z = zeta_prev + G d_prev with the Gram matrix G = Z^T Z
 // (the same numbers without a second pass over the basis).
 // newton_only: skip the error bookkeeping (used after basis growth).
+// Reading 270 KB of partials (p = 32 on 128^3) takes one CU about as long as a
+// second launch: with the sums in a kernel of their own the two took 6.2 + 4.7
+// us there, and 4.9 + 13.5 us for p = 64 on 64^3 (the matrix-vector products ran
+// on 64 threads).
 // ---------------------------------------------------------------------------
-static __global__ __launch_bounds__(kThreads) void k_step_end(DevState* __restrict__ st, const double* __restrict__ sums,
-                                                       int p, int slot, int two_d, int newton_only, int err_mode,
-                                                       int direct, double* __restrict__ hist, int hist_cap)
+constexpr int kStepThreads = 1024;
+static __global__ __launch_bounds__(kStepThreads) void k_step_end(DevState* __restrict__ st,
+                                                                  const double* __restrict__ part_err, int G_err,
+                                                                  const double* __restrict__ part_dots, int G_dots,
+                                                                  int ld, int p, int slot, int two_d,
+                                                                  int newton_only, int err_mode, int direct,
+                                                                  double* __restrict__ hist, int hist_cap)
 {
-    __shared__ int sdone, snow, ssing;
-    __shared__ double dprev[kMaxP], r[kMaxP];
+    constexpr int NW = kStepThreads / 64;
+    __shared__ int snow;
+    __shared__ double sums[2 * kMaxP], red[NW], dprev[kMaxP], r[kMaxP], mv[NW][kMaxP];
     __shared__ double Gs[kMaxP * kMaxP], Ai[kMaxP * kMaxP];
-    const int t = threadIdx.x;
+    const int t = threadIdx.x, lane = t & 63, wave = t >> 6;
+    if (st->done) return;  // uniform
+    const bool sing = st->singular != 0;
     // thread 0 reads every state scalar of the step at once (independent
     // loads, one memory round trip) before any decision
-    int done0 = 0, sing0 = 0, it0 = 0, maxit = 0, win = 0, bit = 0;
-    double err00 = 0.0, tol = 0.0, gnorm = 1.0, best = 0.0, num = 0.0, s[6] = {0, 0, 0, 0, 0, 0};
+    int it0 = 0, maxit = 0, win = 0, bit = 0;
+    double err00 = 0.0, tol = 0.0, gnorm = 1.0, best = 0.0, s[6] = {0, 0, 0, 0, 0, 0};
     if (t == 0) {
-        done0 = st->done;
-        sing0 = st->singular;
         it0 = st->iters;
         maxit = st->max_iter;
         win = st->stall_window;
@@ -1574,28 +1558,36 @@ static __global__ __launch_bounds__(kThreads) void k_step_end(DevState* __restri
         best = st->best_err;
 #pragma unroll
         for (int c = 0; c < 6; ++c) s[c] = st->sig_hat0[c];
-        num = sums[0];
-        sdone = done0;
-        ssing = sing0;
+    }
+    // the small matrices, in LDS while the partials arrive
+    for (int e = t; e < p * kMaxP; e += kStepThreads) {
+        if (!direct) Gs[e] = st->G[e];
+        Ai[e] = st->AinvT[e];
+    }
+    double zold = 0.0;
+    if (t < p) {
+        dprev[t] = st->d[t];
+        zold = st->zeta[t];
+    }
+    double acc = 0.0;
+    if (!newton_only)
+        for (int b = t; b < G_err; b += kStepThreads) acc += part_err[b];
+    acc = wave_sum(acc);
+    if (lane == 0) red[wave] = acc;
+    for (int o = wave; o < (direct ? 2 : 1) * p; o += NW) {
+        const double* src = part_dots + (long long)(o < p ? o : ld + (o - p)) * G_dots;
+        double v = 0.0;
+#pragma unroll 8
+        for (int b = lane; b < G_dots; b += 64) v += src[b];
+        v = wave_sum(v);
+        if (lane == 0) sums[o] = v;
     }
     __syncthreads();
-    if (sdone) return;  // uniform
-    // stage the small matrices while thread 0 does the bookkeeping
-    for (int e = t; e < p * p; e += kThreads) {
-        const int i = e / p, j = e - (e / p) * p;
-        if (!direct) Gs[i * kMaxP + j] = st->G[i * kMaxP + j];
-        Ai[i * kMaxP + j] = st->AinvT[i * kMaxP + j];
-    }
-    for (int j = t; j < p; j += kThreads) dprev[j] = st->d[j];
-    // this thread's basis coordinate (t < p): loads issued with the others
-    double ze = 0.0, zz = 0.0;
-    if (t < p) {
-        ze = sums[1 + t];
-        zz = direct ? sums[1 + p + t] : st->zeta[t];
-    }
     if (t == 0) {
         int done = 0;
         if (!newton_only) {
+            double num = 0.0;
+            for (int w = 0; w < NW; ++w) num += red[w];
             const double den = two_d ? (s[0] * s[0] + s[1] * s[1] + 2.0 * s[5] * s[5])
                                      : (s[0] * s[0] + s[1] * s[1] + s[2] * s[2] +
                                         2.0 * (s[3] * s[3] + s[4] * s[4] + s[5] * s[5]));
@@ -1635,31 +1627,47 @@ static __global__ __launch_bounds__(kThreads) void k_step_end(DevState* __restri
         }
         snow = done;
     }
-    __syncthreads();
+    if (p == 0) {
+        if (t == 0 && sing && !snow) {
+            st->status = 3;
+            st->done = 1;
+        }
+        return;
+    }
+    // products with a p x p matrix: wave w takes columns w, w + NW, ... of row lane
+    auto product = [&](const double* A, const double* x) {
+        double v = 0.0;
+        if (lane < p)
+            for (int j = wave; j < p; j += NW) v += A[j * kMaxP + lane] * x[j];
+        mv[wave][lane] = v;
+        __syncthreads();
+        double y = 0.0;
+        if (t < p)
+#pragma unroll
+            for (int w = 0; w < NW; ++w) y += mv[w][t];
+        return y;
+    };
+    double zz = 0.0;
+    if (!direct) zz = product(Gs, dprev) + zold;
     if (t < p) {
-        const int i = t;
-        if (!direct)
-            for (int j = 0; j < p; ++j) zz += Gs[j * kMaxP + i] * dprev[j];
-        st->zeta[i] = ze;
-        st->z[i] = zz;
-        st->zeta_ring[slot][i] = ze;
-        r[i] = ze - zz;
+        const double ze = sums[t];
+        if (direct) zz = sums[p + t];
+        st->zeta[t] = ze;
+        st->z[t] = zz;
+        st->zeta_ring[slot][t] = ze;
+        r[t] = ze - zz;
     }
     __syncthreads();
     if (snow) return;  // uniform
-    if (ssing) {
+    if (sing) {
         if (t == 0) {
             st->status = 3;
             st->done = 1;
         }
         return;
     }
-    if (t < p) {
-        const int i = t;
-        double y = 0.0;
-        for (int j = 0; j < p; ++j) y += Ai[j * kMaxP + i] * r[j];
-        st->d[i] = y - r[i];  // z' - zeta = (z + y) - zeta
-    }
+    const double y = product(Ai, r);
+    if (t < p) st->d[t] = y - r[t];  // z' - zeta = (z + y) - zeta
 }
 
 // Checksum of the phase map (part of the basis reuse key): wrapping sums over
@@ -1846,17 +1854,23 @@ static __global__ void k_reset_state(DevState* __restrict__ st)
     }
 }
 
-// H gains row and column p: H[i][p] = col[i] (i <= p), H[p][j] = row[j] (j < p);
-// the Gram matrix gains gram[j] = <Z_p, Z_j> (j <= p) in row and column p.
-static __global__ void k_border(DevState* __restrict__ st, const double* __restrict__ col, const double* __restrict__ row,
-                         const double* __restrict__ gram, int p)
+// H gains rows and columns p .. p + n - 1: new column a has H[i][p + a] = col[i]
+// (i <= p + a) and H[p + a][j] = row[j] (j < p + a), and the Gram matrix gains
+// gram[j] = <Z_{p+a}, Z_j> (j <= p + a) in row and column p + a; col and gram of
+// column a at HZ + 2 a ld and HZ + (2 a + 1) ld, row at RW + a kMaxP.
+static __global__ __launch_bounds__(64) void k_border(DevState* __restrict__ st, const double* __restrict__ HZ, int ld,
+                                                      const double* __restrict__ RW, int p, int n)
 {
-    if (threadIdx.x != 0) return;
-    for (int i = 0; i <= p; ++i) st->H[i * kMaxP + p] = col[i];
-    for (int j = 0; j < p; ++j) st->H[p * kMaxP + j] = row[j];
-    for (int j = 0; j <= p; ++j) {
-        st->G[p * kMaxP + j] = gram[j];
-        st->G[j * kMaxP + p] = gram[j];
+    const int i = threadIdx.x;
+    for (int a = 0; a < n; ++a) {
+        const int q = p + a;
+        if (i <= q) {
+            const double g = HZ[(2 * a + 1) * ld + i];
+            st->H[i * kMaxP + q] = HZ[2 * a * ld + i];
+            st->G[q * kMaxP + i] = g;
+            st->G[i * kMaxP + q] = g;
+        }
+        if (i < q) st->H[q * kMaxP + i] = RW[a * kMaxP + i];
     }
 }
 
@@ -1885,28 +1899,38 @@ static __global__ __launch_bounds__(64) void k_factor(DevState* __restrict__ st,
     }
     __syncthreads();
     for (int c = 0; c < p; ++c) {
+        // largest |A[r][c]|, r >= c, the first of equal ones
+        double m = c + t < p ? fabs(A[(c + t) * LD + c]) : -1.0;
+        int q = c + t;
+#pragma unroll
+        for (int off = 32; off > 0; off >>= 1) {
+            const double m2 = __shfl_down(m, off, 64);
+            const int q2 = __shfl_down(q, off, 64);
+            if (m2 > m || (m2 == m && q2 < q)) {
+                m = m2;
+                q = q2;
+            }
+        }
         if (t == 0) {
-            int q = c;
-            for (int r = c + 1; r < p; ++r)
-                if (fabs(A[r * LD + c]) > fabs(A[q * LD + c])) q = r;
             piv_s = q;
             st->piv[c] = q;
             if (!(fabs(A[q * LD + c]) > 1e-14 * amax_s)) sing_s = 1;
         }
         __syncthreads();
         if (sing_s) break;
-        const int q = piv_s;
-        if (q != c)
+        const int qp = piv_s;
+        if (qp != c)
             for (int j = t; j < p; j += 64) {
                 const double tmp = A[c * LD + j];
-                A[c * LD + j] = A[q * LD + j];
-                A[q * LD + j] = tmp;
+                A[c * LD + j] = A[qp * LD + j];
+                A[qp * LD + j] = tmp;
             }
         __syncthreads();
         const int r = c + 1 + t;
         if (r < p) {
             const double f = A[r * LD + c] / A[c * LD + c];
             A[r * LD + c] = f;
+#pragma unroll 8
             for (int j = c + 1; j < p; ++j) A[r * LD + j] -= f * A[c * LD + j];
         }
         __syncthreads();
@@ -1935,11 +1959,13 @@ static __global__ __launch_bounds__(64) void k_factor(DevState* __restrict__ st,
     if (t < p) {
         for (int i = 0; i < p; ++i) {  // unit lower triangle
             double v = perm[i] == t ? 1.0 : 0.0;
+#pragma unroll 8
             for (int k = 0; k < i; ++k) v -= A[i * LD + k] * X[k * kMaxP + t];
             X[i * kMaxP + t] = v;
         }
         for (int i = p - 1; i >= 0; --i) {  // upper triangle
             double v = X[i * kMaxP + t];
+#pragma unroll 8
             for (int k = i + 1; k < p; ++k) v -= A[i * LD + k] * X[k * kMaxP + t];
             X[i * kMaxP + t] = v / A[i * LD + i];
         }

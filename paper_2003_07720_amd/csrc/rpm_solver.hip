@@ -237,11 +237,11 @@ Shapes<T> make_shapes(const int32_t n[3], int ncomp, const rpm_tuning* tn = null
 
 // Per-load-case state of a batched solve (case 0 uses the base offsets).
 struct CaseOff {
-    size_t st, pmean, perr, pinc, pdots, sums, gsum, ring[4], eps, hist;
+    size_t st, pmean, perr, pinc, pdots, gsum, ring[4], eps, hist;
 };
 
 struct Layout {
-    size_t st, twx, twy, twr, lame, hist, pmean, perr, pinc, pdots, pg, sums, gsum, gx, ring[4], eps, tmp, tmp2, S1, S2,
+    size_t st, twx, twy, twr, lame, hist, pmean, perr, pinc, pdots, pg, gsum, gx, ring[4], eps, tmp, tmp2, S1, S2,
         Z, W, D1, D0, shift, sub64, total;
     int ld;
     long long hist_cap;
@@ -301,7 +301,6 @@ Layout make_layout(const Shapes<T>& s, const rpm_options* o, bool map_only)
     const long long Gd = (6 * g.N + 4 * kThreads - 1) / (4 * kThreads);  // k_growth_diff blocks (3 partials each)
     L.pg = take(sizeof(double) * std::max((size_t)(4 * kMaxP + 4) * std::max(std::max(s.Gg, s.Gp), s.Gq),
                                           (size_t)(3 * Gd)));
-    L.sums = take(sizeof(double) * (2 * kMaxP + 8));
     L.gsum = take(sizeof(double) * (kMaxP + 8));
     L.gx = take(sizeof(double) * (10 * kMaxP + 16));
     for (int i = 0; i < 4; ++i) L.ring[i] = take(fT);
@@ -339,7 +338,6 @@ Layout make_layout(const Shapes<T>& s, const rpm_options* o, bool map_only)
             c.perr = take(sizeof(double) * ge);
             c.pinc = take(sizeof(double) * gi);
             c.pdots = take(sizeof(double) * 2 * L.ld * std::max(std::max(s.G1, s.Gp), s.Gq));
-            c.sums = take(sizeof(double) * (2 * kMaxP + 8));
             c.gsum = take(sizeof(double) * (kMaxP + 8));
             for (int i = 0; i < 4; ++i) c.ring[i] = take(fT);
             c.eps = take(fT);
@@ -355,7 +353,6 @@ Layout make_layout(const Shapes<T>& s, const rpm_options* o, bool map_only)
     c0.perr = L.perr;
     c0.pinc = L.pinc;
     c0.pdots = L.pdots;
-    c0.sums = L.sums;
     c0.gsum = L.gsum;
     for (int i = 0; i < 4; ++i) c0.ring[i] = L.ring[i];
     c0.eps = L.eps;
@@ -459,7 +456,6 @@ struct Ctx {
     T* eps() { return at<T>(L.eps); }
     T* Zb() { return at<T>(L.Z); }  // tiled basis Z (column slots: pmax)
     T* Wb() { return at<T>(L.W); }  // tiled W = F_u Z
-    double* sums() { return at<double>(L.sums); }
     double* gsum() { return at<double>(L.gsum); }
     double* gx() { return at<double>(L.gx); }
     double* pdots() { return at<double>(L.pdots); }
@@ -713,21 +709,16 @@ void project(Ctx<T>& c, const T* xi, const T* eps, int p, bool direct)
 
 // Reductions and the step bookkeeping after one F application (plus projections).
 template <typename T>
-void reduce_and_finalize(Ctx<T>& c, int p, int slot, int newton_only, bool direct, const int* done,
-                         int err_mode = 0)
+void reduce_and_finalize(Ctx<T>& c, int p, int slot, int newton_only, bool direct, int err_mode = 0)
 {
     hipEvent_t ev;
-    c.mark_begin(RPM_K_REDUCE, ev);
     const double* perr = newton_only ? nullptr
                                      : (err_mode == 0 ? c.template at<double>(c.L.perr)
                                                       : c.template at<double>(c.L.pinc));
-    const int nf = direct ? 2 : 1;
-    k_reduce_main<<<1 + nf * p, kThreads, 0, c.s>>>(perr, err_mode == 0 ? c.sh.g3() : c.sh.ginc(), c.pdots(), c.sh.Gq,
-                                                    c.L.ld, p, c.sums(), done);
-    c.mark_end(RPM_K_REDUCE, ev);
     c.mark_begin(RPM_K_FINAL, ev);
-    k_step_end<<<1, kThreads, 0, c.s>>>(c.st, c.sums(), p, slot & 3, c.sh.g.two_d, newton_only, err_mode,
-                                        direct ? 1 : 0, c.template at<double>(c.L.hist), (int)c.L.hist_cap);
+    k_step_end<<<1, kStepThreads, 0, c.s>>>(c.st, perr, err_mode == 0 ? c.sh.g3() : c.sh.ginc(), c.pdots(), c.sh.Gq,
+                                            c.L.ld, p, slot & 3, c.sh.g.two_d, newton_only, err_mode, direct ? 1 : 0,
+                                            c.template at<double>(c.L.hist), (int)c.L.hist_cap);
     c.mark_end(RPM_K_FINAL, ev);
     c.check_launch();
 }
@@ -741,10 +732,12 @@ bool sync_read(Ctx<T>& c, void* host, const void* dev, size_t bytes)
     return !c.hip_error;
 }
 
+// out[f * os + j] = sum of G partials part[f * fs + b * bs + j * cs], j < m, f < nf
 template <typename T>
-void reduce_cols(Ctx<T>& c, const double* part, int G, long long bs, long long cs, int m, double* out)
+void reduce_cols(Ctx<T>& c, const double* part, int G, long long bs, long long cs, int m, double* out, int nf = 1,
+                 long long fs = 0, int os = 0)
 {
-    k_reduce_cols<<<m, kThreads, 0, c.s>>>(part, G, bs, cs, out);
+    k_reduce_cols<<<dim3((unsigned)m, (unsigned)nf), kThreads, 0, c.s>>>(part, G, bs, cs, fs, os, out);
 }
 
 // Checksum of the phase map for the reuse key of the basis, before its first column.
@@ -884,9 +877,9 @@ int add_columns(Ctx<T>& c, int& p, double* const* v, int* jvps)
     Fields<double> fv{{v[0], v1}};
     if (p > 0) {
         launch_gdots<double, T, NV, 1>(c.s, Gq, fv, c.Zb(), p, c.pmax, N, c.pg(), kMaxP);
-        for (int f = 0; f < NV; ++f) reduce_cols(c, c.pg() + (long long)f * kMaxP * Gq, Gq, 1, Gq, p, C1 + f * kMaxP);
+        reduce_cols(c, c.pg(), Gq, 1, Gq, p, C1, NV, (long long)kMaxP * Gq, kMaxP);
         launch_update<T, NV, false>(c.s, Gq, v[0], v1, c.Zb(), p, c.pmax, C1, N, c.pg(), rs);
-        for (int f = 0; f < NV; ++f) reduce_cols(c, c.pg() + f * kMaxP, Gq, rs, 1, p, C2 + f * kMaxP);
+        reduce_cols(c, c.pg(), Gq, rs, 1, p, C2, NV, kMaxP, kMaxP);
     }
     launch_update<T, NV, true>(c.s, Gq, v[0], v1, c.Zb(), p, c.pmax, C2, N, c.pg(), rs);
     reduce_cols(c, c.pg() + NV * kMaxP, Gq, rs, 1, NM, nr);
@@ -942,28 +935,45 @@ int add_columns(Ctx<T>& c, int& p, double* const* v, int* jvps)
     else
         launch_gdots<T, T, 4, 1>(c.s, Gq, Fields<T>{{wout[0], zc[0], wout[1], zc[1]}}, c.Zb(), p + 2, c.pmax, N,
                                  c.pg(), kMaxP);
-    for (int f = 0; f < 2 * nacc; ++f)
-        reduce_cols(c, c.pg() + (long long)f * kMaxP * Gq, Gq, 1, Gq, p + f / 2 + 1, HZ + f * ld);
+    reduce_cols(c, c.pg(), Gq, 1, Gq, p + nacc, HZ, 2 * nacc, (long long)kMaxP * Gq, ld);
     // H rows <z_a, w_j>, j < p + a, in one pass over W
     if (p + nacc - 1 > 0) {
         if (nacc == 1)
             launch_gdots<T, T, 1, 1>(c.s, Gq, Fields<T>{{zc[0]}}, c.Wb(), p, c.pmax, N, c.pg(), kMaxP);
         else
             launch_gdots<T, T, 2, 1>(c.s, Gq, Fields<T>{{zc[0], zc[1]}}, c.Wb(), p + 1, c.pmax, N, c.pg(), kMaxP);
-        for (int a = 0; a < nacc; ++a)
-            if (p + a > 0) reduce_cols(c, c.pg() + (long long)a * kMaxP * Gq, Gq, 1, Gq, p + a, RW + a * kMaxP);
+        // (the partials hold p + nacc - 1 columns of every field)
+        reduce_cols(c, c.pg(), Gq, 1, Gq, p + nacc - 1, RW, nacc, (long long)kMaxP * Gq, kMaxP);
     }
-    for (int a = 0; a < nacc; ++a) k_border<<<1, 1, 0, c.s>>>(c.st, HZ + 2 * a * ld, RW + a * kMaxP,
-                                                              HZ + (2 * a + 1) * ld, p + a);
+    k_border<<<1, 64, 0, c.s>>>(c.st, HZ, ld, RW, p, nacc);
     p += nacc;
     return nacc;
 }
 
+// First part of a basis growth after main-loop F application number it: the last
+// two differences of q and their Gram entries (st->gram).
+template <typename T>
+void growth_diff(Ctx<T>& c, int it, int nq, int p)
+{
+    const long long N = c.sh.g.N;
+    double* D1 = c.template at<double>(c.L.D1);
+    double* D0 = c.template at<double>(c.L.D0);
+    const int sa = (it - 1) & 3, sb = (it - 2) & 3, sc = (it - 3) & 3;
+    const bool two = nq >= 3;
+    const int Gd = (int)((6 * N + 4 * kThreads - 1) / (4 * kThreads));
+    k_growth_diff<T><<<Gd, kThreads, 0, c.s>>>(c.ring(sa), c.ring(sb), two ? c.ring(sc) : nullptr, c.Zb(), p,
+                                               c.pmax,
+                                               c.st->zeta_ring[sa], c.st->zeta_ring[sb], c.st->zeta_ring[sc], D1,
+                                               two ? D0 : nullptr, N, c.pg());
+    reduce_cols(c, c.pg(), Gd, 3, 1, 3, c.st->gram);
+}
+
 // Basis growth In(q, Z) after main-loop F application number it (Sec. 3:
 // QR of the last two differences of q, one or two columns, H bordered by one
-// JVP per column).  Returns the number of columns added, or -1 on HIP error.
+// JVP per column), the differences and their Gram entries in place
+// (growth_diff).  Returns the number of columns added, or -1 on HIP error.
 template <typename T>
-int grow_basis(Ctx<T>& c, int it, int nq, int& p, const rpm_options* o, int growth_index, int* want_out,
+int grow_basis(Ctx<T>& c, int nq, const double* gram, int& p, const rpm_options* o, int growth_index, int* want_out,
                int* jvps)
 {
     const long long N = c.sh.g.N;
@@ -971,18 +981,9 @@ int grow_basis(Ctx<T>& c, int it, int nq, int& p, const rpm_options* o, int grow
     double* D0 = c.template at<double>(c.L.D0);
     T* tmp = c.template at<T>(c.L.tmp);
     T* tmp2 = c.template at<T>(c.L.tmp2);
-    const int sa = (it - 1) & 3, sb = (it - 2) & 3, sc = (it - 3) & 3;
     const bool two = nq >= 3;
     hipEvent_t ev;
     c.mark_begin(RPM_K_GROWTH, ev);
-    const int Gd = (int)((6 * N + 4 * kThreads - 1) / (4 * kThreads));
-    k_growth_diff<T><<<Gd, kThreads, 0, c.s>>>(c.ring(sa), c.ring(sb), two ? c.ring(sc) : nullptr, c.Zb(), p,
-                                               c.pmax,
-                                               c.st->zeta_ring[sa], c.st->zeta_ring[sb], c.st->zeta_ring[sc], D1,
-                                               two ? D0 : nullptr, N, c.pg());
-    reduce_cols(c, c.pg(), Gd, 3, 1, 3, c.gsum());
-    double gram[3];
-    if (!sync_read(c, gram, c.gsum(), sizeof(gram))) return -1;
     const double T11 = std::sqrt(std::max(gram[0], 0.0));
     double T22 = 0.0;
     int want = 0;
@@ -1019,6 +1020,8 @@ int grow_basis(Ctx<T>& c, int it, int nq, int& p, const rpm_options* o, int grow
         if (c.pol) {
             // polarization iterates are not compatible: the differences stay as they are
             k_convert<T, double><<<gb, 256, 0, c.s>>>(tmp, v, 1.0, nel);
+        } else if constexpr (sizeof(T) == 8) {
+            project_compatible<T>(c, tmp, v);
         } else {
             project_compatible<T>(c, tmp, tmp2);
             k_convert<T, double><<<gb, 256, 0, c.s>>>(tmp2, v, 1.0, nel);
@@ -1131,7 +1134,7 @@ rpm_status run_solve(Ctx<T>& c, const rpm_problem* pr, const rpm_options* o, con
     }
     run_F<T>(c, c.eps(), 0, nullptr, c.eps(), c.ring(1), OUT_XI, 0, DC_MEAN, c.st->E, done, sp.shift, pinc);
     if (rpm) project(c, c.ring(1), c.eps(), p, true);
-    reduce_and_finalize(c, rpm ? p : 0, 1, 0, true, done, sp.err_mode);
+    reduce_and_finalize(c, rpm ? p : 0, 1, 0, true, sp.err_mode);
 
     int it = 1, nu = 0, nq = 0;
     const int check = std::max(1, o->check_every);
@@ -1142,14 +1145,17 @@ rpm_status run_solve(Ctx<T>& c, const rpm_problem* pr, const rpm_options* o, con
     for (;;) {
         const bool at_growth = rpm && (nu > o->n_max) && p < c.pmax;
         if (at_growth || (it % check) == 0 || it >= o->max_iter) {
-            int flags[4];
-            if (!sync_read(c, flags, &c.st->done, sizeof(flags))) return RPM_E_HIP;
-            if (flags[0] || flags[2] >= o->max_iter) break;
+            // at a growth point the differences are formed before the flags are
+            // known, so that one wait serves both
+            DevHead hd;
+            if (at_growth) growth_diff(c, it, nq, p);
+            if (!sync_read(c, &hd, c.st, offsetof(DevHead, tol))) return RPM_E_HIP;
+            if (hd.done || hd.iters >= o->max_iter) break;
             if (at_growth) {
                 int want = 0;
                 const int p_before = p;
                 store_key(c);
-                const int added = grow_basis(c, it, nq, p, o, (int)so.decisions.size(), &want, &jvps);
+                const int added = grow_basis(c, nq, hd.gram, p, o, (int)so.decisions.size(), &want, &jvps);
                 if (added < 0) return RPM_E_HIP;
                 so.decisions.push_back(want);
                 ++growth;
@@ -1159,7 +1165,7 @@ rpm_status run_solve(Ctx<T>& c, const rpm_problem* pr, const rpm_options* o, con
                 const T* cur = (p_before > 0 || it == 1) ? c.eps() : c.ring(it - 1);
                 // projections of the current pair (eps, xi) on the grown basis, Newton step
                 project(c, c.ring(it), cur, p, true);
-                reduce_and_finalize(c, p, it, 1, true, done, sp.err_mode);
+                reduce_and_finalize(c, p, it, 1, true, sp.err_mode);
             }
         }
         // one RPM iteration: eps = xi + Z d, xi = F(eps), Newton step (while
@@ -1173,7 +1179,7 @@ rpm_status run_solve(Ctx<T>& c, const rpm_problem* pr, const rpm_options* o, con
             } else {
                 run_F<T>(c, xprev, 0, nullptr, xprev, c.ring(i), OUT_XI, 0, DC_MEAN, c.st->E, done, sp.shift, pinc);
             }
-            reduce_and_finalize(c, rpm ? p : 0, i, 0, false, done, sp.err_mode);
+            reduce_and_finalize(c, rpm ? p : 0, i, 0, false, sp.err_mode);
         };
         if (graphs.on) {
             // the kernels of an iteration depend on it only through the ring slot
@@ -1245,7 +1251,7 @@ rpm_status eval64(Ctx<double>& c64, DevHead& hs)
 {
     k_reset_state<<<1, 1, 0, c64.s>>>(c64.st);
     run_F<double>(c64, c64.eps(), 0, nullptr, c64.eps(), c64.ring(1), OUT_XI, 0, DC_MEAN, c64.st->E, nullptr);
-    reduce_and_finalize(c64, 0, 1, 0, true, nullptr);
+    reduce_and_finalize(c64, 0, 1, 0, true);
     if (!sync_read(c64, &hs, c64.st, sizeof(DevHead))) return RPM_E_HIP;
     return RPM_OK;
 }
@@ -1485,7 +1491,7 @@ rpm_status apply_typed(const rpm_problem* pr, const double E[6], const rpm_optio
     rs = prepare(c, pr, o, false, &p, o->tol, E);
     if (rs != RPM_OK) return rs;
     run_F<T>(c, (const T*)eps, 0, nullptr, (const T*)eps, (T*)xi, OUT_XI, 0, DC_MEAN, c.st->E, nullptr);
-    reduce_and_finalize(c, 0, 1, 0, true, nullptr);
+    reduce_and_finalize(c, 0, 1, 0, true);
     DevHead hs;
     if (!sync_read(c, &hs, c.st, sizeof(hs))) return RPM_E_HIP;
     if (err) *err = hs.err;
@@ -1717,7 +1723,6 @@ void case_ctx(Ctx<T>& cf, const Ctx<T>& c, int f)
     cf.L.perr = o.perr;
     cf.L.pinc = o.pinc;
     cf.L.pdots = o.pdots;
-    cf.L.sums = o.sums;
     cf.L.gsum = o.gsum;
     for (int i = 0; i < 4; ++i) cf.L.ring[i] = o.ring[i];
     cf.L.eps = o.eps;
@@ -1821,7 +1826,7 @@ rpm_status eff_batched(const rpm_problem* pr, const rpm_options* o, double* C, r
         run_F<T>(cx[f], cx[f].eps(), 0, nullptr, cx[f].eps(), cx[f].ring(1), OUT_XI, 0, DC_MEAN, cx[f].st->E,
                  done[f]);
         if (p > 0) project(cx[f], cx[f].ring(1), cx[f].eps(), p, true);
-        reduce_and_finalize(cx[f], p, 1, 0, true, done[f]);
+        reduce_and_finalize(cx[f], p, 1, 0, true);
     }
     int it = 1, nu = 0, nq = 0, jvps = 0, growth = 0;
     std::vector<int> decisions;
@@ -1870,7 +1875,10 @@ rpm_status eff_batched(const rpm_problem* pr, const rpm_options* o, double* C, r
                     const int f = order[k];
                     if (f != last) k_copy_basis_state<<<1, kThreads, 0, c.s>>>(cx[f].st, cx[last].st);
                     int want = 0;
-                    const int added = grow_basis(cx[f], it, nq, p, o, (int)decisions.size(), &want, &jvps);
+                    double gram[3];
+                    growth_diff(cx[f], it, nq, p);
+                    if (!sync_read(cx[f], gram, cx[f].st->gram, sizeof(gram))) return RPM_E_HIP;
+                    const int added = grow_basis(cx[f], nq, gram, p, o, (int)decisions.size(), &want, &jvps);
                     if (added < 0) return RPM_E_HIP;
                     decisions.push_back(want);
                     last = f;
@@ -1882,7 +1890,7 @@ rpm_status eff_batched(const rpm_problem* pr, const rpm_options* o, double* C, r
                     if (f != last) k_copy_basis_state<<<1, kThreads, 0, c.s>>>(cx[f].st, cx[last].st);
                     const T* cur = (p_before > 0 || it == 1) ? cx[f].eps() : cx[f].ring(it - 1);
                     project(cx[f], cx[f].ring(it), cur, p, true);
-                    reduce_and_finalize(cx[f], p, it, 1, true, done[f]);
+                    reduce_and_finalize(cx[f], p, it, 1, true);
                 }
             }
         }
@@ -1919,10 +1927,9 @@ rpm_status eff_batched(const rpm_problem* pr, const rpm_options* o, double* C, r
         }
         for (int f = 0; f < nb; ++f) {
             const double* bpd = c.template at<double>(c.L.bpd) + (long long)f * kMaxP * c.sh.Gq;
-            k_reduce_main<<<1 + p, kThreads, 0, c.s>>>(cx[f].template at<double>(cx[f].L.perr), c.sh.g3(), bpd,
-                                                       c.sh.Gq, kMaxP, p, cx[f].sums(), done[f]);
-            k_step_end<<<1, kThreads, 0, c.s>>>(cx[f].st, cx[f].sums(), p, it & 3, g.two_d, 0, 0, 0,
-                                                cx[f].template at<double>(cx[f].L.hist), (int)c.L.hist_cap);
+            k_step_end<<<1, kStepThreads, 0, c.s>>>(cx[f].st, cx[f].template at<double>(cx[f].L.perr), c.sh.g3(), bpd,
+                                                    c.sh.Gq, kMaxP, p, it & 3, g.two_d, 0, 0, 0,
+                                                    cx[f].template at<double>(cx[f].L.hist), (int)c.L.hist_cap);
         }
         c.check_launch();
         ++nu;
