@@ -30,6 +30,7 @@ using namespace rpm;
 namespace {
 
 constexpr size_t kAlign = 256;
+constexpr size_t kBigAlign = 64 * 1024;
 constexpr int kLdsCap = 60 * 1024;  // leaves room for static shared arrays
 constexpr int kMaxN = 512;
 constexpr double kFp32Stage = 1e-5;  // FP32 stage target before FP64 refinement
@@ -283,6 +284,8 @@ Layout make_layout(const Shapes<T>& s, const rpm_options* o, bool map_only)
     L.hist_cap = map_only ? 2 : (long long)o->max_iter + 1;
     size_t off = 0;
     auto take = [&](size_t bytes) {
+        // fields, spectra and the basis on 64 KB boundaries
+        if (bytes >= kBigAlign) off = (off + kBigAlign - 1) / kBigAlign * kBigAlign;
         size_t at = off;
         off = align_up(off + bytes);
         return at;
