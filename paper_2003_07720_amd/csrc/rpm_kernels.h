@@ -31,8 +31,9 @@
 
 namespace rpm {
 
-// 16-byte non-temporal loads: the per-step basis streams read 50 MB per column
-// and would otherwise push the fields the FFT passes re-read out of the caches
+// 16-byte non-temporal loads: the per-step basis streams of large grids read 50
+// MB per column and would otherwise push the fields the FFT passes re-read out of
+// the caches
 typedef float nt_f4 __attribute__((ext_vector_type(4)));
 typedef double nt_d2 __attribute__((ext_vector_type(2)));
 __device__ __forceinline__ float4 nt_load(const float4* p)
@@ -45,6 +46,19 @@ __device__ __forceinline__ double2 nt_load(const double2* p)
     const nt_d2 t = __builtin_nontemporal_load(reinterpret_cast<const nt_d2*>(p));
     return make_double2(t.x, t.y);
 }
+
+template <bool NT, typename V>
+__device__ __forceinline__ V stream_load(const V* p)
+{
+    if constexpr (NT) return nt_load(p);
+    else return *p;
+}
+// Basis streams up to this many bytes are read with plain loads: they stay in the
+// 256 MB Infinity Cache from one pass to the next (48^3 FP64, p = 32, 170 MB: 20
+// steps 2402 -> 2090 us; 64^3 FP32, 201 MB: 2560 -> 2445).  Past it non-temporal
+// loads win (64^3 FP64, p = 64, 805 MB: equal; 128^3 FP32, 1.6 GB: 13.1 ms against
+// 14.3).
+constexpr double kCachedBasis = 240e6;
 
 struct Geo {
     int nx, ny, nz, nh;    // nh = nx/2 + 1 (half spectrum along x)
@@ -1245,7 +1259,7 @@ __global__ __launch_bounds__(512) void k_gdots(Fields<TA> a, const TZ* __restric
 // p <= 64 stream 2-5 % faster than eight columns per wave; FP64, two 16-byte
 // loads per column slice: TB = 1, 6-9 % faster).  Same partial-sum layout as
 // k_gdots.
-template <typename TA, typename TZ, int NF, int SITE, int C, int TB>
+template <typename TA, typename TZ, int NF, int SITE, int C, int TB, bool NT>
 __global__ __launch_bounds__(1024) void k_gdots_split(Fields<TA> a, const TZ* __restrict__ Z, int p, int zP,
                                                       long long N, double* __restrict__ part, int ld)
 {
@@ -1274,7 +1288,7 @@ __global__ __launch_bounds__(1024) void k_gdots_split(Fields<TA> a, const TZ* __
         for (int t = 0; t < TB; ++t)
 #pragma unroll
             for (int u = 0; u < C; ++u)
-                raw[t][u].template load_s<true>(Z + ((t0 + t) * zP + j0 + min(u, nj - 1)) * (long long)kZTile + lo);
+                raw[t][u].template load_s<NT>(Z + ((t0 + t) * zP + j0 + min(u, nj - 1)) * (long long)kZTile + lo);
 #pragma unroll
         for (int t = 0; t < TB; ++t) {
             const long long e0 = (t0 + t) * kZTile + lo;
@@ -1299,10 +1313,10 @@ __global__ __launch_bounds__(1024) void k_gdots_split(Fields<TA> a, const TZ* __
     // tiles past the last whole group, then the last, partial tile
     for (long long tile = ngrp * TB + blockIdx.x; tile <= nfull; tile += gridDim.x) {
         if (tile < nfull)
-            gdots_tile<true, TA, TZ, NF, true, C>(a, tile * kZTile, Z + (tile * zP + j0) * (long long)kZTile, lo, nj,
+            gdots_tile<true, TA, TZ, NF, NT, C>(a, tile * kZTile, Z + (tile * zP + j0) * (long long)kZTile, lo, nj,
                                                   tile * kZTile + lo, L6, N3, acc);
         else if (nfull * kZTile < L6)
-            gdots_tile<false, TA, TZ, NF, true, C>(a, tile * kZTile, Z + (tile * zP + j0) * (long long)kZTile, lo,
+            gdots_tile<false, TA, TZ, NF, NT, C>(a, tile * kZTile, Z + (tile * zP + j0) * (long long)kZTile, lo,
                                                    nj, tile * kZTile + lo, L6, N3, acc);
     }
 #pragma unroll
@@ -2071,7 +2085,7 @@ __global__ __launch_bounds__(kThreads) void k_growth_diff(const T* __restrict__ 
 // contiguous kilobyte of its tile.  Columns go in groups of 8 whose loads are
 // issued together (non-temporal); slots past p repeat column p - 1 with
 // coefficient zero.
-template <typename T>
+template <typename T, bool NT>
 __global__ __launch_bounds__(kThreads) void k_recombine(const T* __restrict__ xi, const T* __restrict__ Z, int p,
                                                         int zP, const double* __restrict__ dco,
                                                         T* __restrict__ eps, long long n,
@@ -2093,7 +2107,7 @@ __global__ __launch_bounds__(kThreads) void k_recombine(const T* __restrict__ xi
             V z[8];
 #pragma unroll
             for (int u = 0; u < 8; ++u)
-                z[u] = nt_load(reinterpret_cast<const V*>(zt + (long long)min(g + u, p - 1) * kZTile));
+                z[u] = stream_load<NT>(reinterpret_cast<const V*>(zt + (long long)min(g + u, p - 1) * kZTile));
 #pragma unroll
             for (int u = 0; u < 8; ++u) {
                 const T* zs = reinterpret_cast<const T*>(&z[u]);
@@ -2127,7 +2141,7 @@ __global__ __launch_bounds__(kThreads) void k_recombine(const T* __restrict__ xi
 #define RPM_RS_TPB 4
 #endif
 constexpr int kRsWaves = 16;
-template <typename T, int C = RPM_RS_CPW, int TB = RPM_RS_TPB>
+template <typename T, bool NT, int C = RPM_RS_CPW, int TB = RPM_RS_TPB>
 __global__ __launch_bounds__(64 * kRsWaves) void k_recombine_split(const T* __restrict__ xi, const T* __restrict__ Z,
                                                                    int p, int zP, const double* __restrict__ dco,
                                                                    T* __restrict__ eps, const int* __restrict__ done)
@@ -2155,7 +2169,7 @@ __global__ __launch_bounds__(64 * kRsWaves) void k_recombine_split(const T* __re
         for (int t = 0; t < TB; ++t)
 #pragma unroll
             for (int u = 0; u < C; ++u)
-                z[t][u] = nt_load(reinterpret_cast<const V*>(zt0 + (long long)t * zP * kZTile +
+                z[t][u] = stream_load<NT>(reinterpret_cast<const V*>(zt0 + (long long)t * zP * kZTile +
                                                              (long long)min(g + u, p - 1) * kZTile));
 #pragma unroll
         for (int t = 0; t < TB; ++t) {

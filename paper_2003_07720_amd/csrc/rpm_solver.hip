@@ -43,10 +43,10 @@ constexpr double kFp32Stage = 1e-5;  // FP32 stage target before FP64 refinement
 constexpr bool kYPipe = RPM_YPIPE != 0;        // software-pipelined y passes
 // persistent grid of the pipelined y passes (four resident blocks per CU)
 constexpr int kYPipeBlocks = RPM_YPIPE_BLOCKS;
-#ifndef RPM_TDOTS_BLOCKS
-#define RPM_TDOTS_BLOCKS 1024
-#endif
-constexpr int kTdotsBlocks = RPM_TDOTS_BLOCKS;  // grid cap of the basis products
+// grid cap of the basis products: one resident round of 16-wave blocks (20 steps
+// with 512 / 1024 / 2048 blocks: 64^3 FP64, p = 64, 7214 / 7356 / 7647 us; 64^3
+// FP32, p = 32, 2331 / 2438 / 2632; 128^3 FP32 13134 / 13138 / 13381)
+constexpr int kTdotsBlocks = 512;
 #ifndef RPM_GPIPE
 #define RPM_GPIPE 1
 #endif
@@ -60,11 +60,6 @@ constexpr bool kGPipe = RPM_GPIPE != 0;        // software-pipelined gamma pass
 // FP32 recombination with the basis columns split over the waves of a block
 // (k_recombine_split)
 constexpr bool kSplitRecombine = RPM_SPLIT_RECOMBINE != 0;
-#ifndef RPM_SPLIT_DOTS
-#define RPM_SPLIT_DOTS 1
-#endif
-// per-step basis products with two or four columns per wave (k_gdots_split)
-constexpr bool kSplitDots = RPM_SPLIT_DOTS != 0;
 constexpr int kGPipeBlocks = RPM_GPIPE_BLOCKS;  // its persistent grid
 
 size_t align_up(size_t x) { return (x + kAlign - 1) / kAlign * kAlign; }
@@ -544,25 +539,29 @@ void run_F(Ctx<T>& c, const T* xin, int p_corr, T* eps_store, const T* eps_for_i
         const long long nel = 6 * g.N;
         const int VL = 16 / (int)sizeof(T);
         const int gb = (int)((nel / VL + kThreads - 1) / kThreads) + 1;
-        c.mark_begin(RPM_K_RECOMBINE, ev);
-        if constexpr (sizeof(T) == 4) {
-            if (split && p_corr > 0) {
-                // whole groups of RPM_RS_TPB tiles, then the remaining tiles
-                // (addressed from their first tile) one run per thread
-                const long long ngrp = nel / kZTile / RPM_RS_TPB;
-                const long long off = ngrp * RPM_RS_TPB * kZTile;
-                if (ngrp > 0)
-                    k_recombine_split<T><<<(int)ngrp, 64 * kRsWaves, 0, c.s>>>(xin, c.Zb(), p_corr, c.pmax, c.st->d,
-                                                                               eps_store, done);
-                if (off < nel)
-                    k_recombine<T><<<(int)((nel - off) / VL + kThreads - 1) / kThreads + 1, kThreads, 0, c.s>>>(
-                        xin + off, c.Zb() + off * c.pmax, p_corr, c.pmax, c.st->d, eps_store + off, nel - off, done);
-            } else {
-                k_recombine<T><<<gb, kThreads, 0, c.s>>>(xin, c.Zb(), p_corr, c.pmax, c.st->d, eps_store, nel, done);
+        auto launch = [&](auto nt) {
+            constexpr bool NT = decltype(nt)::value;
+            if constexpr (sizeof(T) == 4) {
+                if (split && p_corr > 0) {
+                    // whole groups of RPM_RS_TPB tiles, then the remaining tiles
+                    // (addressed from their first tile) one run per thread
+                    const long long ngrp = nel / kZTile / RPM_RS_TPB;
+                    const long long off = ngrp * RPM_RS_TPB * kZTile;
+                    if (ngrp > 0)
+                        k_recombine_split<T, NT><<<(int)ngrp, 64 * kRsWaves, 0, c.s>>>(xin, c.Zb(), p_corr, c.pmax,
+                                                                                       c.st->d, eps_store, done);
+                    if (off < nel)
+                        k_recombine<T, NT><<<(int)((nel - off) / VL + kThreads - 1) / kThreads + 1, kThreads, 0,
+                                             c.s>>>(xin + off, c.Zb() + off * c.pmax, p_corr, c.pmax, c.st->d,
+                                                    eps_store + off, nel - off, done);
+                    return;
+                }
             }
-        } else {
-            k_recombine<T><<<gb, kThreads, 0, c.s>>>(xin, c.Zb(), p_corr, c.pmax, c.st->d, eps_store, nel, done);
-        }
+            k_recombine<T, NT><<<gb, kThreads, 0, c.s>>>(xin, c.Zb(), p_corr, c.pmax, c.st->d, eps_store, nel, done);
+        };
+        c.mark_begin(RPM_K_RECOMBINE, ev);
+        if (fieldB * p_corr <= kCachedBasis) launch(std::false_type());
+        else launch(std::true_type());
         c.mark_end(RPM_K_RECOMBINE, ev, fieldB * (2 + p_corr));
         xin = eps_store;
     }
@@ -685,27 +684,23 @@ void project(Ctx<T>& c, const T* xi, const T* eps, int p, bool direct)
     if (direct)
         launch_gdots<T, T, 2, 0>(c.s, c.sh.Gq, Fields<T>{{xi, eps}}, c.Zb(), p, c.pmax, c.sh.g.N, c.pdots(),
                                  c.L.ld);
-    else if constexpr (sizeof(T) == 4) {
-        if (kSplitDots && p <= 32)
-            k_gdots_split<T, T, 1, 0, 2, 8><<<c.sh.Gq, 64 * ((p + 1) / 2), 0, c.s>>>(Fields<T>{{xi}}, c.Zb(), p, c.pmax,
-                                                                                    c.sh.g.N, c.pdots(), c.L.ld);
-        else if (kSplitDots && p <= 64)
-            k_gdots_split<T, T, 1, 0, 4, 4><<<c.sh.Gq, 64 * ((p + 3) / 4), 0, c.s>>>(Fields<T>{{xi}}, c.Zb(), p, c.pmax,
-                                                                                    c.sh.g.N, c.pdots(), c.L.ld);
-        else
-            launch_gdots<T, T, 1, 0>(c.s, c.sh.Gq, Fields<T>{{xi}}, c.Zb(), p, c.pmax, c.sh.g.N, c.pdots(), c.L.ld);
-    } else {
-        // FP64 fields: fewer loads in flight per lane (two or four columns of
-        // one tile per wave) stream faster than eight columns (759 -> 693 us
-        // at p = 32, 1391 -> 1308 us at p = 64 on 128^3)
-        if (kSplitDots && p <= 32)
-            k_gdots_split<T, T, 1, 0, 2, 1><<<c.sh.Gq, 64 * ((p + 1) / 2), 0, c.s>>>(Fields<T>{{xi}}, c.Zb(), p, c.pmax,
-                                                                                    c.sh.g.N, c.pdots(), c.L.ld);
-        else if (kSplitDots && p <= 64)
-            k_gdots_split<T, T, 1, 0, 4, 1><<<c.sh.Gq, 64 * ((p + 3) / 4), 0, c.s>>>(Fields<T>{{xi}}, c.Zb(), p, c.pmax,
-                                                                                    c.sh.g.N, c.pdots(), c.L.ld);
-        else
-            launch_gdots<T, T, 1, 0>(c.s, c.sh.Gq, Fields<T>{{xi}}, c.Zb(), p, c.pmax, c.sh.g.N, c.pdots(), c.L.ld);
+    else {
+        // FP64 fields: fewer loads in flight per lane (two or four columns of one
+        // tile per wave) stream faster than eight columns (759 -> 693 us at p = 32,
+        // 1391 -> 1308 us at p = 64 on 128^3)
+        auto launch = [&](auto nt) {
+            constexpr bool NT = decltype(nt)::value;
+            constexpr bool f4 = sizeof(T) == 4;
+            const Fields<T> f{{xi}};
+            if (p <= 32)
+                k_gdots_split<T, T, 1, 0, 2, f4 ? 8 : 1, NT><<<c.sh.Gq, 64 * ((p + 1) / 2), 0, c.s>>>(
+                    f, c.Zb(), p, c.pmax, c.sh.g.N, c.pdots(), c.L.ld);
+            else
+                k_gdots_split<T, T, 1, 0, 4, f4 ? 4 : 1, NT><<<c.sh.Gq, 64 * ((p + 3) / 4), 0, c.s>>>(
+                    f, c.Zb(), p, c.pmax, c.sh.g.N, c.pdots(), c.L.ld);
+        };
+        if (6.0 * (double)c.sh.g.N * sizeof(T) * p <= kCachedBasis) launch(std::false_type());
+        else launch(std::true_type());
     }
     c.mark_end(RPM_K_PROJECT, ev, 6.0 * (double)c.sh.g.N * sizeof(T) * ((direct ? 2 : 1) + p));
 }
