@@ -54,12 +54,6 @@ constexpr int kTdotsBlocks = 512;
 #define RPM_GPIPE_BLOCKS 1280
 #endif
 constexpr bool kGPipe = RPM_GPIPE != 0;        // software-pipelined gamma pass
-#ifndef RPM_SPLIT_RECOMBINE
-#define RPM_SPLIT_RECOMBINE 1
-#endif
-// FP32 recombination with the basis columns split over the waves of a block
-// (k_recombine_split)
-constexpr bool kSplitRecombine = RPM_SPLIT_RECOMBINE != 0;
 constexpr int kGPipeBlocks = RPM_GPIPE_BLOCKS;  // its persistent grid
 
 size_t align_up(size_t x) { return (x + kAlign - 1) / kAlign * kAlign; }
@@ -517,8 +511,11 @@ void run_F(Ctx<T>& c, const T* xin, int p_corr, T* eps_store, const T* eps_for_i
     const bool vec = g.nx % (16 / (int)sizeof(T)) == 0;
     const double cf = (double)g.ncomp / 6.0;  // spectral components carried forward, over 6
     const double bx = fieldB + (use_ref ? 0.0 : (double)g.N) + cf * specB;
-    // FP32 with whole basis tiles: the split-column streaming pass
-    const bool split = sizeof(T) == 4 && kSplitRecombine && (6 * g.N) % kZTile == 0;
+    // FP32 with whole basis tiles: the split-column streaming pass where its 16
+    // waves have two columns each and the basis comes from HBM (steps at 128^3 with
+    // it / without: p = 2 249 / 213 us, 16 420 / 418, 28 613 / 611, 32 643 / 664, 64
+    // 1115 / 1159; 64^3: 32 107 / 105, 64 173 / 175; 48^3: 64 95 / 93)
+    const bool split = sizeof(T) == 4 && (6 * g.N) % kZTile == 0 && p_corr >= 30 && fieldB * p_corr >= 400e6;
     // FP64 on 128-point rows: eps = xin + Z d recombined inside the x pass, which
     // stores it for the x-inverse (128^3, p = 32: 610 us, as the two passes)
     constexpr bool can_fuse = sizeof(T) == 8;
@@ -542,7 +539,7 @@ void run_F(Ctx<T>& c, const T* xin, int p_corr, T* eps_store, const T* eps_for_i
         auto launch = [&](auto nt) {
             constexpr bool NT = decltype(nt)::value;
             if constexpr (sizeof(T) == 4) {
-                if (split && p_corr > 0) {
+                if (split) {
                     // whole groups of RPM_RS_TPB tiles, then the remaining tiles
                     // (addressed from their first tile) one run per thread
                     const long long ngrp = nel / kZTile / RPM_RS_TPB;
