@@ -69,6 +69,7 @@ struct Geo {
     int np;                // pencils per gamma tile
     int two_d;
     int ncomp;             // spectral components of the forward passes (6, or 12 with eps)
+    int nph;               // phases of the table the x-forward pass stages
     FDiv fnx, fny, fnh, fty, ftz, frow;  // divisions by nx, ny, nh, ty, tz and the gamma row length
     double kh[3];          // 2 pi / n per axis (wave number of index 1)
 };
@@ -2091,23 +2092,31 @@ __global__ __launch_bounds__(kThreads) void k_recombine(const T* __restrict__ xi
                                                         T* __restrict__ eps, long long n,
                                                         const int* __restrict__ done)
 {
-    if (done && *done) return;
     constexpr int VL = 16 / sizeof(T);
     using V = typename Vec4<T>::type;
     __shared__ T dj[kMaxP + 8];
+    const int stop = done ? *done : 0;
     for (int j = threadIdx.x; j < kMaxP + 8; j += kThreads) dj[j] = j < p ? (T)dco[j] : T(0);
-    __syncthreads();
     const long long e = ((long long)blockIdx.x * kThreads + threadIdx.x) * VL;
-    if (e >= n) return;
-    if (e + VL <= n) {
-        V acc = *reinterpret_cast<const V*>(xi + e);
-        T* a = reinterpret_cast<T*>(&acc);
-        const T* zt = Z + zix(e, 0, zP);  // column j at zt + j * kZTile
-        for (int g = 0; g < p; g += 8) {
-            V z[8];
+    // the first loads leave before the coefficients are there
+    const bool run = e + VL <= n;
+    const T* zt = Z + (run ? zix(e, 0, zP) : 0);  // column j at zt + j * kZTile
+    V acc = V(), z[8];
+    auto load = [&](int g) {
 #pragma unroll
-            for (int u = 0; u < 8; ++u)
-                z[u] = stream_load<NT>(reinterpret_cast<const V*>(zt + (long long)min(g + u, p - 1) * kZTile));
+        for (int u = 0; u < 8; ++u)
+            z[u] = stream_load<NT>(reinterpret_cast<const V*>(zt + (long long)min(g + u, p - 1) * kZTile));
+    };
+    if (run) {
+        acc = *reinterpret_cast<const V*>(xi + e);
+        if (p > 0) load(0);
+    }
+    if (stop) return;
+    __syncthreads();
+    if (run) {
+        T* a = reinterpret_cast<T*>(&acc);
+        for (int g = 0; g < p; g += 8) {
+            if (g > 0) load(g);
 #pragma unroll
             for (int u = 0; u < 8; ++u) {
                 const T* zs = reinterpret_cast<const T*>(&z[u]);

@@ -14,6 +14,10 @@
 // sum_q w_R1^(q k1) x[j + R2 q].  First butterfly j: radix R1 over q, twiddles
 // w_N^(j k1); second butterfly k1: radix R2 over j.
 //
+// What a pass does not depend on is loaded up front (the stop flag is looked at
+// once the data are on their way): a step of a small grid is a chain of such
+// kernels, each a few memory latencies long.
+//
 // The x passes run one block per tile and packed component pair (three pairs):
 // three times the blocks and a third of the serial chain of a block that loops
 // over the pairs.
@@ -148,6 +152,20 @@ __device__ __forceinline__ void twiddle(cx<T>* v, const cx<T>* __restrict__ tw, 
         v[k] = cmul(v[k], w);
     }
 }
+// The same with the table entries loaded ahead, beside the data they belong to
+// (a kernel's first access to the table misses the caches).
+template <typename T, int R>
+__device__ __forceinline__ void load_twiddles(cx<T> (&w)[R], const cx<T>* __restrict__ tw, int j)
+{
+#pragma unroll
+    for (int k = 1; k < R; ++k) w[k] = tw[j * k];
+}
+template <typename T, int R, int D>
+__device__ __forceinline__ void apply_twiddles(cx<T>* v, const cx<T> (&w)[R])
+{
+#pragma unroll
+    for (int k = 1; k < R; ++k) v[k] = cmul(v[k], D > 0 ? cconj(w[k]) : w[k]);
+}
 
 // Rows per x- or y-pass tile: the transposed side moves in segments of this
 // many complex numbers (128 bytes; FP64 lengths whose smaller factor would leave
@@ -170,7 +188,7 @@ __global__ __launch_bounds__((tile_threads<T, N>())) void k_py(const cx<T>* __re
                                                                const cx<T>* __restrict__ tw,
                                                                const int* __restrict__ done)
 {
-    if (done && *done) return;
+    const int stop = done ? *done : 0;
     constexpr int TZ = tile_rows<T, N>(), NT = tile_threads<T, N>(), LS = TZ + 1;
     constexpr int R1 = D < 0 ? Fac<N>::B : Fac<N>::A, R2 = N / R1;
     constexpr int I1 = (R2 * TZ + NT - 1) / NT, I2 = (R1 * TZ + NT - 1) / NT;
@@ -184,7 +202,7 @@ __global__ __launch_bounds__((tile_threads<T, N>())) void k_py(const cx<T>* __re
     cx<T>* dst = Sout + (long long)c * g.nspec;
     const long long row = ((long long)kx * g.nz + z0) * N;               // first row of the tile in S1
     const long long seg = (long long)kx * g.nz + z0, ks = (long long)g.nh * g.nz;  // its segment of a ky plane in S2
-    cx<T> v[I1][R1];
+    cx<T> v[I1][R1], w[I1][R1];
 #pragma unroll
     for (int i = 0; i < I1; ++i) {
         const int e = threadIdx.x + i * NT;
@@ -195,7 +213,9 @@ __global__ __launch_bounds__((tile_threads<T, N>())) void k_py(const cx<T>* __re
             const long long o = D < 0 ? row + r * N + j + R2 * q : (j + R2 * q) * ks + seg + r;
             v[i][q] = in ? src[o] : cx<T>{T(0), T(0)};
         }
+        load_twiddles<T, R1>(w[i], tw, e < R2 * TZ ? j : 0);
     }
+    if (stop) return;
     // element (j, k1) of row r: neighbouring lanes of both sides on different banks
     auto at = [](int j, int k1, int r) { return (D < 0 ? k1 * R2 + j : j * R1 + k1) * LS + r; };
 #pragma unroll
@@ -204,7 +224,7 @@ __global__ __launch_bounds__((tile_threads<T, N>())) void k_py(const cx<T>* __re
         const int j = D < 0 ? e % R2 : e / TZ, r = D < 0 ? e / R2 : e % TZ;
         if (R2 * TZ % NT == 0 || e < R2 * TZ) {
             dft<T, R1, D>(v[i]);
-            twiddle<T, R1, D>(v[i], tw, j);
+            apply_twiddles<T, R1, D>(v[i], w[i]);
 #pragma unroll
             for (int k1 = 0; k1 < R1; ++k1) X[at(j, k1, r)] = v[i][k1];
         }
@@ -273,11 +293,12 @@ __global__ __launch_bounds__((tile_threads<T, N>())) void k_pxf(const T* __restr
                                                                 int nyt, const cx<T>* __restrict__ tw,
                                                                 const int* __restrict__ done)
 {
-    if (done && *done) return;
+    const int stop = done ? *done : 0;
     constexpr int TY = tile_rows<T, N>(), NT = tile_threads<T, N>(), LS = TY + 1;
     constexpr int R1 = Fac<N>::B, R2 = Fac<N>::A, NH = N / 2 + 1;
     constexpr int I1 = (R2 * TY + NT - 1) / NT, I2 = (R1 * TY + NT - 1) / NT;
     __shared__ cx<T> X[N * LS];
+    __shared__ T lt[2 * 256];  // phase table
     int tile, pair;
     if (!x_block(blockIdx.x, ntiles, NP, tile, pair)) return;
     const int z = tile / nyt, y0 = (tile - z * nyt) * TY;
@@ -295,16 +316,20 @@ __global__ __launch_bounds__((tile_threads<T, N>())) void k_pxf(const T* __restr
             for (int q = 0; q < R1; ++q) f(i, q, in ? r * N + j + R2 * q : 0, in);
         }
     };
-    // phase constants (lam, mu) of an element
-    T lam[I1][R1], mu[I1][R1];
-    if (pair < 3) {
-        int lab[I1][R1];
-        each([&](int i, int q, int o, bool) { lab[i][q] = use_ref ? 0 : (int)ph[o]; });
-        each([&](int i, int q, int, bool) {
-            lam[i][q] = use_ref ? (T)lam0 : (T)lame[2 * lab[i][q]];
-            mu[i][q] = use_ref ? (T)mu0 : (T)lame[2 * lab[i][q] + 1];
-        });
+    // phase labels; the table comes from LDS once both have arrived
+    const bool tab = pair < 3 && !use_ref;
+    int lab[I1][R1];
+    if (tab) {
+        for (int i = threadIdx.x; i < 2 * g.nph; i += NT) lt[i] = (T)lame[i];
+        each([&](int i, int q, int o, bool) { lab[i][q] = (int)ph[o]; });
     }
+    cx<T> w[I1][R1];
+#pragma unroll
+    for (int i = 0; i < I1; ++i) load_twiddles<T, R1>(w[i], tw, (threadIdx.x + i * NT) % R2);
+    auto lam_mu = [&](int i, int q, T& l, T& m) {
+        l = use_ref ? (T)lam0 : lt[2 * lab[i][q]];
+        m = use_ref ? (T)mu0 : lt[2 * lab[i][q] + 1];
+    };
     const long long M = g.N;
     if (pair == 0 || pair == 1) {
         T e0[I1][R1], e1[I1][R1], e2[I1][R1], e3[I1][R1];
@@ -314,8 +339,12 @@ __global__ __launch_bounds__((tile_threads<T, N>())) void k_pxf(const T* __restr
             e2[i][q] = src[2 * M + o];
             if (pair == 1) e3[i][q] = src[3 * M + o];
         });
+        if (stop) return;
+        if (tab) __syncthreads();
         each([&](int i, int q, int, bool in) {
-            const T l = lam[i][q] * (e0[i][q] + e1[i][q] + e2[i][q]), m2 = mu[i][q] + mu[i][q];
+            T lam, mu;
+            lam_mu(i, q, lam, mu);
+            const T l = lam * (e0[i][q] + e1[i][q] + e2[i][q]), m2 = mu + mu;
             const T a = pair == 0 ? e0[i][q] : e2[i][q], b = pair == 0 ? e1[i][q] : e3[i][q];
             v[i][q] = in ? cx<T>{m2 * a + l, pair == 0 ? m2 * b + l : m2 * b} : cx<T>{T(0), T(0)};
             ms[0] += in ? (double)a : 0.0;
@@ -328,8 +357,12 @@ __global__ __launch_bounds__((tile_threads<T, N>())) void k_pxf(const T* __restr
             a[i][q] = src[c * M + o];
             b[i][q] = src[(c + 1) * M + o];
         });
+        if (stop) return;
+        if (tab) __syncthreads();
         each([&](int i, int q, int, bool in) {
-            const T m2 = pair == 2 ? mu[i][q] + mu[i][q] : T(1);
+            T lam = T(0), mu = T(0.5);
+            if (pair == 2) lam_mu(i, q, lam, mu);
+            const T m2 = mu + mu;
             v[i][q] = in ? cx<T>{m2 * a[i][q], m2 * b[i][q]} : cx<T>{T(0), T(0)};
             ms[0] += in ? (double)a[i][q] : 0.0;
             ms[1] += in ? (double)b[i][q] : 0.0;
@@ -341,7 +374,7 @@ __global__ __launch_bounds__((tile_threads<T, N>())) void k_pxf(const T* __restr
         const int j = e % R2, r = e / R2;
         if (R2 * TY % NT == 0 || e < R2 * TY) {
             dft<T, R1, -1>(v[i]);
-            twiddle<T, R1, -1>(v[i], tw, j);
+            apply_twiddles<T, R1, -1>(v[i], w[i]);
 #pragma unroll
             for (int k1 = 0; k1 < R1; ++k1) X[(k1 * R2 + j) * LS + r] = v[i][k1];
         }
@@ -395,13 +428,13 @@ __global__ __launch_bounds__((tile_threads<T, N>())) void k_pxf(const T* __restr
 // t of tile_threads).
 template <typename T, int N>
 __device__ __forceinline__ void xinv_first(const cx<T>* __restrict__ S1, cx<T>* X, int q_, int t, int z, int y0,
-                                           const Geo& g, const cx<T>* __restrict__ tw)
+                                           const Geo& g, const cx<T>* __restrict__ tw, int stop)
 {
     constexpr int TY = tile_rows<T, N>(), NT = tile_threads<T, N>(), LS = TY + 1;
     constexpr int R1 = Fac<N>::A, R2 = Fac<N>::B, I1 = (R2 * TY + NT - 1) / NT;
     const cx<T>* ina = S1 + (long long)(2 * q_) * g.nspec + (long long)z * g.ny + y0;
     const long long ks = (long long)g.nz * g.ny;
-    cx<T> v[I1][R1], w[I1][R1];
+    cx<T> v[I1][R1], w[I1][R1], f[I1][R1];
 #pragma unroll
     for (int i = 0; i < I1; ++i) {
         const int e = t + i * NT;
@@ -414,7 +447,9 @@ __device__ __forceinline__ void xinv_first(const cx<T>* __restrict__ S1, cx<T>* 
             v[i][q] = ina[o];
             w[i][q] = ina[g.nspec + o];
         }
+        load_twiddles<T, R1>(f[i], tw, e < R2 * TY ? j : 0);
     }
+    if (stop) return;
 #pragma unroll
     for (int i = 0; i < I1; ++i) {
         const int e = t + i * NT;
@@ -428,7 +463,7 @@ __device__ __forceinline__ void xinv_first(const cx<T>* __restrict__ S1, cx<T>* 
                 v[i][q] = 2 * k <= N ? cx<T>{a.x - b.y, a.y + b.x} : cx<T>{a.x + b.y, b.x - a.y};
             }
             dft<T, R1, +1>(v[i]);
-            twiddle<T, R1, +1>(v[i], tw, j);
+            apply_twiddles<T, R1, +1>(v[i], f[i]);
 #pragma unroll
             for (int k1 = 0; k1 < R1; ++k1) X[(j * R1 + k1) * LS + r] = v[i][k1];
         }
@@ -443,7 +478,7 @@ __global__ __launch_bounds__((tile_threads<T, N>())) void k_pxi(const cx<T>* __r
                                                                 int nyt, const cx<T>* __restrict__ tw,
                                                                 const int* __restrict__ done)
 {
-    if (done && *done) return;
+    const int stop = done ? *done : 0;
     constexpr int TY = tile_rows<T, N>(), NT = tile_threads<T, N>(), LS = TY + 1;
     constexpr int R1 = Fac<N>::A, R2 = Fac<N>::B, I2 = (R1 * TY + NT - 1) / NT;
     __shared__ cx<T> X[N * LS];
@@ -454,7 +489,8 @@ __global__ __launch_bounds__((tile_threads<T, N>())) void k_pxi(const cx<T>* __r
     const T invN = T(1.0 / (double)M);
     const int ca = 2 * pair, cb = ca + 1;
     double inc[1] = {0.0};
-    xinv_first<T, N>(S1, X, pair, threadIdx.x, z, y0, g, tw);
+    xinv_first<T, N>(S1, X, pair, threadIdx.x, z, y0, g, tw, stop);
+    if (stop) return;
     T ea[I2][R2], eb[I2][R2];
     if (out_mode == OUT_XI)
 #pragma unroll
@@ -557,7 +593,7 @@ __global__ __launch_bounds__((pol_groups<T, N>() * tile_threads<T, N>())) void k
     double* __restrict__ part_inc, Geo g, int nyt, const cx<T>* __restrict__ tw, const uint8_t* __restrict__ phase,
     const double* __restrict__ lame, double lam0, double mu0, double beta, const int* __restrict__ done)
 {
-    if (done && *done) return;
+    const int stop = done ? *done : 0;
     constexpr int TY = tile_rows<T, N>(), NT = tile_threads<T, N>(), LS = TY + 1, NG = pol_groups<T, N>();
     constexpr int R1 = Fac<N>::A, R2 = Fac<N>::B, I2 = (R1 * TY + NT - 1) / NT;
     __shared__ cx<T> X_[NG * N * LS];
@@ -571,7 +607,8 @@ __global__ __launch_bounds__((pol_groups<T, N>() * tile_threads<T, N>())) void k
 #pragma unroll
     for (int pp = 0; pp < (NG == 1 ? 3 : 1); ++pp) {
         if (pp > 0) __syncthreads();  // the previous pair's exchange has been read
-        xinv_first<T, N>(S1, X, NG == 1 ? pp : grp, t, z, y0, g, tw);
+        xinv_first<T, N>(S1, X, NG == 1 ? pp : grp, t, z, y0, g, tw, stop);
+        if (stop) return;
         __syncthreads();
 #pragma unroll
         for (int i = 0; i < I2; ++i) {
@@ -662,7 +699,7 @@ __global__ __launch_bounds__((GCfg<T, N, POL>::NT)) void k_pg(cx<T>* __restrict_
                                                               DevState* __restrict__ st,
                                                               const int* __restrict__ done)
 {
-    if (done && *done) return;
+    const int stop = done ? *done : 0;
     using G = GCfg<T, N, POL>;
     constexpr int A = G::A, B = G::B, P = G::P, NT = G::NT, LS = G::LS, NC = G::NC;
     __shared__ cx<T> X[G::SLOTS];
@@ -673,6 +710,14 @@ __global__ __launch_bounds__((GCfg<T, N, POL>::NT)) void k_pg(cx<T>* __restrict_
     const int p0 = blockIdx.x * P;
     // (component, pencil, j or k2, k1)
     auto slot = [](int c, int p, int j, int k) { return ((c * P + p) * B + j) * LS + k; };
+    // <eps> from the x-pass partial sums (block 0 holds k = 0)
+    double acc[6] = {0, 0, 0, 0, 0, 0};
+    if (blockIdx.x == 0 && dc_mode == DC_MEAN) {
+#pragma unroll 4
+        for (int b = t; b < n_mean; b += NT)
+#pragma unroll
+            for (int c = 0; c < 6; ++c) acc[c] += part_mean[(long long)b * 6 + c];
+    }
     // first butterflies, from memory: column j fastest
     constexpr int NF = NC * B * P, IF = (NF + NT - 1) / NT;
 #pragma unroll
@@ -686,6 +731,7 @@ __global__ __launch_bounds__((GCfg<T, N, POL>::NT)) void k_pg(cx<T>* __restrict_
         for (int q = 0; q < A; ++q) v[q] = s[in ? B * q : 0];
         if (i == 0) {
             for (int m = t; m < N; m += NT) W[m] = tw[m];
+            if (stop) return;
             __syncthreads();
         }
         if (NF % NT == 0 || e < NF) {
@@ -695,17 +741,7 @@ __global__ __launch_bounds__((GCfg<T, N, POL>::NT)) void k_pg(cx<T>* __restrict_
             for (int k = 0; k < A; ++k) X[slot(c, p, j, k)] = v[k];
         }
     }
-    if (blockIdx.x == 0) {
-        // <eps> from the x-pass partial sums (this block holds k = 0)
-        double acc[6] = {0, 0, 0, 0, 0, 0};
-        if (dc_mode == DC_MEAN) {
-#pragma unroll 4
-            for (int b = t; b < n_mean; b += NT)
-#pragma unroll
-                for (int c = 0; c < 6; ++c) acc[c] += part_mean[(long long)b * 6 + c];
-        }
-        block_sum<6, NT>(acc, dcm);
-    }
+    if (blockIdx.x == 0) block_sum<6, NT>(acc, dcm);
     __syncthreads();
     // second butterflies in place: column k1 fastest
     constexpr int NS = NC * A * P, NI = 6 * A * P;

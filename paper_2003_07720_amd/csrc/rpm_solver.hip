@@ -1227,6 +1227,7 @@ void sub64_init(Ctx<double>& c64, Ctx<float>& c, const rpm_options* o)
     const int32_t n[3] = {c.sh.g.nx, c.sh.g.ny, c.sh.g.nz};
     const rpm_options b = basic_fp64_options(o);
     c64.sh = make_shapes<double>(n, spectral_comps(&b));
+    c64.sh.g.nph = c.sh.g.nph;
     c64.L = make_layout<double>(c64.sh, &b);
     c64.s = c.s;
     c64.ws = c.ws + c.L.sub64;
@@ -1437,6 +1438,7 @@ rpm_status ctx_init(Ctx<T>& c, const rpm_problem* pr, const rpm_options* o, void
     // FP32 fields are certified by an FP64 pipeline on the same grid
     if (sizeof(T) == 4 && !map_only && !make_shapes<double>(pr->n, spectral_comps(o)).ok)
         return RPM_E_UNSUPPORTED_SIZE;
+    c.sh.g.nph = pr->n_phases;
     c.L = make_layout<T>(c.sh, o, map_only);
     if (map_only && c.L.total > ws_bytes) return RPM_E_SCRATCH;
     if (!ws || ws_bytes < c.L.total) return RPM_E_WORKSPACE;
@@ -1526,6 +1528,7 @@ rpm_status tune_typed(const rpm_problem* pr, const rpm_options* o, int reps, rpm
         const Shapes<T> sh = make_shapes<T>(pr->n, spectral_comps(&ob), &tn);
         if (!sh.ok || !sh.tune_ok) return -1.0;
         c.sh = sh;
+        c.sh.g.nph = base.g.nph;
         run_F<T>(c, c.eps(), 0, nullptr, c.eps(), c.ring(0), OUT_XI, 0, DC_MEAN, c.st->E, nullptr);
         hipEventRecord(e0, c.s);
         for (int r = 0; r < reps; ++r)
