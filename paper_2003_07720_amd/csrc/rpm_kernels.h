@@ -660,11 +660,41 @@ __device__ __forceinline__ void wave_vector(int kx, int ky, int kz, const Geo& g
 // 3-D: rows along z of S2 (pencil = ky * nh + kx).  2-D: rows along y of S1
 // (pencil = kx, kz = 0).  grid: ceil(npencils / np).
 // ---------------------------------------------------------------------------
+// What the Green operator takes from the frequency and the reference medium.
+template <typename T>
+struct GreenAt {
+    T n[3];          // unit direction
+    double kk;       // |k|^2
+    double c0, imu;  // (lam0 + mu0) / (mu0 (lam0 + 2 mu0)), 1 / mu0
+};
+template <typename T>
+__device__ __forceinline__ GreenAt<T> green_at(int kx, int ky, int kz, const Geo& g, double lam0, double mu0)
+{
+    GreenAt<T> d;
+    d.c0 = (lam0 + mu0) / (mu0 * (lam0 + 2.0 * mu0));
+    d.imu = 1.0 / mu0;
+    double k[3];
+    wave_vector(kx, ky, kz, g, k);
+    d.kk = k[0] * k[0] + k[1] * k[1] + k[2] * k[2];
+    if constexpr (sizeof(T) == 4) {
+        // FP32 fields: the unit direction to FP32 accuracy is all the filter uses
+        const float ik = rsqrtf((float)d.kk);
+#pragma unroll
+        for (int a = 0; a < 3; ++a) d.n[a] = (float)k[a] * ik;
+    } else {
+        const double ik = 1.0 / sqrt(d.kk);
+#pragma unroll
+        for (int a = 0; a < 3; ++a) d.n[a] = k[a] * ik;
+    }
+    return d;
+}
+
 // Green operator at one frequency of a gamma tile: component c sits at
 // R[c * cs].  Overwrites components 0..5 with t_hat (the k = 0 entry as
 // described above) and returns the frequency's share of the equilibrium error.
 template <typename T, bool POL>
-__device__ __forceinline__ double gamma_point_at(cx<T>* R, int cs, int kx, int ky, int kz, const Geo& g,
+__device__ __forceinline__ double gamma_point_at(cx<T>* R, int cs, int kx, int ky, int kz, const GreenAt<T>& d,
+                                                 const Geo& g,
                                                  double lam0, double mu0, double alpha, double beta, int dc_mode,
                                                  const double* __restrict__ E, const double* dc_mean,
                                                  DevState* __restrict__ st)
@@ -704,24 +734,8 @@ __device__ __forceinline__ double gamma_point_at(cx<T>* R, int cs, int kx, int k
             o[c] = cx<T>{(T)v, T(0)};
         }
     } else {
-        const double c0 = (lam0 + mu0) / (mu0 * (lam0 + 2.0 * mu0));
-        const double imu = 1.0 / mu0;
-        double k[3];
-        wave_vector(kx, ky, kz, g, k);
-        const double kk = k[0] * k[0] + k[1] * k[1] + k[2] * k[2];
-        T n0, n1, n2;
-        if constexpr (sizeof(T) == 4) {
-            // FP32 fields: the unit direction to FP32 accuracy is all the filter uses
-            const float ik = rsqrtf((float)kk);
-            n0 = (float)k[0] * ik;
-            n1 = (float)k[1] * ik;
-            n2 = (float)k[2] * ik;
-        } else {
-            const double ik = 1.0 / sqrt(kk);
-            n0 = k[0] * ik;
-            n1 = k[1] * ik;
-            n2 = k[2] * ik;
-        }
+        const double kk = d.kk;
+        const T n0 = d.n[0], n1 = d.n[1], n2 = d.n[2];
         // s = sigma_hat n with components xx,yy,zz,yz,xz,xy = 0..5
         cx<T> sx = cadd(cadd(cscale(s[0], n0), cscale(s[5], n1)), cscale(s[4], n2));
         cx<T> sy = cadd(cadd(cscale(s[5], n0), cscale(s[1], n1)), cscale(s[3], n2));
@@ -735,7 +749,7 @@ __device__ __forceinline__ double gamma_point_at(cx<T>* R, int cs, int kx, int k
             sz = cadd(cadd(cscale(sg[4], n0), cscale(sg[3], n1)), cscale(sg[2], n2));
         }
         const cx<T> a = cadd(cadd(cscale(sx, n0), cscale(sy, n1)), cscale(sz, n2));
-        const T m1 = (T)imu, cc = (T)c0, hm = T(0.5) * (T)imu;
+        const T m1 = (T)d.imu, cc = (T)d.c0, hm = T(0.5) * (T)d.imu;
         o[0] = csub(cscale(sx, m1 * n0), cscale(a, cc * n0 * n0));
         o[1] = csub(cscale(sy, m1 * n1), cscale(a, cc * n1 * n1));
         o[2] = csub(cscale(sz, m1 * n2), cscale(a, cc * n2 * n2));
@@ -755,7 +769,8 @@ __device__ __forceinline__ double gamma_point(cx<T>* R, int ss, int nrs, int r, 
                                               int dc_mode, const double* __restrict__ E, const double* dc_mean,
                                               DevState* __restrict__ st)
 {
-    return gamma_point_at<T, POL>(R + r * ss + lpad(i), nrs * ss, kx, ky, kz, g, lam0, mu0, alpha, beta, dc_mode, E,
+    return gamma_point_at<T, POL>(R + r * ss + lpad(i), nrs * ss, kx, ky, kz,
+                                  green_at<T>(kx, ky, kz, g, lam0, mu0), g, lam0, mu0, alpha, beta, dc_mode, E,
                                   dc_mean, st);
 }
 

@@ -671,10 +671,32 @@ __global__ __launch_bounds__((pol_groups<T, N>() * tile_threads<T, N>())) void k
 // gamma: transform along the last axis, Green operator, inverse transform, in
 // place (see k_gamma for the operator and the k = 0 term).  A block owns P
 // pencils with all their components: first butterflies from memory, second ones
-// in place in LDS, the filter frequency by frequency, and back.  P fills the
-// block's waves with radix-A butterflies of the six components (6 B P of them).
+// in place in LDS, the filter frequency by frequency, and back.
+// Wide blocks: one pencil and a thread for every butterfly and frequency of it, so
+// that no stage is a loop and the filter's direction (a square root and three
+// divisions) is computed while the data are on their way.  Narrow blocks: P pencils
+// that fill the waves with radix-A butterflies of the six components (6 B P of
+// them), the other stages looping.  Small grids are bound by the chain of stages,
+// large ones by memory if enough blocks are in flight.  Narrow / wide, us:
+//   FP64 32^2 6.8 / 5.3, 128^2 9.5 / 6.6, 32^3 7.1 / 5.7, 64^3 13.3 / 11.7, 128^3 54
+//   / 44.8, 96x96x256 61 / 53; FP32 48^3 7.7 / 6.4, 64^3 8.3 / 7.5, 128^3 29.4 / 29.8
+//   polarization: FP64 128^2 10.8 / 6.9, 64^3 17.9 / 14.0, 128^3 100 / 67
+// Narrow ones are better where a pencil leaves many of a wide block's lanes idle and
+// there are pencils enough to hide the stages: FP32 192x192x96 40.2 / 44.8, 192^3 77 /
+// 97; FP64 192x192x32 25.7 / 29.0, 256x256x48 62 / 68, 144^3 63 / 73; at 144, 544
+// pencils take 11.5 / 10.3, 2112 take 18.8 / 20.6.
 // ---------------------------------------------------------------------------
-template <typename T, int N, bool POL>
+template <typename T, int N>
+__host__ __device__ constexpr bool always_wide(bool pol)
+{
+    return pol || (sizeof(T) == 8 && ((N >= 64 && N <= 128) || N == 256));
+}
+template <typename T, int N>
+constexpr bool gamma_wide(bool pol, int npen)
+{
+    return always_wide<T, N>(pol) || npen <= (N > 128 && N < 256 ? 1024 : 4096);
+}
+template <typename T, int N, bool POL, bool WIDE>
 struct GCfg {
     static constexpr int A = Fac<N>::A, B = Fac<N>::B;
     static constexpr int NC = POL ? 12 : 6;
@@ -684,13 +706,13 @@ struct GCfg {
     // pencils whose butterflies fill whole waves best, for B of 3, 4, 6, 8, 9, 12, 16
     static constexpr int want = B == 3 ? 7 : B == 4 ? 8 : B == 6 ? 7 : B == 8 ? 4 : B == 9 ? 4 : B == 12 ? 3 : 2;
     static constexpr int fit = (int)((cap - N * 2 * sizeof(T)) / pencil);
-    static constexpr int P = fit < 1 ? 1 : fit < want ? fit : want;
-    static constexpr int NT = (6 * B * P + 63) / 64 * 64;
+    static constexpr int P = WIDE ? 1 : fit < 1 ? 1 : fit < want ? fit : want;
+    static constexpr int NT = ((WIDE ? (NC * A > N ? NC * A : N) : 6 * B * P) + 63) / 64 * 64;
     static constexpr int SLOTS = NC * P * B * LS;
 };
 
-template <typename T, int N, bool POL>
-__global__ __launch_bounds__((GCfg<T, N, POL>::NT)) void k_pg(cx<T>* __restrict__ S, Geo g,
+template <typename T, int N, bool POL, bool WIDE>
+__global__ __launch_bounds__((GCfg<T, N, POL, WIDE>::NT)) void k_pg(cx<T>* __restrict__ S, Geo g,
                                                               const cx<T>* __restrict__ tw, double lam0, double mu0,
                                                               double alpha, double beta, int dc_mode,
                                                               const double* __restrict__ E,
@@ -700,7 +722,7 @@ __global__ __launch_bounds__((GCfg<T, N, POL>::NT)) void k_pg(cx<T>* __restrict_
                                                               const int* __restrict__ done)
 {
     const int stop = done ? *done : 0;
-    using G = GCfg<T, N, POL>;
+    using G = GCfg<T, N, POL, WIDE>;
     constexpr int A = G::A, B = G::B, P = G::P, NT = G::NT, LS = G::LS, NC = G::NC;
     __shared__ cx<T> X[G::SLOTS];
     __shared__ cx<T> W[N];
@@ -718,6 +740,7 @@ __global__ __launch_bounds__((GCfg<T, N, POL>::NT)) void k_pg(cx<T>* __restrict_
 #pragma unroll
             for (int c = 0; c < 6; ++c) acc[c] += part_mean[(long long)b * 6 + c];
     }
+    GreenAt<T> at;  // WIDE: of the thread's only frequency, while the data are on their way
     // first butterflies, from memory: column j fastest
     constexpr int NF = NC * B * P, IF = (NF + NT - 1) / NT;
 #pragma unroll
@@ -731,6 +754,11 @@ __global__ __launch_bounds__((GCfg<T, N, POL>::NT)) void k_pg(cx<T>* __restrict_
         for (int q = 0; q < A; ++q) v[q] = s[in ? B * q : 0];
         if (i == 0) {
             for (int m = t; m < N; m += NT) W[m] = tw[m];
+            if constexpr (WIDE) {
+                int kx, ky, kz;
+                gamma_freq(g, p0, t % A + A * (t / A % B), kx, ky, kz);
+                at = green_at<T>(kx, ky, kz, g, lam0, mu0);
+            }
             if (stop) return;
             __syncthreads();
         }
@@ -764,7 +792,8 @@ __global__ __launch_bounds__((GCfg<T, N, POL>::NT)) void k_pg(cx<T>* __restrict_
         if (pen < npen) {
             int kx, ky, kz;
             gamma_freq(g, pen, k1 + A * k2, kx, ky, kz);
-            esum[0] += gamma_point_at<T, POL>(X + slot(0, p, k2, k1), P * B * LS, kx, ky, kz, g, lam0, mu0, alpha,
+            if constexpr (!WIDE) at = green_at<T>(kx, ky, kz, g, lam0, mu0);
+            esum[0] += gamma_point_at<T, POL>(X + slot(0, p, k2, k1), P * B * LS, kx, ky, kz, at, g, lam0, mu0, alpha,
                                               beta, dc_mode, E, dcm, st);
         }
     }
@@ -812,7 +841,7 @@ struct Pencil {
                           double lam0, double mu0, double beta, const int* done, hipStream_t s);
     static int gamma_blocks(bool pol, int npen)
     {
-        const int p = pol ? GCfg<T, N, true>::P : GCfg<T, N, false>::P;
+        const int p = gamma_wide<T, N>(pol, npen) ? 1 : GCfg<T, N, false, false>::P;
         return (npen + p - 1) / p;
     }
     static void gamma(bool pol, cx<T>* S, const Geo& g, const cx<T>* tw, double lam0, double mu0, double alpha,

@@ -3,6 +3,8 @@
 // side by side).
 #include "rpm_pencil.h"
 
+#include <type_traits>
+
 namespace rpm {
 
 template <typename T, int N>
@@ -50,13 +52,17 @@ void Pencil<T, N>::gamma(bool pol, cx<T>* S, const Geo& g, const cx<T>* tw, doub
                          double beta, int dc_mode, const double* E, const double* part_mean, int n_mean,
                          double* part_err, DevState* st, const int* done, hipStream_t s)
 {
-    const int grid = gamma_blocks(pol, g.two_d ? g.nh : g.ny * g.nh);
-    if (pol)
-        k_pg<T, N, true><<<grid, GCfg<T, N, true>::NT, 0, s>>>(S, g, tw, lam0, mu0, alpha, beta, dc_mode, E, part_mean, n_mean,
-                                             part_err, st, done);
-    else
-        k_pg<T, N, false><<<grid, GCfg<T, N, false>::NT, 0, s>>>(S, g, tw, lam0, mu0, alpha, beta, dc_mode, E, part_mean, n_mean,
-                                              part_err, st, done);
+    const int npen = g.two_d ? g.nh : g.ny * g.nh;
+    auto launch = [&](auto p, auto w) {
+        constexpr bool POL = decltype(p)::value, W = decltype(w)::value;
+        k_pg<T, N, POL, W><<<gamma_blocks(POL, npen), GCfg<T, N, POL, W>::NT, 0, s>>>(
+            S, g, tw, lam0, mu0, alpha, beta, dc_mode, E, part_mean, n_mean, part_err, st, done);
+    };
+    using std::false_type, std::true_type;
+    if (pol) launch(true_type(), true_type());
+    else if constexpr (always_wide<T, N>(false)) launch(false_type(), true_type());
+    else if (gamma_wide<T, N>(false, npen)) launch(false_type(), true_type());
+    else launch(false_type(), false_type());
 }
 
 #define RPM_INST(N)              \

@@ -61,3 +61,10 @@ def test_length_on_each_axis(n, prec):
 @pytest.mark.parametrize("grid", [(12, 8, 6), (216, 3, 2), (2, 9, 8), (8, 12, 1), (3, 2, 216)])
 def test_generic_lengths(grid, prec):
     check(grid, prec, "classical")
+
+
+@pytest.mark.parametrize("prec", ["fp64", "fp32"])
+@pytest.mark.parametrize("n", [16, 32, 48, 54, 96, 144, 192, 256])
+def test_gamma_many_pencils(n, prec):
+    """More pencils (73 x 81 or 73 x 27, odd) than one to a block is used for."""
+    check((144, 27 if 128 < n < 256 else 81, n), prec, "classical")
