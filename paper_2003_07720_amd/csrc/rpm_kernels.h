@@ -1233,11 +1233,12 @@ __device__ __forceinline__ void gdots_tile(const Fields<TA>& a, long long t0, co
     }
 }
 
+// (Arguments in one struct: see RecombineArgs.)
 // SITE separates the call sites in profiles (0: the per-step projections, 1:
 // basis growth); both read the basis with non-temporal loads.
 template <typename TA, typename TZ, int NF, int SITE>
-__global__ __launch_bounds__(512) void k_gdots(Fields<TA> a, const TZ* __restrict__ Z, int p, int zP, long long N,
-                                               double* __restrict__ part, int ld)
+__device__ __forceinline__ void gdots_body(Fields<TA> a, const TZ* __restrict__ Z, int p, int zP, long long N,
+                                           double* __restrict__ part, int ld)
 {
     const int lane = threadIdx.x & 63;
     const int g = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);  // wave-uniform
@@ -1267,6 +1268,21 @@ __global__ __launch_bounds__(512) void k_gdots(Fields<TA> a, const TZ* __restric
         }
 }
 
+template <typename TA, typename TZ>
+struct GdotsArgs {
+    Fields<TA> a;
+    const TZ* Z;
+    long long N;
+    double* part;
+    int p, zP, ld;
+};
+
+template <typename TA, typename TZ, int NF, int SITE>
+__global__ __launch_bounds__(512) void k_gdots(GdotsArgs<TA, TZ> a)
+{
+    gdots_body<TA, TZ, NF, SITE>(a.a, a.Z, a.p, a.zP, a.N, a.part, a.ld);
+}
+
 // The per-step products with the columns split finer: a wave owns C columns
 // (the block has ceil(p / C) <= 16 waves) and streams their slices of TB
 // consecutive tiles per round (C * TB loads issued together), so the block's
@@ -1276,8 +1292,8 @@ __global__ __launch_bounds__(512) void k_gdots(Fields<TA> a, const TZ* __restric
 // loads per column slice: TB = 1, 6-9 % faster).  Same partial-sum layout as
 // k_gdots.
 template <typename TA, typename TZ, int NF, int SITE, int C, int TB, bool NT>
-__global__ __launch_bounds__(1024) void k_gdots_split(Fields<TA> a, const TZ* __restrict__ Z, int p, int zP,
-                                                      long long N, double* __restrict__ part, int ld)
+__device__ __forceinline__ void gdots_split_body(Fields<TA> a, const TZ* __restrict__ Z, int p, int zP,
+                                                 long long N, double* __restrict__ part, int ld)
 {
     const int lane = threadIdx.x & 63;
     const int g = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);  // wave-uniform
@@ -1342,6 +1358,12 @@ __global__ __launch_bounds__(1024) void k_gdots_split(Fields<TA> a, const TZ* __
             const double sum = wave_sum(acc[f][u]);
             if (lane == 0 && u < nj) part[(long long)(f * ld + j0 + u) * gridDim.x + blockIdx.x] = sum;
         }
+}
+
+template <typename TA, typename TZ, int NF, int SITE, int C, int TB, bool NT>
+__global__ __launch_bounds__(1024) void k_gdots_split(GdotsArgs<TA, TZ> a)
+{
+    gdots_split_body<TA, TZ, NF, SITE, C, TB, NT>(a.a, a.Z, a.p, a.zP, a.N, a.part, a.ld);
 }
 
 // Update-and-project (Gram-Schmidt step) k_tdots: a wave owns whole tiles;
@@ -1453,10 +1475,9 @@ __device__ __forceinline__ void tdots_tile(TA* __restrict__ a0, TA* __restrict__
 }
 
 template <typename TA, typename TZ, int NF, int PC, bool UPD, bool NRM>
-__global__ __launch_bounds__(kThreads) void k_tdots(TA* __restrict__ a0, TA* __restrict__ a1,
-                                                    const TZ* __restrict__ Z, int p, int zP,
-                                                    const double* __restrict__ coef, long long N,
-                                                    double* __restrict__ part, int ld, int rs)
+__device__ __forceinline__ void tdots_body(TA* __restrict__ a0, TA* __restrict__ a1, const TZ* __restrict__ Z,
+                                           int p, int zP, const double* __restrict__ coef, long long N,
+                                           double* __restrict__ part, int ld, int rs)
 {
     static_assert(NF == 1 || NF == 2, "one or two fields");
     constexpr int NM = tdots_nrm<NF>();
@@ -1520,13 +1541,30 @@ __global__ __launch_bounds__(kThreads) void k_tdots(TA* __restrict__ a0, TA* __r
     }
 }
 
+template <typename TA, typename TZ>
+struct TdotsArgs {
+    TA* a0;
+    TA* a1;
+    const TZ* Z;
+    const double* coef;
+    long long N;
+    double* part;
+    int p, zP, ld, rs;
+};
+
+template <typename TA, typename TZ, int NF, int PC, bool UPD, bool NRM>
+__global__ __launch_bounds__(kThreads) void k_tdots(TdotsArgs<TA, TZ> a)
+{
+    tdots_body<TA, TZ, NF, PC, UPD, NRM>(a.a0, a.a1, a.Z, a.p, a.zP, a.coef, a.N, a.part, a.ld, a.rs);
+}
+
 // ---------------------------------------------------------------------------
 // Reductions of per-block partial sums (fixed order: deterministic).
 // ---------------------------------------------------------------------------
 // out[f * os + j] = sum_b part[f * fs + b * bs + j * cs].  grid: (j, f).
-static __global__ __launch_bounds__(kThreads) void k_reduce_cols(const double* __restrict__ part, int G, long long bs,
-                                                                 long long cs, long long fs, int os,
-                                                                 double* __restrict__ out)
+static __device__ __forceinline__ void reduce_cols_body(const double* __restrict__ part, int G, long long bs,
+                                                        long long cs, long long fs, int os,
+                                                        double* __restrict__ out)
 {
     __shared__ double red[kWaves];
     __shared__ double tot[1];
@@ -1537,6 +1575,20 @@ static __global__ __launch_bounds__(kThreads) void k_reduce_cols(const double* _
     double v[1] = {acc};
     wg_sum_store<1>(v, tot, red);
     if (threadIdx.x == 0) out[f * os + j] = tot[0];
+}
+
+struct ReduceArgs {
+    const double* part;
+    long long bs;
+    long long cs;
+    long long fs;
+    double* out;
+    int G, os;
+};
+
+static __global__ __launch_bounds__(kThreads) void k_reduce_cols(ReduceArgs a)
+{
+    reduce_cols_body(a.part, a.G, a.bs, a.cs, a.fs, a.os, a.out);
 }
 
 // ---------------------------------------------------------------------------
@@ -1559,19 +1611,18 @@ static __global__ __launch_bounds__(kThreads) void k_reduce_cols(const double* _
 // on 64 threads).
 // ---------------------------------------------------------------------------
 constexpr int kStepThreads = 1024;
-static __global__ __launch_bounds__(kStepThreads) void k_step_end(DevState* __restrict__ st,
-                                                                  const double* __restrict__ part_err, int G_err,
-                                                                  const double* __restrict__ part_dots, int G_dots,
-                                                                  int ld, int p, int slot, int two_d,
-                                                                  int newton_only, int err_mode, int direct,
-                                                                  double* __restrict__ hist, int hist_cap)
+static __device__ __forceinline__ void step_end_body(DevState* __restrict__ st,
+                                                     const double* __restrict__ part_err, int G_err,
+                                                     const double* __restrict__ part_dots, int G_dots, int ld,
+                                                     int p, int slot, int two_d, int newton_only, int err_mode,
+                                                     int direct, double* __restrict__ hist, int hist_cap)
 {
     constexpr int NW = kStepThreads / 64;
     __shared__ int snow;
     __shared__ double sums[2 * kMaxP], red[NW], dprev[kMaxP], r[kMaxP], mv[NW][kMaxP];
     __shared__ double Gs[kMaxP * kMaxP], Ai[kMaxP * kMaxP];
     const int t = threadIdx.x, lane = t & 63, wave = t >> 6;
-    if (st->done) return;  // uniform
+    const int stop = st->done;  // uniform; looked at when the loads are on their way
     const bool sing = st->singular != 0;
     // thread 0 reads every state scalar of the step at once (independent
     // loads, one memory round trip) before any decision
@@ -1612,6 +1663,7 @@ static __global__ __launch_bounds__(kStepThreads) void k_step_end(DevState* __re
         v = wave_sum(v);
         if (lane == 0) sums[o] = v;
     }
+    if (stop) return;
     __syncthreads();
     if (t == 0) {
         int done = 0;
@@ -1698,6 +1750,20 @@ static __global__ __launch_bounds__(kStepThreads) void k_step_end(DevState* __re
     }
     const double y = product(Ai, r);
     if (t < p) st->d[t] = y - r[t];  // z' - zeta = (z + y) - zeta
+}
+
+struct StepEndArgs {
+    DevState* st;
+    const double* part_err;
+    const double* part_dots;
+    double* hist;
+    int G_err, G_dots, ld, p, slot, two_d, newton_only, err_mode, direct, hist_cap;
+};
+
+static __global__ __launch_bounds__(kStepThreads) void k_step_end(StepEndArgs a)
+{
+    step_end_body(a.st, a.part_err, a.G_err, a.part_dots, a.G_dots, a.ld, a.p, a.slot, a.two_d,
+        a.newton_only, a.err_mode, a.direct, a.hist, a.hist_cap);
 }
 
 // Checksum of the phase map (part of the basis reuse key): wrapping sums over
@@ -2102,10 +2168,9 @@ __global__ __launch_bounds__(kThreads) void k_growth_diff(const T* __restrict__ 
 // issued together (non-temporal); slots past p repeat column p - 1 with
 // coefficient zero.
 template <typename T, bool NT>
-__global__ __launch_bounds__(kThreads) void k_recombine(const T* __restrict__ xi, const T* __restrict__ Z, int p,
-                                                        int zP, const double* __restrict__ dco,
-                                                        T* __restrict__ eps, long long n,
-                                                        const int* __restrict__ done)
+__device__ __forceinline__ void recombine_body(const T* __restrict__ xi, const T* __restrict__ Z, int p,
+                                               int zP, const double* __restrict__ dco, T* __restrict__ eps,
+                                               long long n, const int* __restrict__ done)
 {
     constexpr int VL = 16 / sizeof(T);
     using V = typename Vec4<T>::type;
@@ -2148,6 +2213,29 @@ __global__ __launch_bounds__(kThreads) void k_recombine(const T* __restrict__ xi
             eps[i] = v;
         }
     }
+}
+
+// The kernels that a step launches take their arguments as one struct of at most 112
+// bytes: a launch costs the host 2.6-2.8 us then, 3.8 with nine or more separate
+// arguments (3.4-3.7 with a larger struct), and the chain of a small grid, whose
+// kernels take 2.5 to 6 us, waits for the host where that is slower.  One step,
+// separate arguments / one struct: 32^2 FP64 30.0 / 28.2 us, 64^2 32.3 / 28.4, 32^3
+// 41.1 / 37.8, 48^3 FP32 46.8 / 44.1.
+template <typename T>
+struct RecombineArgs {
+    const T* xi;
+    const T* Z;
+    const double* dco;
+    T* eps;
+    long long n;
+    const int* done;
+    int p, zP;
+};
+
+template <typename T, bool NT>
+__global__ __launch_bounds__(kThreads) void k_recombine(RecombineArgs<T> a)
+{
+    recombine_body<T, NT>(a.xi, a.Z, a.p, a.zP, a.dco, a.eps, a.n, a.done);
 }
 
 // The same recombination with the columns split over the waves of a block:

@@ -167,6 +167,16 @@ __device__ __forceinline__ void apply_twiddles(cx<T>* v, const cx<T> (&w)[R])
     for (int k = 1; k < R; ++k) v[k] = cmul(v[k], D > 0 ? cconj(w[k]) : w[k]);
 }
 
+// The grid as these passes take it (Geo is more than their arguments have room for).
+struct PGeo {
+    int ny, nz, nh;
+    long long N, nspec;
+    __device__ __forceinline__ PGeo(int nx, int ny_, int nz_, int nh_)
+        : ny(ny_), nz(nz_), nh(nh_), N((long long)nx * ny_ * nz_), nspec((long long)nh_ * ny_ * nz_)
+    {
+    }
+};
+
 // Rows per x- or y-pass tile: the transposed side moves in segments of this
 // many complex numbers (128 bytes; FP64 lengths whose smaller factor would leave
 // half a wave idle take 16 rows).
@@ -183,10 +193,8 @@ constexpr int tile_threads() { return (tile_rows<T, N>() * Fac<N>::B + 63) / 64 
 // B, A of them side by side) and the second along z, inverse the other way.
 // ---------------------------------------------------------------------------
 template <typename T, int N, int D>
-__global__ __launch_bounds__((tile_threads<T, N>())) void k_py(const cx<T>* __restrict__ Sin,
-                                                               cx<T>* __restrict__ Sout, Geo g, int nzt,
-                                                               const cx<T>* __restrict__ tw,
-                                                               const int* __restrict__ done)
+__device__ __forceinline__ void py_body(const cx<T>* __restrict__ Sin, cx<T>* __restrict__ Sout, const PGeo& g,
+                                        int nzt, const cx<T>* __restrict__ tw, const int* __restrict__ done)
 {
     const int stop = done ? *done : 0;
     constexpr int TZ = tile_rows<T, N>(), NT = tile_threads<T, N>(), LS = TZ + 1;
@@ -248,6 +256,23 @@ __global__ __launch_bounds__((tile_threads<T, N>())) void k_py(const cx<T>* __re
     }
 }
 
+template <typename T>
+struct PyArgs {
+    const cx<T>* Sin;
+    cx<T>* Sout;
+    const cx<T>* tw;
+    const int* done;
+    int nh, nz, nzt;
+};
+static_assert(sizeof(PyArgs<double>) <= 112, "one cheap launch");
+
+template <typename T, int N, int D>
+__global__ __launch_bounds__((tile_threads<T, N>())) void k_py(PyArgs<T> a)
+{
+    const PGeo g(0, N, a.nz, a.nh);
+    py_body<T, N, D>(a.Sin, a.Sout, g, a.nzt, a.tw, a.done);
+}
+
 // Blocks of the x passes: tile and component pair of block id b.  The pairs of a
 // tile go to the same XCD (blocks are dealt to the eight in turn), whose L2 then
 // serves the strains they share.  Returns false past the last tile.
@@ -285,13 +310,11 @@ __device__ __forceinline__ void block_sum(double (&v)[M], double* __restrict__ d
 // spectrum to S1[c][kx][z][y], <eps> partial sums of the pair's components.
 // ---------------------------------------------------------------------------
 template <typename T, int N, int NP>
-__global__ __launch_bounds__((tile_threads<T, N>())) void k_pxf(const T* __restrict__ xin,
-                                                                const uint8_t* __restrict__ phase,
-                                                                const double* __restrict__ lame, int use_ref,
-                                                                double lam0, double mu0, cx<T>* __restrict__ S1,
-                                                                double* __restrict__ part_mean, Geo g, int ntiles,
-                                                                int nyt, const cx<T>* __restrict__ tw,
-                                                                const int* __restrict__ done)
+__device__ __forceinline__ void pxf_body(const T* __restrict__ xin, const uint8_t* __restrict__ phase,
+                                         const double* __restrict__ lame, int nph, int use_ref, double lam0, double mu0,
+                                         cx<T>* __restrict__ S1, double* __restrict__ part_mean, const PGeo& g,
+                                         int ntiles, int nyt, const cx<T>* __restrict__ tw,
+                                         const int* __restrict__ done)
 {
     const int stop = done ? *done : 0;
     constexpr int TY = tile_rows<T, N>(), NT = tile_threads<T, N>(), LS = TY + 1;
@@ -320,7 +343,7 @@ __global__ __launch_bounds__((tile_threads<T, N>())) void k_pxf(const T* __restr
     const bool tab = pair < 3 && !use_ref;
     int lab[I1][R1];
     if (tab) {
-        for (int i = threadIdx.x; i < 2 * g.nph; i += NT) lt[i] = (T)lame[i];
+        for (int i = threadIdx.x; i < 2 * nph; i += NT) lt[i] = (T)lame[i];
         each([&](int i, int q, int o, bool) { lab[i][q] = (int)ph[o]; });
     }
     cx<T> w[I1][R1];
@@ -419,6 +442,28 @@ __global__ __launch_bounds__((tile_threads<T, N>())) void k_pxf(const T* __restr
     if (part_mean && pair < 3) block_sum<2, NT>(ms, part_mean + (long long)tile * 6 + 2 * pair);
 }
 
+template <typename T>
+struct PxfArgs {
+    const T* xin;
+    const uint8_t* phase;
+    const double* lame;
+    cx<T>* S1;
+    double* part_mean;
+    const cx<T>* tw;
+    const int* done;
+    double lam0, mu0;
+    int use_ref, nph, ny, nz, ntiles, nyt;
+};
+static_assert(sizeof(PxfArgs<double>) <= 112, "one cheap launch");
+
+template <typename T, int N, int NP>
+__global__ __launch_bounds__((tile_threads<T, N>())) void k_pxf(PxfArgs<T> a)
+{
+    const PGeo g(N, a.ny, a.nz, N / 2 + 1);
+    pxf_body<T, N, NP>(a.xin, a.phase, a.lame, a.nph, a.use_ref, a.lam0, a.mu0, a.S1, a.part_mean, g, a.ntiles, a.nyt,
+                       a.tw, a.done);
+}
+
 // ---------------------------------------------------------------------------
 // x-inverse: S1 -> complex-to-real transform along x, out = eps - t (OUT_XI) or
 // t (OUT_T), for one packed pair.  Entries k > N/2 of the packed pair are
@@ -428,7 +473,7 @@ __global__ __launch_bounds__((tile_threads<T, N>())) void k_pxf(const T* __restr
 // t of tile_threads).
 template <typename T, int N>
 __device__ __forceinline__ void xinv_first(const cx<T>* __restrict__ S1, cx<T>* X, int q_, int t, int z, int y0,
-                                           const Geo& g, const cx<T>* __restrict__ tw, int stop)
+                                           const PGeo& g, const cx<T>* __restrict__ tw, int stop)
 {
     constexpr int TY = tile_rows<T, N>(), NT = tile_threads<T, N>(), LS = TY + 1;
     constexpr int R1 = Fac<N>::A, R2 = Fac<N>::B, I1 = (R2 * TY + NT - 1) / NT;
@@ -471,12 +516,10 @@ __device__ __forceinline__ void xinv_first(const cx<T>* __restrict__ S1, cx<T>* 
 }
 
 template <typename T, int N>
-__global__ __launch_bounds__((tile_threads<T, N>())) void k_pxi(const cx<T>* __restrict__ S1,
-                                                                const T* __restrict__ eps, T* __restrict__ out,
-                                                                int out_mode, const T* __restrict__ shift,
-                                                                double* __restrict__ part_inc, Geo g, int ntiles,
-                                                                int nyt, const cx<T>* __restrict__ tw,
-                                                                const int* __restrict__ done)
+__device__ __forceinline__ void pxi_body(const cx<T>* __restrict__ S1, const T* __restrict__ eps,
+                                         T* __restrict__ out, int out_mode, const T* __restrict__ shift,
+                                         double* __restrict__ part_inc, const PGeo& g, int ntiles, int nyt,
+                                         const cx<T>* __restrict__ tw, const int* __restrict__ done)
 {
     const int stop = done ? *done : 0;
     constexpr int TY = tile_rows<T, N>(), NT = tile_threads<T, N>(), LS = TY + 1;
@@ -541,6 +584,26 @@ __global__ __launch_bounds__((tile_threads<T, N>())) void k_pxi(const cx<T>* __r
     if (part_inc) block_sum<1, NT>(inc, part_inc + (tile * 3 + pair));
 }
 
+template <typename T>
+struct PxiArgs {
+    const cx<T>* S1;
+    const T* eps;
+    T* out;
+    const T* shift;
+    double* part_inc;
+    const cx<T>* tw;
+    const int* done;
+    int out_mode, ny, nz, ntiles, nyt;
+};
+static_assert(sizeof(PxiArgs<double>) <= 112, "one cheap launch");
+
+template <typename T, int N>
+__global__ __launch_bounds__((tile_threads<T, N>())) void k_pxi(PxiArgs<T> a)
+{
+    const PGeo g(N, a.ny, a.nz, N / 2 + 1);
+    pxi_body<T, N>(a.S1, a.eps, a.out, a.out_mode, a.shift, a.part_inc, g, a.ntiles, a.nyt, a.tw, a.done);
+}
+
 // The polarization map's x-inverse (OUT_XI): t is Gamma0 s_b - beta E, and out =
 // (C + C0)^-1 (sigma + (1 - beta) C0 eps - C0 t) voxel by voxel, so a block takes
 // all three pairs of its tile: side by side in three groups of waves where the
@@ -588,10 +651,12 @@ __device__ __forceinline__ double pol_voxel(const T* __restrict__ eps, T* __rest
 }
 
 template <typename T, int N>
-__global__ __launch_bounds__((pol_groups<T, N>() * tile_threads<T, N>())) void k_pxi_pol(
-    const cx<T>* __restrict__ S1, const T* __restrict__ eps, T* __restrict__ out, const T* __restrict__ shift,
-    double* __restrict__ part_inc, Geo g, int nyt, const cx<T>* __restrict__ tw, const uint8_t* __restrict__ phase,
-    const double* __restrict__ lame, double lam0, double mu0, double beta, const int* __restrict__ done)
+__device__ __forceinline__ void pxi_pol_body(const cx<T>* __restrict__ S1, const T* __restrict__ eps,
+                                             T* __restrict__ out, const T* __restrict__ shift,
+                                             double* __restrict__ part_inc, const PGeo& g, int nyt,
+                                             const cx<T>* __restrict__ tw, const uint8_t* __restrict__ phase,
+                                             const double* __restrict__ lame, double lam0, double mu0,
+                                             double beta, const int* __restrict__ done)
 {
     const int stop = done ? *done : 0;
     constexpr int TY = tile_rows<T, N>(), NT = tile_threads<T, N>(), LS = TY + 1, NG = pol_groups<T, N>();
@@ -667,6 +732,30 @@ __global__ __launch_bounds__((pol_groups<T, N>() * tile_threads<T, N>())) void k
     if (part_inc) block_sum<1, NG * NT>(inc, part_inc + tile);
 }
 
+template <typename T>
+struct PxpArgs {
+    const cx<T>* S1;
+    const T* eps;
+    T* out;
+    const T* shift;
+    double* part_inc;
+    const cx<T>* tw;
+    const uint8_t* phase;
+    const double* lame;
+    const int* done;
+    double lam0, mu0, beta;
+    int ny, nz, nyt;
+};
+static_assert(sizeof(PxpArgs<double>) <= 112, "one cheap launch");
+
+template <typename T, int N>
+__global__ __launch_bounds__((pol_groups<T, N>() * tile_threads<T, N>())) void k_pxi_pol(PxpArgs<T> a)
+{
+    const PGeo g(N, a.ny, a.nz, N / 2 + 1);
+    pxi_pol_body<T, N>(a.S1, a.eps, a.out, a.shift, a.part_inc, g, a.nyt, a.tw, a.phase, a.lame, a.lam0, a.mu0, a.beta,
+                       a.done);
+}
+
 // ---------------------------------------------------------------------------
 // gamma: transform along the last axis, Green operator, inverse transform, in
 // place (see k_gamma for the operator and the k = 0 term).  A block owns P
@@ -712,29 +801,33 @@ struct GCfg {
 };
 
 template <typename T, int N, bool POL, bool WIDE>
-__global__ __launch_bounds__((GCfg<T, N, POL, WIDE>::NT)) void k_pg(cx<T>* __restrict__ S, Geo g,
-                                                              const cx<T>* __restrict__ tw, double lam0, double mu0,
-                                                              double alpha, double beta, int dc_mode,
-                                                              const double* __restrict__ E,
-                                                              const double* __restrict__ part_mean, int n_mean,
-                                                              double* __restrict__ part_err,
-                                                              DevState* __restrict__ st,
-                                                              const int* __restrict__ done)
+__device__ __forceinline__ void pg_body(cx<T>* __restrict__ S, const Geo& g, const cx<T>* __restrict__ tw,
+                                        double lam0, double mu0, double alpha, double beta, int dc_mode,
+                                        const double* __restrict__ E, const double* __restrict__ part_mean,
+                                        int n_mean, double* __restrict__ part_err, DevState* __restrict__ st,
+                                        const int* __restrict__ done)
 {
     const int stop = done ? *done : 0;
     using G = GCfg<T, N, POL, WIDE>;
     constexpr int A = G::A, B = G::B, P = G::P, NT = G::NT, LS = G::LS, NC = G::NC;
     __shared__ cx<T> X[G::SLOTS];
     __shared__ cx<T> W[N];
-    __shared__ double dcm[6];
+    __shared__ double dcm[6], Es[6];
     const int t = threadIdx.x;
     const int npen = g.two_d ? g.nh : g.ny * g.nh;
     const int p0 = blockIdx.x * P;
     // (component, pencil, j or k2, k1)
     auto slot = [](int c, int p, int j, int k) { return ((c * P + p) * B + j) * LS + k; };
+    auto freq = [&](int pen, int i, int& kx, int& ky, int& kz) {
+        const int q = g.two_d ? 0 : (int)((unsigned)pen / (unsigned)g.nh);
+        kx = pen - q * g.nh;
+        ky = g.two_d ? i : q;
+        kz = g.two_d ? 0 : i;
+    };
     // <eps> from the x-pass partial sums (block 0 holds k = 0)
     double acc[6] = {0, 0, 0, 0, 0, 0};
     if (blockIdx.x == 0 && dc_mode == DC_MEAN) {
+        if (t < 6) Es[t] = E[t];
 #pragma unroll 4
         for (int b = t; b < n_mean; b += NT)
 #pragma unroll
@@ -756,7 +849,7 @@ __global__ __launch_bounds__((GCfg<T, N, POL, WIDE>::NT)) void k_pg(cx<T>* __res
             for (int m = t; m < N; m += NT) W[m] = tw[m];
             if constexpr (WIDE) {
                 int kx, ky, kz;
-                gamma_freq(g, p0, t % A + A * (t / A % B), kx, ky, kz);
+                freq(p0, t % A + A * (t / A % B), kx, ky, kz);
                 at = green_at<T>(kx, ky, kz, g, lam0, mu0);
             }
             if (stop) return;
@@ -791,10 +884,10 @@ __global__ __launch_bounds__((GCfg<T, N, POL, WIDE>::NT)) void k_pg(cx<T>* __res
         const int pen = p0 + p;
         if (pen < npen) {
             int kx, ky, kz;
-            gamma_freq(g, pen, k1 + A * k2, kx, ky, kz);
+            freq(pen, k1 + A * k2, kx, ky, kz);
             if constexpr (!WIDE) at = green_at<T>(kx, ky, kz, g, lam0, mu0);
             esum[0] += gamma_point_at<T, POL>(X + slot(0, p, k2, k1), P * B * LS, kx, ky, kz, at, g, lam0, mu0, alpha,
-                                              beta, dc_mode, E, dcm, st);
+                                              beta, dc_mode, Es, dcm, st);
         }
     }
     __syncthreads();
@@ -823,6 +916,39 @@ __global__ __launch_bounds__((GCfg<T, N, POL, WIDE>::NT)) void k_pg(cx<T>* __res
         }
     }
     if (part_err) block_sum<1, NT>(esum, part_err + blockIdx.x);
+}
+
+template <typename T>
+struct PgArgs {
+    cx<T>* S;
+    const cx<T>* tw;
+    const double* E;
+    const double* part_mean;
+    double* part_err;
+    DevState* st;
+    const int* done;
+    double lam0, mu0;
+    double c[3];  // 2 pi / n per axis; polarization: alpha, beta
+    int nx, ny, nz;
+    int n_mean;  // partial sums of the mean, 0: no mean (DC_ZERO)
+};
+static_assert(sizeof(PgArgs<double>) <= 112, "one cheap launch");
+
+template <typename T, int N, bool POL, bool WIDE>
+__global__ __launch_bounds__((GCfg<T, N, POL, WIDE>::NT)) void k_pg(PgArgs<T> a)
+{
+    Geo g;
+    g.nx = a.nx;
+    g.ny = a.ny;
+    g.nz = a.nz;
+    g.nh = a.nx / 2 + 1;
+    g.two_d = a.nz == 1;
+    g.N = (long long)a.nx * a.ny * a.nz;
+    g.nspec = (long long)g.nh * a.ny * a.nz;
+    for (int i = 0; i < 3; ++i)
+        g.kh[i] = POL ? 2.0 * 3.14159265358979323846 / (double)(i == 0 ? a.nx : i == 1 ? a.ny : a.nz) : a.c[i];
+    pg_body<T, N, POL, WIDE>(a.S, g, a.tw, a.lam0, a.mu0, POL ? a.c[0] : 0.0, POL ? a.c[1] : 0.0,
+                             a.n_mean > 0 ? DC_MEAN : DC_ZERO, a.E, a.part_mean, a.n_mean, a.part_err, a.st, a.done);
 }
 
 // ---------------------------------------------------------------------------

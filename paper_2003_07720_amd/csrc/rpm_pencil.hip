@@ -13,8 +13,9 @@ void Pencil<T, N>::y_pass(int dir, int comps, const cx<T>* in, cx<T>* out, const
 {
     const int nzt = (g.nz + rows() - 1) / rows(), grid = comps * g.nh * nzt;
     constexpr int NT = tile_threads<T, N>();
-    if (dir < 0) k_py<T, N, -1><<<grid, NT, 0, s>>>(in, out, g, nzt, tw, done);
-    else k_py<T, N, +1><<<grid, NT, 0, s>>>(in, out, g, nzt, tw, done);
+    const PyArgs<T> a{in, out, tw, done, g.nh, g.nz, nzt};
+    if (dir < 0) k_py<T, N, -1><<<grid, NT, 0, s>>>(a);
+    else k_py<T, N, +1><<<grid, NT, 0, s>>>(a);
 }
 
 template <typename T, int N>
@@ -24,12 +25,9 @@ void Pencil<T, N>::x_forward(bool pol, const T* xin, const uint8_t* phase, const
 {
     const int nyt = (g.ny + rows() - 1) / rows(), nt = g.nz * nyt;
     constexpr int NT = tile_threads<T, N>();
-    if (pol)
-        k_pxf<T, N, 6><<<x_grid(nt, 6), NT, 0, s>>>(xin, phase, lame, use_ref, lam0, mu0, S1, part_mean, g, nt, nyt,
-                                                    tw, done);
-    else
-        k_pxf<T, N, 3><<<x_grid(nt, 3), NT, 0, s>>>(xin, phase, lame, use_ref, lam0, mu0, S1, part_mean, g, nt, nyt,
-                                                    tw, done);
+    const PxfArgs<T> a{xin, phase, lame, S1, part_mean, tw, done, lam0, mu0, use_ref, g.nph, g.ny, g.nz, nt, nyt};
+    if (pol) k_pxf<T, N, 6><<<x_grid(nt, 6), NT, 0, s>>>(a);
+    else k_pxf<T, N, 3><<<x_grid(nt, 3), NT, 0, s>>>(a);
 }
 
 template <typename T, int N>
@@ -41,10 +39,11 @@ void Pencil<T, N>::x_inverse(bool pol, const cx<T>* S1, const T* eps, T* out, in
     const int nyt = (g.ny + rows() - 1) / rows(), nt = g.nz * nyt;
     constexpr int NT = tile_threads<T, N>();
     if (pol)
-        k_pxi_pol<T, N><<<nt, pol_groups<T, N>() * NT, 0, s>>>(S1, eps, out, shift, part_inc, g, nyt, tw, phase, lame,
-                                                               lam0, mu0, beta, done);
+        k_pxi_pol<T, N><<<nt, pol_groups<T, N>() * NT, 0, s>>>(PxpArgs<T>{
+            S1, eps, out, shift, part_inc, tw, phase, lame, done, lam0, mu0, beta, g.ny, g.nz, nyt});
     else
-        k_pxi<T, N><<<x_grid(nt, 3), NT, 0, s>>>(S1, eps, out, out_mode, shift, part_inc, g, nt, nyt, tw, done);
+        k_pxi<T, N><<<x_grid(nt, 3), NT, 0, s>>>(
+            PxiArgs<T>{S1, eps, out, shift, part_inc, tw, done, out_mode, g.ny, g.nz, nt, nyt});
 }
 
 template <typename T, int N>
@@ -53,10 +52,15 @@ void Pencil<T, N>::gamma(bool pol, cx<T>* S, const Geo& g, const cx<T>* tw, doub
                          double* part_err, DevState* st, const int* done, hipStream_t s)
 {
     const int npen = g.two_d ? g.nh : g.ny * g.nh;
+    PgArgs<T> a{S,   tw,  E,    part_mean,    part_err, st,   done,
+                lam0, mu0, {g.kh[0], g.kh[1], g.kh[2]}, g.nx, g.ny, g.nz, dc_mode == DC_MEAN ? n_mean : 0};
+    if (pol) {
+        a.c[0] = alpha;
+        a.c[1] = beta;
+    }
     auto launch = [&](auto p, auto w) {
         constexpr bool POL = decltype(p)::value, W = decltype(w)::value;
-        k_pg<T, N, POL, W><<<gamma_blocks(POL, npen), GCfg<T, N, POL, W>::NT, 0, s>>>(
-            S, g, tw, lam0, mu0, alpha, beta, dc_mode, E, part_mean, n_mean, part_err, st, done);
+        k_pg<T, N, POL, W><<<gamma_blocks(POL, npen), GCfg<T, N, POL, W>::NT, 0, s>>>(a);
     };
     using std::false_type, std::true_type;
     if (pol) launch(true_type(), true_type());

@@ -549,12 +549,14 @@ void run_F(Ctx<T>& c, const T* xin, int p_corr, T* eps_store, const T* eps_for_i
                                                                                        c.st->d, eps_store, done);
                     if (off < nel)
                         k_recombine<T, NT><<<(int)((nel - off) / VL + kThreads - 1) / kThreads + 1, kThreads, 0,
-                                             c.s>>>(xin + off, c.Zb() + off * c.pmax, p_corr, c.pmax, c.st->d,
-                                                    eps_store + off, nel - off, done);
+                                             c.s>>>(RecombineArgs<T>{xin + off, c.Zb() + off * c.pmax, c.st->d,
+                                                                     eps_store + off, nel - off, done, p_corr,
+                                                                     c.pmax});
                     return;
                 }
             }
-            k_recombine<T, NT><<<gb, kThreads, 0, c.s>>>(xin, c.Zb(), p_corr, c.pmax, c.st->d, eps_store, nel, done);
+            k_recombine<T, NT><<<gb, kThreads, 0, c.s>>>(
+                RecombineArgs<T>{xin, c.Zb(), c.st->d, eps_store, nel, done, p_corr, c.pmax});
         };
         c.mark_begin(RPM_K_RECOMBINE, ev);
         if (fieldB * p_corr <= kCachedBasis) launch(std::false_type());
@@ -651,7 +653,7 @@ template <typename TA, typename TZ, int NF, int SITE>
 void launch_gdots(hipStream_t s, int G, Fields<TA> a, const TZ* Z, int p, int zP, long long N, double* part, int ld)
 {
     const int ng = (p + 7) / 8;
-    k_gdots<TA, TZ, NF, SITE><<<G, 64 * ng, 0, s>>>(a, Z, p, zP, N, part, ld);
+    k_gdots<TA, TZ, NF, SITE><<<G, 64 * ng, 0, s>>>(GdotsArgs<TA, TZ>{a, Z, N, part, p, zP, ld});
 }
 
 // v_f <- v_f - sum_j coef[f * kMaxP + j] Z_j (f < NF), then the products
@@ -661,14 +663,11 @@ template <typename TZ, int NF, bool NRM>
 void launch_update(hipStream_t s, int G, double* v0, double* v1, const TZ* Z, int p, int zP, const double* coef,
                    long long N, double* part, int rs)
 {
-    if (p <= 8)
-        k_tdots<double, TZ, NF, 8, true, NRM><<<G, kThreads, 0, s>>>(v0, v1, Z, p, zP, coef, N, part, kMaxP, rs);
-    else if (p <= 16)
-        k_tdots<double, TZ, NF, 16, true, NRM><<<G, kThreads, 0, s>>>(v0, v1, Z, p, zP, coef, N, part, kMaxP, rs);
-    else if (p <= 32)
-        k_tdots<double, TZ, NF, 32, true, NRM><<<G, kThreads, 0, s>>>(v0, v1, Z, p, zP, coef, N, part, kMaxP, rs);
-    else if constexpr (NF == 1)
-        k_tdots<double, TZ, 1, 64, true, NRM><<<G, kThreads, 0, s>>>(v0, v1, Z, p, zP, coef, N, part, kMaxP, rs);
+    const TdotsArgs<double, TZ> a{v0, v1, Z, coef, N, part, p, zP, kMaxP, rs};
+    if (p <= 8) k_tdots<double, TZ, NF, 8, true, NRM><<<G, kThreads, 0, s>>>(a);
+    else if (p <= 16) k_tdots<double, TZ, NF, 16, true, NRM><<<G, kThreads, 0, s>>>(a);
+    else if (p <= 32) k_tdots<double, TZ, NF, 32, true, NRM><<<G, kThreads, 0, s>>>(a);
+    else if constexpr (NF == 1) k_tdots<double, TZ, 1, 64, true, NRM><<<G, kThreads, 0, s>>>(a);
 }
 
 // zeta_j = <Z_j, xi> (and, direct, z_j = <Z_j, eps>) partial sums for the Newton step.
@@ -688,13 +687,9 @@ void project(Ctx<T>& c, const T* xi, const T* eps, int p, bool direct)
         auto launch = [&](auto nt) {
             constexpr bool NT = decltype(nt)::value;
             constexpr bool f4 = sizeof(T) == 4;
-            const Fields<T> f{{xi}};
-            if (p <= 32)
-                k_gdots_split<T, T, 1, 0, 2, f4 ? 8 : 1, NT><<<c.sh.Gq, 64 * ((p + 1) / 2), 0, c.s>>>(
-                    f, c.Zb(), p, c.pmax, c.sh.g.N, c.pdots(), c.L.ld);
-            else
-                k_gdots_split<T, T, 1, 0, 4, f4 ? 4 : 1, NT><<<c.sh.Gq, 64 * ((p + 3) / 4), 0, c.s>>>(
-                    f, c.Zb(), p, c.pmax, c.sh.g.N, c.pdots(), c.L.ld);
+            const GdotsArgs<T, T> a{Fields<T>{{xi}}, c.Zb(), c.sh.g.N, c.pdots(), p, c.pmax, (int)c.L.ld};
+            if (p <= 32) k_gdots_split<T, T, 1, 0, 2, f4 ? 8 : 1, NT><<<c.sh.Gq, 64 * ((p + 1) / 2), 0, c.s>>>(a);
+            else k_gdots_split<T, T, 1, 0, 4, f4 ? 4 : 1, NT><<<c.sh.Gq, 64 * ((p + 3) / 4), 0, c.s>>>(a);
         };
         if (6.0 * (double)c.sh.g.N * sizeof(T) * p <= kCachedBasis) launch(std::false_type());
         else launch(std::true_type());
@@ -711,9 +706,10 @@ void reduce_and_finalize(Ctx<T>& c, int p, int slot, int newton_only, bool direc
                                      : (err_mode == 0 ? c.template at<double>(c.L.perr)
                                                       : c.template at<double>(c.L.pinc));
     c.mark_begin(RPM_K_FINAL, ev);
-    k_step_end<<<1, kStepThreads, 0, c.s>>>(c.st, perr, err_mode == 0 ? c.sh.g3() : c.sh.ginc(), c.pdots(), c.sh.Gq,
-                                            c.L.ld, p, slot & 3, c.sh.g.two_d, newton_only, err_mode, direct ? 1 : 0,
-                                            c.template at<double>(c.L.hist), (int)c.L.hist_cap);
+    k_step_end<<<1, kStepThreads, 0, c.s>>>(StepEndArgs{c.st, perr, c.pdots(), c.template at<double>(c.L.hist),
+                                                        err_mode == 0 ? c.sh.g3() : c.sh.ginc(), c.sh.Gq, (int)c.L.ld,
+                                                        p, slot & 3, c.sh.g.two_d, newton_only, err_mode,
+                                                        direct ? 1 : 0, (int)c.L.hist_cap});
     c.mark_end(RPM_K_FINAL, ev);
     c.check_launch();
 }
@@ -732,7 +728,7 @@ template <typename T>
 void reduce_cols(Ctx<T>& c, const double* part, int G, long long bs, long long cs, int m, double* out, int nf = 1,
                  long long fs = 0, int os = 0)
 {
-    k_reduce_cols<<<dim3((unsigned)m, (unsigned)nf), kThreads, 0, c.s>>>(part, G, bs, cs, fs, os, out);
+    k_reduce_cols<<<dim3((unsigned)m, (unsigned)nf), kThreads, 0, c.s>>>(ReduceArgs{part, bs, cs, fs, out, G, os});
 }
 
 // Checksum of the phase map for the reuse key of the basis, before its first column.
@@ -1925,9 +1921,10 @@ rpm_status eff_batched(const rpm_problem* pr, const rpm_options* o, double* C, r
         }
         for (int f = 0; f < nb; ++f) {
             const double* bpd = c.template at<double>(c.L.bpd) + (long long)f * kMaxP * c.sh.Gq;
-            k_step_end<<<1, kStepThreads, 0, c.s>>>(cx[f].st, cx[f].template at<double>(cx[f].L.perr), c.sh.g3(), bpd,
-                                                    c.sh.Gq, kMaxP, p, it & 3, g.two_d, 0, 0, 0,
-                                                    cx[f].template at<double>(cx[f].L.hist), (int)c.L.hist_cap);
+            k_step_end<<<1, kStepThreads, 0, c.s>>>(
+                StepEndArgs{cx[f].st, cx[f].template at<double>(cx[f].L.perr), bpd,
+                            cx[f].template at<double>(cx[f].L.hist), c.sh.g3(), c.sh.Gq, kMaxP, p, it & 3, g.two_d, 0,
+                            0, 0, (int)c.L.hist_cap});
         }
         c.check_launch();
         ++nu;
