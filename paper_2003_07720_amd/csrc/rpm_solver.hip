@@ -267,14 +267,16 @@ Layout make_layout(const Shapes<T>& s, const rpm_options* o, bool map_only)
     const Geo& g = s.g;
     const size_t fT = map_only ? 0 : (size_t)6 * g.N * sizeof(T);
     const size_t fD = (size_t)6 * g.N * sizeof(double);
-    const size_t spec = (size_t)g.ncomp * g.nspec * sizeof(cx<T>);
+    // (whole 64 KB blocks per six components: twelve take exactly twice the room of six)
+    const size_t spec6 = (size_t)6 * g.nspec * sizeof(cx<T>);
+    const size_t spec = (size_t)(g.ncomp / 6) * (spec6 < kBigAlign ? spec6 : (spec6 + kBigAlign - 1) / kBigAlign * kBigAlign);
     const int pmax = (o->scheme == RPM_SCHEME_RPM && !map_only) ? o->p_max : 0;
     L.ld = kMaxP;
     L.hist_cap = map_only ? 2 : (long long)o->max_iter + 1;
     size_t off = 0;
-    auto take = [&](size_t bytes) {
+    auto take = [&](size_t bytes, bool big = true) {
         // fields, spectra and the basis on 64 KB boundaries
-        if (bytes >= kBigAlign) off = (off + kBigAlign - 1) / kBigAlign * kBigAlign;
+        if (big && bytes >= kBigAlign) off = (off + kBigAlign - 1) / kBigAlign * kBigAlign;
         size_t at = off;
         off = align_up(off + bytes);
         return at;
@@ -337,8 +339,8 @@ Layout make_layout(const Shapes<T>& s, const rpm_options* o, bool map_only)
     }
     // last: its size follows max_iter, which may differ between calls that
     // carry the basis, so nothing the workspace keeps may sit behind it
-    L.hist = take(sizeof(double) * L.hist_cap);
-    for (int f = 1; f < L.nb; ++f) L.cs[f].hist = take(sizeof(double) * L.hist_cap);
+    L.hist = take(sizeof(double) * L.hist_cap, false);
+    for (int f = 1; f < L.nb; ++f) L.cs[f].hist = take(sizeof(double) * L.hist_cap, false);
     CaseOff& c0 = L.cs[0];
     c0.st = L.st;
     c0.pmean = L.pmean;
@@ -538,7 +540,7 @@ void run_F(Ctx<T>& c, const T* xin, int p_corr, T* eps_store, const T* eps_for_i
         const int gb = (int)((nel / VL + kThreads - 1) / kThreads) + 1;
         auto launch = [&](auto nt) {
             constexpr bool NT = decltype(nt)::value;
-            if constexpr (sizeof(T) == 4) {
+            if constexpr (sizeof(T) == 4 && NT) {  // (a basis this large is never a cached one)
                 if (split) {
                     // whole groups of RPM_RS_TPB tiles, then the remaining tiles
                     // (addressed from their first tile) one run per thread
