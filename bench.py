@@ -32,16 +32,17 @@ PEAK_HBM_GBS = 8000.0
 # reported while the kernel sources are the ones it was measured on.
 TRAFFIC_FILE = os.path.join(ROOT, "profiles", "traffic_128cube_voids_fp32.json")
 KERNEL_SOURCES = ["include/rpmfft.h", "paper_2003_07720_amd/csrc/rpm_device.h",
-                  "paper_2003_07720_amd/csrc/rpm_kernels.h", "paper_2003_07720_amd/csrc/rpm_solver.hip"]
+                  "paper_2003_07720_amd/csrc/rpm_kernels.h", "paper_2003_07720_amd/csrc/rpm_pencil.h",
+                  "paper_2003_07720_amd/csrc/rpm_pencil.hip", "paper_2003_07720_amd/csrc/rpm_solver.hip"]
 # kernel symbols behind each timing class of rpm_stats ({T}: float or double)
 CLASS_SYMBOLS = {
-    "xfwd": r"rpm::k_xfwd<{T}, (true|false), false(, \d+)?(, (true|false)){0,3}>",
-    "yfwd": r"rpm::k_ypipe<{T}, -1, \d+(, (true|false))?>|rpm::k_yfwd<{T}>|rpm::k_ywave<-1>",
-    "gamma": r"rpm::k_(gamma|gpipe)<{T}, false(, (true|false))?>",
-    "yinv": r"rpm::k_ypipe<{T}, 1, \d+(, (true|false))?>|rpm::k_yinv<{T}>|rpm::k_ywave<1>",
-    "xinv": r"rpm::k_xinv<{T}, false(, \d+)?(, (true|false))?>",
-    "project": r"rpm::k_gdots(_split)?<{T}, {T}, [12], 0(, \d+, \d+)?>",
-    "recombine": r"rpm::k_recombine(_split)?<{T}(, \d+, \d+)?>",
+    "xfwd": r"rpm::k_pxf<{T}, \d+, 3>|rpm::k_xfwd<{T}, (true|false), false(, (true|false))?>",
+    "yfwd": r"rpm::k_py<{T}, \d+, -1>|rpm::k_ypipe<{T}, -1, \d+>|rpm::k_yfwd<{T}>|rpm::k_ywave<-1>",
+    "gamma": r"rpm::k_pg<{T}, \d+, false, (true|false)>|rpm::k_(gamma|gpipe)<{T}, false>",
+    "yinv": r"rpm::k_py<{T}, \d+, 1>|rpm::k_ypipe<{T}, 1, \d+>|rpm::k_yinv<{T}>|rpm::k_ywave<1>",
+    "xinv": r"rpm::k_pxi<{T}, \d+>|rpm::k_xinv<{T}, false>",
+    "project": r"rpm::k_gdots(_split)?<{T}, {T}, [12], 0(, \d+, \d+, (true|false))?>",
+    "recombine": r"rpm::k_recombine(_split)?<{T}, (true|false)(, \d+, \d+)?>",
 }
 
 

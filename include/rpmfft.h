@@ -65,6 +65,10 @@ extern "C" {
  * transformed with the same arithmetic; only the grouping of the per-block
  * error partial sums follows gamma_blocks.  y_regs changes the factorisation
  * of the y transforms, so their rounding.
+ * Axes of 16, 18, 24, 27, 32, 36, 48, 54, 64, 72, 81, 96, 108, 128, 144, 162, 192
+ * or 256 points run passes whose length is fixed at compile time and which have
+ * one launch shape: y_cols, y_blocks (y axis) and gamma_blocks (the axis of the
+ * gamma pass) are checked as ever and change nothing there.
  *   y_cols        z positions per y-pass tile: a divisor of nz, at most
  *                 128 / (2 sizeof(real)) and 8 x 256 / ny; other values make
  *                 the calls that use the tuning return RPM_E_INVALID
@@ -111,7 +115,8 @@ enum { RPM_FP64 = 0,         /* fields, FFTs and Z in double                    
                                 products that form H, H and the Newton solve in
                                 double                                            */
 
-/* kernel classes of rpm_stats.kernel_* (profile = 1) */
+/* kernel classes of rpm_stats.kernel_* (profile = 1).  RPM_K_REDUCE has no launches
+ * of its own: RPM_K_FINAL sums the partials and ends the step.               */
 enum { RPM_K_XFWD = 0, RPM_K_YFWD, RPM_K_GAMMA, RPM_K_YINV, RPM_K_XINV, RPM_K_REDUCE, RPM_K_FINAL,
        RPM_K_GROWTH, RPM_K_PROJECT, RPM_K_RECOMBINE, RPM_NKERNEL };
 
@@ -254,7 +259,8 @@ rpm_status rpm_fft_apply(const rpm_problem *pr, const double E[6], const rpm_opt
  * coordinate at a time, in this order, each from the best so far: y_cols over
  * the admissible divisors of nz (largest first, at most four), then y_blocks
  * and gamma_blocks over 256 x {1, 2, 3, 4, 5, 6, 8} capped at the number of
- * tiles; 0 is tried first for each (the default).  Each candidate: one
+ * tiles; 0 is tried first for each (the default).  A knob that changes nothing on
+ * the grid (see rpm_tuning) is not searched.  Each candidate: one
  * untimed map, then reps maps between HIP events.
  *   reps      1 .. 1000
  *   best      HOST: the fastest shape (fields of 0 where the default won)
