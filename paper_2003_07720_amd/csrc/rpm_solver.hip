@@ -789,7 +789,9 @@ rpm_status prepare(Ctx<T>& c, const rpm_problem* pr, const rpm_options* o, bool 
                sum[0] == sum[1];
         if (keep) p = hs.p;
     }
-    c.keyed = keep;
+    // a later stage leaves the mark as it is: the stage before it may have ended
+    // with an empty basis and no checksum
+    if (!(want_reuse && c.resident)) c.keyed = keep;
     c.resident = true;
     c.p_resident = p;
     *p_io = p;
