@@ -1936,8 +1936,11 @@ rpm_status eff_batched(const rpm_problem* pr, const rpm_options* o, double* C, r
     }
     for (int f = 0; f < nb; ++f)
         if (!seen_done[f]) p_end[f] = p;
-    // per case: the returned iterate, FP64 certification / refinement, outputs
+    // per case: the returned iterate, FP64 certification / refinement, outputs.
+    // Corrections start from the p columns the cases share and may add some, each
+    // case in the same slots.
     rpm_status worst = RPM_OK;
+    int grown = -1;  // the last case that did
     for (int f = 0; f < nb; ++f) {
         SolveOut<T> so;
         cx[f].p_resident = p;
@@ -1952,8 +1955,17 @@ rpm_status eff_batched(const rpm_problem* pr, const rpm_options* o, double* C, r
         double sav[6];
         rs = finish_solve<T>(cx[f], c64, pr, o, so, nullptr, nullptr, sav, stv ? stv + f : nullptr, t0);
         if (rs < 0) return rs;
+        if (so.p > p) grown = f;
         if (rs != RPM_OK && worst == RPM_OK) worst = rs;
         for (int row = 0; row < nb; ++row) C[row * nb + f] = sav[two_d ? cases3[row] : row];
+    }
+    // case 0's state is the one a later call reads: the basis whose columns are the
+    // ones in place, and the checksum of the map
+    if (grown >= 0) {
+        if (grown > 0) k_copy_basis_state<<<1, kThreads, 0, c.s>>>(cx[0].st, cx[grown].st);
+        store_key(cx[0]);
+        c.check_launch();
+        if (hipStreamSynchronize(c.s) != hipSuccess || c.hip_error) return RPM_E_HIP;
     }
     if (c.prof.on) {
         c.prof.harvest();
