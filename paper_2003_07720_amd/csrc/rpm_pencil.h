@@ -339,12 +339,14 @@ __device__ __forceinline__ void pxf_body(const T* __restrict__ xin, const uint8_
             for (int q = 0; q < R1; ++q) f(i, q, in ? r * N + j + R2 * q : 0, in);
         }
     };
-    // phase labels; the table comes from LDS once both have arrived
+    // phase labels; the table comes from LDS once both have arrived.  Labels past
+    // the table take the first of the zeros behind it in memory: voids, as in the
+    // passes that read it there.
     const bool tab = pair < 3 && !use_ref;
     int lab[I1][R1];
     if (tab) {
-        for (int i = threadIdx.x; i < 2 * nph; i += NT) lt[i] = (T)lame[i];
-        each([&](int i, int q, int o, bool) { lab[i][q] = (int)ph[o]; });
+        for (int i = threadIdx.x; i < 2 * min(nph + 1, 256); i += NT) lt[i] = (T)lame[i];
+        each([&](int i, int q, int o, bool) { lab[i][q] = min((int)ph[o], nph); });
     }
     cx<T> w[I1][R1];
 #pragma unroll
