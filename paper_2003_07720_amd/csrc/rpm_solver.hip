@@ -267,16 +267,18 @@ Layout make_layout(const Shapes<T>& s, const rpm_options* o, bool map_only)
     const Geo& g = s.g;
     const size_t fT = map_only ? 0 : (size_t)6 * g.N * sizeof(T);
     const size_t fD = (size_t)6 * g.N * sizeof(double);
-    // (whole 64 KB blocks per six components: twelve take exactly twice the room of six)
+    // (whole 64 KB blocks per six components: twelve take exactly twice the room of
+    // six; the allocation-free map has no room to spare in its fixed scratch)
     const size_t spec6 = (size_t)6 * g.nspec * sizeof(cx<T>);
-    const size_t spec = (size_t)(g.ncomp / 6) * (spec6 < kBigAlign ? spec6 : (spec6 + kBigAlign - 1) / kBigAlign * kBigAlign);
+    const bool whole = !map_only && spec6 >= kBigAlign;
+    const size_t spec = (size_t)(g.ncomp / 6) * (whole ? (spec6 + kBigAlign - 1) / kBigAlign * kBigAlign : spec6);
     const int pmax = (o->scheme == RPM_SCHEME_RPM && !map_only) ? o->p_max : 0;
     L.ld = kMaxP;
     L.hist_cap = map_only ? 2 : (long long)o->max_iter + 1;
     size_t off = 0;
     auto take = [&](size_t bytes, bool big = true) {
         // fields, spectra and the basis on 64 KB boundaries
-        if (big && bytes >= kBigAlign) off = (off + kBigAlign - 1) / kBigAlign * kBigAlign;
+        if (big && !map_only && bytes >= kBigAlign) off = (off + kBigAlign - 1) / kBigAlign * kBigAlign;
         size_t at = off;
         off = align_up(off + bytes);
         return at;
