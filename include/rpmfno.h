@@ -64,7 +64,9 @@ rpm_status rpm_gemm_bf16(int32_t M, int32_t N, int32_t K, int32_t batch, const f
 /* Number of FP32 parameters.  RPM_E_INVALID for an out-of-range config. */
 rpm_status rpm_fno_param_count(const rpm_fno_config *cfg, int64_t *count);
 
-/* Workspace bytes for a grid n = {nx, ny, nz} and a batch of fields. */
+/* Workspace bytes for a grid n = {nx, ny, nz} and a batch of fields.  A larger
+ * buffer lets rpm_fno_backward form the weight gradients of more layers side by
+ * side (L + 1 fields of [batch][C][N] for all of them). */
 rpm_status rpm_fno_workspace_size(const rpm_fno_config *cfg, const int32_t n[3], int32_t batch, size_t *bytes);
 
 /* Initial parameters from a counter-based generator (splitmix64 of seed):

@@ -206,9 +206,10 @@ __global__ void k_add(float* __restrict__ a, const float* __restrict__ b, long l
 // stiffest phase, 10^(3 x0) from the first feature (1 without features), so
 // the strain inside pores -- which carries no stress -- hardly counts;
 // dy = 2 w (y - t) / n; per-block partial sums of w (y - t)^2
-__global__ __launch_bounds__(256) void k_mse(const float* __restrict__ y, const float* __restrict__ t,
+// (dy may be y)
+__global__ __launch_bounds__(256) void k_mse(const float* y, const float* __restrict__ t,
                                              const float* __restrict__ x, int cin, int cout, long long N,
-                                             float* __restrict__ dy, double* __restrict__ part, long long n)
+                                             float* dy, double* __restrict__ part, long long n)
 {
     __shared__ double red[256];
     // a thread takes all channels of a voxel: one weight per voxel
@@ -217,13 +218,20 @@ __global__ __launch_bounds__(256) void k_mse(const float* __restrict__ y, const 
     for (long long i = (long long)blockIdx.x * 256 + threadIdx.x; i < nv; i += (long long)gridDim.x * 256) {
         const long long b = i / N, v = i - b * N;
         const float w = x ? expf(6.90775527898f * x[b * cin * N + v]) : 1.f;
-#pragma unroll 18
-        for (int c = 0; c < cout; ++c) {
-            const long long o = (b * cout + c) * N + v;
-            const float e = y[o] - t[o];
-            if (dy) dy[o] = 2.f * w * e / (float)n;
+        const long long o = b * cout * N + v;
+        auto put = [&](int c, float e) {
+            if (dy) dy[o + c * N] = 2.f * w * e / (float)n;
             s += (double)w * e * e;
+        };
+        int c = 0;
+        for (; c + 18 <= cout; c += 18) {
+            float e[18];
+#pragma unroll
+            for (int u = 0; u < 18; ++u) e[u] = y[o + (c + u) * N] - t[o + (c + u) * N];
+#pragma unroll
+            for (int u = 0; u < 18; ++u) put(c + u, e[u]);
         }
+        for (; c < cout; ++c) put(c, y[o + c * N] - t[o + c * N]);
     }
     red[threadIdx.x] = s;
     __syncthreads();
@@ -331,21 +339,28 @@ Net make_net(const rpm_fno_config* c)
     return n;
 }
 
-// Workspace: twiddles, activations kept for the backward pass, spectral
-// temporaries.  All offsets in floats.
+// Workspace: twiddles, activations kept for the backward pass, temporaries.  All
+// offsets in floats.  What a backward call takes over from the forward call lies
+// in the same place for the fused passes and the batched GEMMs.
 struct FWs {
     long long tw[3];                  // per axis: cos then sin tables, m x n each
     long long h;                      // h_0 .. h_L: (L + 1) x [B][C][N]
     long long pre;                    // pre-activations of the L layers: L x [B][C][N]
     long long xhat;                   // DFT of each layer input: L x 2 x [B][C][m3]
-    long long s1, s2, s3, s4;         // spectral temporaries (2 planes each)
-    long long acc, dh, dh2, dpre;     // [B][C][N] scratch
     long long y;                      // output [B][cout][N]
     long long feat;                   // input features of a warm start [cin][N]
     long long part;                   // loss partial sums (double, 1024)
-    long long tab[3];                 // bfloat16 twiddle tables of the fused passes
-    long long dp;                     // gradients of the pre-activations of all layers: L x [B][C][N]
-    long long wg;                     // results of the fused weight-gradient chains
+    // batched GEMMs: spectral temporaries (2 planes each), [B][C][N] scratch.
+    // Fused passes: s1 and s3 hold a spectrum, s2 and s4 the half-transformed ones on
+    // the way there and back (in one place, k_dft_xy took 5.0 us instead of 4.6)
+    long long s1, s2, s3, s4;
+    long long acc, dh, dh2, dpre;
+    // fused passes: bfloat16 twiddle tables, results of the weight-gradient chains
+    // and, last, room for nd gradients of activations ([B][C][N] each)
+    long long tab[3];
+    long long wg;
+    long long d;
+    int nd;
     long long total;
     long long N;
     int n[3];
@@ -361,7 +376,7 @@ bool fused_fits(const Net& net, const int* n)
            n[1] <= 512 && n[2] <= 512;
 }
 
-FWs make_fws(const Net& net, const int32_t n[3], int B)
+FWs make_fws(const Net& net, const int32_t n[3], int B, bool fused)
 {
     FWs w{};
     const long long N = (long long)n[0] * n[1] * n[2];
@@ -382,25 +397,36 @@ FWs make_fws(const Net& net, const int32_t n[3], int B)
     const long long sx = (long long)B * C * n[2] * n[1] * m;
     const long long sy = (long long)B * C * n[2] * m * m;
     const long long sz = (long long)B * C * net.m3;
-    const long long smax = std::max(std::max(sx, sy), sz);
-    w.s1 = take(2 * smax);
-    w.s2 = take(2 * smax);
-    w.s3 = take(2 * smax);
-    w.s4 = take(2 * smax);
-    w.acc = take((long long)B * std::max<long long>(C, net.cout) * N);
-    w.dh = take((long long)B * std::max<long long>(C, net.cin) * N);
-    w.dh2 = take((long long)B * C * N);
-    w.dpre = take((long long)B * std::max<long long>(C, net.cout) * N);
     w.y = take((long long)B * net.cout * N);
     w.feat = take((long long)net.cin * N);
     w.part = take(2 * 1024);
-    for (int a = 0; a < 3; ++a) w.tab[a] = take(2 * fno::kModeSlots * ((n[a] + 15) / 16 * 16));
-    if (fused_fits(net, n)) {
-        w.dp = take((long long)net.L * B * C * N);
-        const auto t16 = [](int c) { return (c + 15) / 16; };
-        const int mt = std::max(t16(net.C) * std::max(t16(net.C), t16(net.cin)), t16(net.cout) * t16(net.C));
-        w.wg = take((((net.L + 2ll) * B + 7) / 8 * 8) * mt * 256);
+    if (!fused) {
+        const long long smax = std::max(std::max(sx, sy), sz);
+        w.s1 = take(2 * smax);
+        w.s2 = take(2 * smax);
+        w.s3 = take(2 * smax);
+        w.s4 = take(2 * smax);
+        w.acc = take((long long)B * std::max<long long>(C, net.cout) * N);
+        w.dh = take((long long)B * std::max<long long>(C, net.cin) * N);
+        w.dh2 = take((long long)B * C * N);
+        w.dpre = take((long long)B * std::max<long long>(C, net.cout) * N);
+        w.total = off;
+        return w;
     }
+    w.s1 = take(2 * sz);
+    w.s2 = take(2 * sy);
+    w.s3 = take(2 * sz);
+    w.s4 = take(2 * sy);
+    for (int a = 0; a < 3; ++a) w.tab[a] = take(2 * fno::kModeSlots * ((n[a] + 15) / 16 * 16));
+    const auto t16 = [](int c) { return (c + 15) / 16; };
+    const int mt = std::max(t16(net.C) * std::max(t16(net.C), t16(net.cin)), t16(net.cout) * t16(net.C));
+    w.wg = take((((net.L + 2ll) * B + 7) / 8 * 8) * mt * 256);
+    // a backward call of its own keeps the pre-activations and runs all weight gradients
+    // side by side where the gradients of the L + 1 activations find room: as many as the
+    // batched GEMMs' workspace has (the output's place is one more), two at least
+    const long long act = (long long)B * C * N, room = make_fws(net, n, B, false).total - off;
+    w.nd = (int)std::min<long long>(net.L + 1, std::max<long long>(2, room / act));
+    w.d = take(w.nd * act);
     w.total = off;
     return w;
 }
@@ -778,7 +804,7 @@ void fused_forward(Fno& f, const float* P, const float* x, float* y, bool keep_p
     const long long act = (long long)f.B * net.C * f.w.N, xplane = (long long)f.B * net.C * net.m3;
     const long long uplane = (long long)f.B * net.C * f.w.n[2] * net.m * net.m;
     float* h0 = f.at(f.w.h);
-    float *Y = f.at(f.w.s1), *U = f.at(f.w.s3);
+    float *Y = f.at(f.w.s1), *U = f.at(f.w.s4);
     fused_pointwise(f, P + net.lift_w, net.C, net.cin, 0, x, h0, P + net.lift_b, nullptr);
     for (int l = 0; l < net.L; ++l) {
         const float* h = h0 + l * act;
@@ -792,8 +818,9 @@ void fused_forward(Fno& f, const float* P, const float* x, float* y, bool keep_p
     fused_pointwise(f, P + net.proj_w, net.cout, net.C, 0, h0 + net.L * act, y, P + net.proj_b, nullptr);
 }
 
+// last_use: the pre-activations are not needed any more (a training step)
 template <int CT>
-void fused_backward(Fno& f, const float* P, const float* x, const float* dy, float* g, float* dx)
+void fused_backward(Fno& f, const float* P, const float* x, const float* dy, float* g, float* dx, bool last_use)
 {
     const Net& net = f.net;
     const int C = net.C, L = net.L;
@@ -801,25 +828,43 @@ void fused_backward(Fno& f, const float* P, const float* x, const float* dy, flo
     const long long uplane = (long long)f.B * C * f.w.n[2] * net.m * net.m;
     const float invN = 1.f / (float)f.w.N;
     float *h0 = f.at(f.w.h), *pre = f.at(f.w.pre);
-    // gradient of every layer's pre-activations (the weight gradients read them
-    // at the end), and of the lift's output
-    float *dp = f.at(f.w.dp), *dh = f.at(f.w.dh2);
     float *D = f.at(f.w.s3), *RD = f.at(f.w.s1), *U = f.at(f.w.s4);
+    // The weight gradients read the gradients of every layer's pre-activations and of
+    // the lift's output at the end, all maps side by side.  Where the pool has too few
+    // places, those of a training step take the pre-activations' (layer passes of 32
+    // channels on 128^3 258 -> 275 us, weight gradients 9.3 -> 9.5 ms); a backward call of
+    // its own has the output's place too, and goes through the pool in groups of layers
+    // beyond that.
+    const bool in_place = last_use && f.w.nd < L + 1;
+    const int places = std::min(f.w.nd + (!last_use && net.cout >= C ? 1 : 0), L + 1);
+    int slot = 0, held = 0;
+    auto next = [&](int l) {  // for layer l or, -1, the lift
+        if (in_place) return l >= 0 ? pre + l * act : f.at(f.w.d);
+        const int k = slot;
+        slot = (slot + 1) % places;
+        ++held;
+        return k < f.w.nd ? f.at(f.w.d) + k * act : f.at(f.w.y);
+    };
     fno::WItems w;
     w.n = 0;
     w.it[w.n++] = {dy, h0 + L * act, g + net.proj_w, g + net.proj_b, net.cout, C};
-    float* d = L > 0 ? dp + (L - 1) * act : dh;
+    float* d = next(L - 1);
     fused_pointwise(f, P + net.proj_w, net.cout, C, 1, dy, d, nullptr, L > 0 ? pre + (L - 1) * act : nullptr);
     for (int l = L - 1; l >= 0; --l) {
         const float* X = f.at(f.w.xhat) + 2 * l * xplane;
         w.it[w.n++] = {d, h0 + l * act, g + net.pw_w[l], g + net.pw_b[l], C, C};
+        if (held == places) {
+            fused_wgrad(f, w);
+            w.n = 0;
+            held = 1;  // d itself
+        }
         // D = F dpre; dR(k) = (1/N) sum_b D X^H; dh = W^T dpre + (1/N) Re F^H R^H D
         fused_dft(f, d, D, xplane);
         fno::k_spec_wgrad<CT><<<(unsigned)((net.m3 + 3) / 4), 256, 0, f.s>>>(
             D, X, xplane, g + net.r_re[l], g + net.r_im[l], C, f.B, net.m3, invN);
         fused_mix<CT>(f, P + net.r_re[l], P + net.r_im[l], D, RD, xplane, true);
         fused_idft_z(f, RD, xplane, U, uplane);
-        float* dn = l > 0 ? dp + (l - 1) * act : dh;
+        float* dn = next(l - 1);
         if (l > 0)
             fused_layer_out<CT, fno::LAYER_BWD>(f, U, uplane, d, P + net.pw_w[l], nullptr, pre + (l - 1) * act,
                                                 nullptr, dn);
@@ -846,17 +891,17 @@ void net_forward(Fno& f, const float* P, const float* x, float* y, bool keep_pre
     }
 }
 
-void net_backward(Fno& f, const float* P, const float* x, const float* dy, float* g, float* dx)
+void net_backward(Fno& f, const float* P, const float* x, const float* dy, float* g, float* dx, bool last_use)
 {
     if (!f.fused) {
         backward(f, P, x, dy, g, dx);
         return;
     }
     switch ((f.net.C + 15) / 16) {
-        case 1: fused_backward<1>(f, P, x, dy, g, dx); break;
-        case 2: fused_backward<2>(f, P, x, dy, g, dx); break;
-        case 3: fused_backward<3>(f, P, x, dy, g, dx); break;
-        default: fused_backward<4>(f, P, x, dy, g, dx); break;
+        case 1: fused_backward<1>(f, P, x, dy, g, dx, last_use); break;
+        case 2: fused_backward<2>(f, P, x, dy, g, dx, last_use); break;
+        case 3: fused_backward<3>(f, P, x, dy, g, dx, last_use); break;
+        default: fused_backward<4>(f, P, x, dy, g, dx, last_use); break;
     }
 }
 
@@ -865,12 +910,22 @@ rpm_status fno_open(Fno& f, const rpm_fno_config* cfg, const int32_t n[3], int32
 {
     f.net = make_net(cfg);
     if (!f.net.ok || !valid_grid(n) || batch < 1 || batch > 4096) return RPM_E_INVALID;
-    f.w = make_fws(f.net, n, batch);
+    // (a grid of few voxels may need more for the fused passes: a buffer with room for
+    // the batched GEMMs only takes them, with the same results)
+    f.fused = fused_fits(f.net, n);
+    f.w = make_fws(f.net, n, batch, f.fused);
+    if (f.fused && ws_bytes < (size_t)f.w.total * sizeof(float)) {
+        f.fused = false;
+        f.w = make_fws(f.net, n, batch, false);
+    }
     if (!ws || ws_bytes < (size_t)f.w.total * sizeof(float)) return RPM_E_WORKSPACE;
     f.ws = (float*)ws;
     f.s = (hipStream_t)stream;
     f.B = batch;
-    f.fused = fused_fits(f.net, f.w.n);
+    if (f.fused) {  // a larger buffer has room for more gradients
+        const long long act = (long long)batch * f.net.C * f.w.N;
+        f.w.nd = (int)std::min<long long>(f.net.L + 1, ((long long)(ws_bytes / sizeof(float)) - f.w.d) / act);
+    }
     if (f.fused) make_tables(f);
     else if (!upload_twiddles(f)) return RPM_E_HIP;
     return RPM_OK;
@@ -906,7 +961,7 @@ rpm_status rpm_fno_workspace_size(const rpm_fno_config* cfg, const int32_t n[3],
 {
     const Net net = make_net(cfg);
     if (!net.ok || !valid_grid(n) || batch < 1 || batch > 4096 || !bytes) return RPM_E_INVALID;
-    *bytes = (size_t)make_fws(net, n, batch).total * sizeof(float);
+    *bytes = (size_t)make_fws(net, n, batch, fused_fits(net, n)).total * sizeof(float);
     return RPM_OK;
 }
 
@@ -963,7 +1018,7 @@ rpm_status rpm_fno_backward(const rpm_fno_config* cfg, const float* params, cons
     Fno f;
     rpm_status rs = fno_open(f, cfg, n, batch, workspace, ws_bytes, hip_stream);
     if (rs != RPM_OK) return rs;
-    net_backward(f, params, x, dy, grad, dx);
+    net_backward(f, params, x, dy, grad, dx, false);
     if (!f.ok || hipGetLastError() != hipSuccess || hipStreamSynchronize(f.s) != hipSuccess) return RPM_E_HIP;
     return RPM_OK;
 }
@@ -978,12 +1033,13 @@ rpm_status rpm_fno_train_step(const rpm_fno_config* cfg, float* params, float* g
     if (rs != RPM_OK) return rs;
     net_forward(f, params, x, f.at(f.w.y), true);
     const long long ny = (long long)batch * f.net.cout * f.w.N;
-    // the output gradient in the accumulator slot (backward does not use it)
-    float* dy = f.at(f.w.acc);
+    // the output gradient: in the output's place; batched: in the accumulator slot, which
+    // their backward pass does not use
+    float* dy = f.at(f.fused ? f.w.y : f.w.acc);
     const int nb = (int)std::min<long long>(1024, (batch * f.w.N + 255) / 256);
     double* part = reinterpret_cast<double*>(f.at(f.w.part));
     k_mse<<<nb, 256, 0, f.s>>>(f.at(f.w.y), target, x, f.net.cin, f.net.cout, f.w.N, dy, part, ny);
-    net_backward(f, params, x, dy, grad, nullptr);
+    net_backward(f, params, x, dy, grad, nullptr, true);
     const float b1 = 0.9f, b2 = 0.999f, eps = 1e-8f;
     const float c1 = 1.f - std::pow(b1, (float)step), c2 = 1.f - std::pow(b2, (float)step);
     k_adam<<<blocks(f.net.total), 256, 0, f.s>>>(params, grad, adam_m, adam_v, f.net.total, lr, b1, b2, eps, c1, c2);

@@ -357,7 +357,7 @@ __global__ __launch_bounds__(256) void k_spec_wgrad(const float* __restrict__ D,
 //   val = (1/N) Re sum_kx V exp(2 pi i kx x / n) + W h        (W^T h with trans)
 // FWD: pre = val + bias (kept when pre_out is given), out = gelu(pre).
 // BWD: out = val gelu'(aux) (aux: pre-activations of the layer below), the
-// gradient the next lower layer starts from; PLAIN: out = val.
+// gradient the next lower layer starts from, possibly in aux's place; PLAIN: out = val.
 enum { LAYER_FWD = 0, LAYER_BWD = 1, LAYER_PLAIN = 2 };
 __host__ __device__ constexpr int layer_vs(int CT) { return CT * 256 + (CT < 4 ? 4 : 0); }  // row of V, per y
 
@@ -365,9 +365,8 @@ template <int CT, int MODE>
 __global__ __launch_bounds__(1024) void k_layer_out(const float* __restrict__ U, long long planeU,
                                                     const float* __restrict__ h, const float* __restrict__ W,
                                                     int trans, const float* __restrict__ bias,
-                                                    const float* __restrict__ aux, float* __restrict__ pre_out,
-                                                    float* __restrict__ out, int C, int n2, int m, float alpha,
-                                                    AxTab ax, AxTab ay)
+                                                    const float* aux, float* __restrict__ pre_out, float* out, int C,
+                                                    int n2, int m, float alpha, AxTab ax, AxTab ay)
 {
 #pragma clang fp contract(off)
     extern __shared__ __align__(16) short V[];  // [re, im][y][c][kx]
@@ -495,12 +494,12 @@ __global__ __launch_bounds__(1024) void k_layer_out(const float* __restrict__ U,
 }
 
 // out[b][o][v] = sum_i W(o, i) in[b][i][v] (W row-major [M][K], or [K][M] with
-// trans) for K <= 16 KT, M <= 64: + bias[o], or * gelu'(aux[b][o][v]).  A wave
-// takes 32 voxels and all rows at a time.
+// trans) for K <= 16 KT, M <= 64: + bias[o], or * gelu'(aux[b][o][v]) (out may be
+// aux).  A wave takes 32 voxels and all rows at a time.
 template <int KT>
 __global__ __launch_bounds__(256) void k_pointwise(const float* __restrict__ W, int trans,
-                                                   const float* __restrict__ in, float* __restrict__ out,
-                                                   const float* __restrict__ bias, const float* __restrict__ aux,
+                                                   const float* __restrict__ in, float* out,
+                                                   const float* __restrict__ bias, const float* aux,
                                                    int M, int K, long long N, long long ntiles, long long tpb)
 {
     constexpr int KS = 16 * KT + 4;
@@ -534,6 +533,16 @@ __global__ __launch_bounds__(256) void k_pointwise(const float* __restrict__ W, 
             }
         for (int m0 = 0; m0 < Mp; m0 += 16) {
             f32x4 acc[2] = {zero, zero};
+            float z[2][4];  // aux, before the first store
+            if (aux)
+#pragma unroll
+                for (int u = 0; u < 2; ++u)
+#pragma unroll
+                    for (int q = 0; q < 4; ++q) {
+                        const int o = m0 + lk + q;
+                        const long long v = v0 + 16 * u + li;
+                        z[u][q] = aux[o < M && v < N ? (b * M + o) * N + v : 0];
+                    }
 #pragma unroll
             for (int ks = 0; ks < KT; ++ks) {
                 const bf16x4 a = ld4(Ws + (m0 + li) * KS + 16 * ks + lk);
@@ -547,11 +556,10 @@ __global__ __launch_bounds__(256) void k_pointwise(const float* __restrict__ W, 
                     const int o = m0 + lk + q;
                     const long long v = v0 + 16 * u + li;
                     if (o < M && v < N) {
-                        const long long e = (b * M + o) * N + v;
                         float r = acc[u][q];
                         if (bias) r += bias[o];
-                        if (aux) r *= gelu_grad(aux[e]);
-                        out[e] = r;
+                        if (aux) r *= gelu_grad(z[u][q]);
+                        out[(b * M + o) * N + v] = r;
                     }
                 }
         }
