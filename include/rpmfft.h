@@ -237,10 +237,10 @@ rpm_status rpm_lame_from_young(double E, double nu, double *lam, double *mu);
 
 /* Bytes of device workspace needed for grid n under options o.
  * RPM_E_UNSUPPORTED_SIZE when an extent is not 2,3-smooth in [2, 512] (nz may
- * be 1), or when a pencil pass would not fit its LDS tile: with the
- * polarization map the z (2-D: y) pencils carry 12 components, which bounds
- * their length to 144 in FP64 and, since FP32 fields are certified in FP64,
- * in FP32 as well. */
+ * be 1), or when a pencil pass would not fit its LDS tile: the z (2-D: y)
+ * pencils end at 256 points, and with the polarization map, where they carry 12
+ * components, at 128; in FP64 and, since FP32 fields are certified in FP64, in
+ * FP32 as well (but for rpm_fft_apply_static, which certifies nothing). */
 rpm_status rpm_workspace_size(const int32_t n[3], const rpm_options *o, size_t *bytes);
 
 /*

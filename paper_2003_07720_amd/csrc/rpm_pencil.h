@@ -782,6 +782,10 @@ __host__ __device__ constexpr bool always_wide(bool pol)
 {
     return pol || (sizeof(T) == 8 && ((N >= 64 && N <= 128) || N == 256));
 }
+// The polarization map's FP64 grids end at 128 points along the last axis (the run-time
+// pass's LDS, which decides what a call takes), so its pass is not there beyond.
+template <typename T, int N>
+constexpr bool pol_gamma() { return sizeof(T) == 4 || N <= 128; }
 template <typename T, int N>
 constexpr bool gamma_wide(bool pol, int npen)
 {
@@ -961,6 +965,7 @@ struct Pencil {
     static void y_pass(int dir, int comps, const cx<T>* in, cx<T>* out, const Geo& g, const cx<T>* tw,
                        const int* done, hipStream_t s);
     static int rows() { return tile_rows<T, N>(); }
+    static bool has_gamma(bool pol) { return !pol || pol_gamma<T, N>(); }
     static void x_forward(bool pol, const T* xin, const uint8_t* phase, const double* lame, int use_ref, double lam0,
                           double mu0, cx<T>* S1, double* part_mean, const Geo& g, const cx<T>* tw, const int* done,
                           hipStream_t s);

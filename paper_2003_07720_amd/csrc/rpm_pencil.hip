@@ -63,8 +63,9 @@ void Pencil<T, N>::gamma(bool pol, cx<T>* S, const Geo& g, const cx<T>* tw, doub
         k_pg<T, N, POL, W><<<gamma_blocks(POL, npen), GCfg<T, N, POL, W>::NT, 0, s>>>(a);
     };
     using std::false_type, std::true_type;
-    if (pol) launch(true_type(), true_type());
-    else if constexpr (always_wide<T, N>(false)) launch(false_type(), true_type());
+    if (pol) {
+        if constexpr (pol_gamma<T, N>()) launch(true_type(), true_type());
+    } else if constexpr (always_wide<T, N>(false)) launch(false_type(), true_type());
     else if (gamma_wide<T, N>(false, npen)) launch(false_type(), true_type());
     else launch(false_type(), false_type());
 }

@@ -217,7 +217,10 @@ Shapes<T> make_shapes(const int32_t n[3], int ncomp, const rpm_tuning* tn = null
         s.Gxi = ncomp == 12 ? s.Gx : 3 * s.Gx;
     });
     s.fy = !g.two_d && with_length<T>(g.ny, [](auto) {});
-    s.fg = with_length<T>(nrow, [&](auto pc) { s.Gpg = pc.gamma_blocks(ncomp == 12, npen); });
+    with_length<T>(nrow, [&](auto pc) {
+        s.fg = pc.has_gamma(ncomp == 12);
+        s.Gpg = s.fg ? pc.gamma_blocks(ncomp == 12, npen) : 0;
+    });
     s.Gg = (int)((g.N + kChunk - 1) / kChunk);
     s.Gp = (int)((6 * g.N + kVecBlock - 1) / kVecBlock);
     const long long ntile = (6 * g.N + kZTile - 1) / kZTile;
