@@ -2165,27 +2165,42 @@ __global__ __launch_bounds__(kThreads) void k_growth_diff(const T* __restrict__ 
 // RPM recombination eps = xi + sum_j d_j Z_j as a streaming pass: each thread
 // handles runs of VL consecutive elements; for a column, a wave reads one
 // contiguous kilobyte of its tile.  Columns go in groups of 8 whose loads are
-// issued together (non-temporal); slots past p repeat column p - 1 with
-// coefficient zero.
+// issued together; slots past p repeat column p - 1 with coefficient zero.
+//
+// FP64 sums the columns in one chain from xi.  FP32 takes them in pairs, in the
+// order and rounding of k_recombine_split: pair k of ceil(p / 2) has columns
+// pair_col, and the sum of a wave's columns there (two, or two and the two 32
+// further on) is added to the result as one term, half as many roundings at the
+// size of eps (20 steps at 64^3, p = 28: 3.5e-7 off the 64-bit value, 4.8e-7 with
+// one chain).
+__device__ __forceinline__ int pair_col(int k, int w2)  // w2: waves with four columns
+{
+    return k < 2 * w2 ? (k & ~1) + 32 * (k & 1) : 2 * (k - w2);
+}
+
 template <typename T, bool NT>
 __device__ __forceinline__ void recombine_body(const T* __restrict__ xi, const T* __restrict__ Z, int p,
                                                int zP, const double* __restrict__ dco, T* __restrict__ eps,
                                                long long n, const int* __restrict__ done)
 {
     constexpr int VL = 16 / sizeof(T);
+    constexpr bool PAIRS = sizeof(T) == 4;
     using V = typename Vec4<T>::type;
     __shared__ T dj[kMaxP + 8];
     const int stop = done ? *done : 0;
     for (int j = threadIdx.x; j < kMaxP + 8; j += kThreads) dj[j] = j < p ? (T)dco[j] : T(0);
     const long long e = ((long long)blockIdx.x * kThreads + threadIdx.x) * VL;
+    const int w2 = p > 32 ? (p - 31) / 2 : 0, np = (p + 1) / 2;
     // the first loads leave before the coefficients are there
     const bool run = e + VL <= n;
     const T* zt = Z + (run ? zix(e, 0, zP) : 0);  // column j at zt + j * kZTile
     V acc = V(), z[8];
     auto load = [&](int g) {
 #pragma unroll
-        for (int u = 0; u < 8; ++u)
-            z[u] = stream_load<NT>(reinterpret_cast<const V*>(zt + (long long)min(g + u, p - 1) * kZTile));
+        for (int u = 0; u < 8; ++u) {
+            const int j = PAIRS ? pair_col((g + u) / 2, w2) + (u & 1) : g + u;
+            z[u] = stream_load<NT>(reinterpret_cast<const V*>(zt + (long long)min(j, p - 1) * kZTile));
+        }
     };
     if (run) {
         acc = *reinterpret_cast<const V*>(xi + e);
@@ -2195,21 +2210,61 @@ __device__ __forceinline__ void recombine_body(const T* __restrict__ xi, const T
     __syncthreads();
     if (run) {
         T* a = reinterpret_cast<T*>(&acc);
-        for (int g = 0; g < p; g += 8) {
-            if (g > 0) load(g);
+        if constexpr (PAIRS) {
+            T sum[VL] = {};  // acc: the pairs of one wave, the first one's from xi on
+            for (int g = 0; g < p; g += 8) {
+                if (g > 0) load(g);
 #pragma unroll
-            for (int u = 0; u < 8; ++u) {
-                const T* zs = reinterpret_cast<const T*>(&z[u]);
-                const T c = dj[g + u];
+                for (int h = 0; h < 4; ++h) {
+                    const int k = g / 2 + h, j = pair_col(k, w2);
 #pragma unroll
-                for (int q = 0; q < VL; ++q) a[q] += c * zs[q];
+                    for (int u = 0; u < 2; ++u) {
+                        const T* zs = reinterpret_cast<const T*>(&z[2 * h + u]);
+                        const T c = k < np ? dj[j + u] : T(0);
+#pragma unroll
+                        for (int q = 0; q < VL; ++q) a[q] += c * zs[q];
+                    }
+                    if (k >= 2 * w2 || (k & 1))
+#pragma unroll
+                        for (int q = 0; q < VL; ++q) {
+                            sum[q] += a[q];
+                            a[q] = T(0);
+                        }
+                }
+            }
+#pragma unroll
+            for (int q = 0; q < VL; ++q) a[q] += sum[q];
+        } else {
+            for (int g = 0; g < p; g += 8) {
+                if (g > 0) load(g);
+#pragma unroll
+                for (int u = 0; u < 8; ++u) {
+                    const T* zs = reinterpret_cast<const T*>(&z[u]);
+                    const T c = dj[g + u];
+#pragma unroll
+                    for (int q = 0; q < VL; ++q) a[q] += c * zs[q];
+                }
             }
         }
         *reinterpret_cast<V*>(eps + e) = acc;
     } else {
         for (long long i = e; i < n; ++i) {
             T v = xi[i];
-            for (int j = 0; j < p; ++j) v += dj[j] * Z[zix(i, j, zP)];
+            if constexpr (PAIRS) {
+                T sum = T(0);
+                for (int k = 0; k < np; ++k) {
+                    const int j = pair_col(k, w2);
+                    v += dj[j] * Z[zix(i, j, zP)];
+                    if (j + 1 < p) v += dj[j + 1] * Z[zix(i, j + 1, zP)];
+                    if (k >= 2 * w2 || (k & 1)) {
+                        sum += v;
+                        v = T(0);
+                    }
+                }
+                v += sum;
+            } else {
+                for (int j = 0; j < p; ++j) v += dj[j] * Z[zix(i, j, zP)];
+            }
             eps[i] = v;
         }
     }
