@@ -337,7 +337,7 @@ __device__ __forceinline__ void pxf_body(const T* __restrict__ xin, const uint8_
     constexpr int R1 = Fac<N>::B, R2 = Fac<N>::A, NH = N / 2 + 1;
     constexpr int I1 = (R2 * TY + NT - 1) / NT, I2 = (R1 * TY + NT - 1) / NT;
     __shared__ cx<T> X[N * LS];
-    __shared__ T lt[2 * 256];  // phase table
+    __shared__ __align__(16) T lt[2 * 256];  // phase table
     int tile, pair;
     if (!x_block(blockIdx.x, ntiles, NP, tile, pair)) return;
     const int z = tile / nyt, y0 = (tile - z * nyt) * TY;
@@ -355,14 +355,23 @@ __device__ __forceinline__ void pxf_body(const T* __restrict__ xin, const uint8_
             for (int q = 0; q < R1; ++q) f(i, q, in ? r * N + j + R2 * q : 0, in);
         }
     };
-    // phase labels; the table comes from LDS once both have arrived.  Labels past
-    // the table take the first of the zeros behind it in memory: voids, as in the
-    // passes that read it there.
+    // phase labels; the table comes from LDS once both have arrived, zeros behind its
+    // own entries: labels past the table are voids, as in the passes that read it in
+    // memory (bounding each label instead took k_pxf 107 -> 115 us at 192^3)
     const bool tab = pair < 3 && !use_ref;
     int lab[I1][R1];
+    const int n4 = (2 * nph + 3) / 4;  // (memory has zeros up to 512)
+    auto table_ready = [&]() {
+        if (!tab) return;
+        for (int i = threadIdx.x; i < 128; i += NT)
+            if (i >= n4)
+#pragma unroll
+                for (int q = 0; q < 4; ++q) lt[4 * i + q] = T(0);
+        __syncthreads();
+    };
     if (tab) {
-        for (int i = threadIdx.x; i < 2 * min(nph + 1, 256); i += NT) lt[i] = (T)lame[i];
-        each([&](int i, int q, int o, bool) { lab[i][q] = min((int)ph[o], nph); });
+        for (int i = threadIdx.x; i < 4 * n4; i += NT) lt[i] = (T)lame[i];
+        each([&](int i, int q, int o, bool) { lab[i][q] = (int)ph[o]; });
     }
     cx<T> w[I1][R1];
 #pragma unroll
@@ -381,7 +390,7 @@ __device__ __forceinline__ void pxf_body(const T* __restrict__ xin, const uint8_
             if (pair == 1) e3[i][q] = src[3 * M + o];
         });
         if (stop) return;
-        if (tab) __syncthreads();
+        table_ready();
         each([&](int i, int q, int, bool in) {
             T lam, mu;
             lam_mu(i, q, lam, mu);
@@ -399,7 +408,7 @@ __device__ __forceinline__ void pxf_body(const T* __restrict__ xin, const uint8_
             b[i][q] = src[(c + 1) * M + o];
         });
         if (stop) return;
-        if (tab) __syncthreads();
+        table_ready();
         each([&](int i, int q, int, bool in) {
             T lam = T(0), mu = T(0.5);
             if (pair == 2) lam_mu(i, q, lam, mu);
