@@ -15,10 +15,11 @@
 //   xinv   S1 -> complex-to-real inverse FFT along x -> xi = eps - t
 //
 // and, in an RPM iteration, two streams over the basis Z: the recombination
-// eps = xi_prev + Z d before the map (k_recombine_split for FP32 fields; for
-// FP64 fields on 128-point rows inside xfwd, else k_recombine) and the
-// projections Z^T xi after it (k_gdots_split / k_gdots, FP64 accumulation).  The kernels of this file take any 2,3-smooth length;
-// rpm_pencil.h has the passes of the usual ones.
+// eps = xi_prev + Z d before the map (k_recombine; k_recombine_split for large
+// FP32 bases; for FP64 fields on 128-point rows inside xfwd) and the projections
+// Z^T xi after it (k_gdots_split / k_gdots, FP64 accumulation).  The passes of
+// this file take any 2,3-smooth length; those of rpm_pencil.h have theirs at
+// compile time and serve the lengths listed there.
 //
 // In 2-D (nz == 1) the y passes are skipped and gamma runs along y on S1.
 // The k = 0 term of t is N(<eps> - E), so xi = eps - F^-1[Gamma sigma_hat]
@@ -1234,8 +1235,8 @@ __device__ __forceinline__ void gdots_tile(const Fields<TA>& a, long long t0, co
 }
 
 // (Arguments in one struct: see RecombineArgs.)
-// SITE separates the call sites in profiles (0: the per-step projections, 1:
-// basis growth); both read the basis with non-temporal loads.
+// SITE separates the call sites in profiles (0: the projections after a growth and
+// of batched cases, 1: basis growth); both read the basis with non-temporal loads.
 template <typename TA, typename TZ, int NF, int SITE>
 __device__ __forceinline__ void gdots_body(Fields<TA> a, const TZ* __restrict__ Z, int p, int zP, long long N,
                                            double* __restrict__ part, int ld)

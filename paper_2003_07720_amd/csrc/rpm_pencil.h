@@ -54,6 +54,13 @@ RPM_FAC(162, 18, 9)
 RPM_FAC(192, 16, 12)
 RPM_FAC(256, 16, 16)
 #undef RPM_FAC
+// The lengths that are built: the extents from 16 points on that the benchmark and the
+// timed workloads run.  The scheme would reach others, which stay with the run-time
+// passes although these are faster there, measured with the same kernels (a map
+// application, run-time / fixed): 216^3 FP32 1343 / 787 us, FP64 2761 / 1351; 288x288x64
+// 603 / 458; 324x324x64 813 / 563; 12^3 101 / 75; 8^3 90 / 66; each length takes 250 KB of
+// library and 5 s of the build.  Out of reach: 2, 3 (one factor) and 243, 384, 432, 486,
+// 512 (a factor above 18).
 #define RPM_PENCIL_LENGTHS(X) \
     X(16) X(18) X(24) X(27) X(32) X(36) X(48) X(54) X(64) X(72) X(81) X(96) X(108) X(128) X(144) X(162) X(192) X(256)
 
@@ -337,7 +344,7 @@ __device__ __forceinline__ void pxf_body(const T* __restrict__ xin, const uint8_
     constexpr int R1 = Fac<N>::B, R2 = Fac<N>::A, NH = N / 2 + 1;
     constexpr int I1 = (R2 * TY + NT - 1) / NT, I2 = (R1 * TY + NT - 1) / NT;
     __shared__ cx<T> X[N * LS];
-    __shared__ __align__(16) T lt[2 * 256];  // phase table
+    __shared__ T lt[2 * 256];  // phase table
     int tile, pair;
     if (!x_block(blockIdx.x, ntiles, NP, tile, pair)) return;
     const int z = tile / nyt, y0 = (tile - z * nyt) * TY;
@@ -355,22 +362,22 @@ __device__ __forceinline__ void pxf_body(const T* __restrict__ xin, const uint8_
             for (int q = 0; q < R1; ++q) f(i, q, in ? r * N + j + R2 * q : 0, in);
         }
     };
-    // phase labels; the table comes from LDS once both have arrived, zeros behind its
-    // own entries: labels past the table are voids, as in the passes that read it in
-    // memory (bounding each label instead took k_pxf 107 -> 115 us at 192^3)
+    // phase labels; the table comes from LDS once both have arrived.  Labels past the
+    // table are voids, as in the passes that read it in memory, where zeros follow it: a
+    // wave that meets one writes those zeros here.  (In every block the zeros took 0.17 us
+    // of 5.1 on 32^2 grids; a bound on each label, 115 us instead of 107 at 192^3.)
     const bool tab = pair < 3 && !use_ref;
     int lab[I1][R1];
-    const int n4 = (2 * nph + 3) / 4;  // (memory has zeros up to 512)
     auto table_ready = [&]() {
         if (!tab) return;
-        for (int i = threadIdx.x; i < 128; i += NT)
-            if (i >= n4)
-#pragma unroll
-                for (int q = 0; q < 4; ++q) lt[4 * i + q] = T(0);
+        int top = 0;
+        each([&](int i, int q, int, bool) { top = max(top, lab[i][q]); });
+        if (__any(top >= nph))
+            for (int i = 2 * nph + (threadIdx.x & 63); i < 512; i += 64) lt[i] = T(0);
         __syncthreads();
     };
     if (tab) {
-        for (int i = threadIdx.x; i < 4 * n4; i += NT) lt[i] = (T)lame[i];
+        for (int i = threadIdx.x; i < 2 * nph; i += NT) lt[i] = (T)lame[i];
         each([&](int i, int q, int o, bool) { lab[i][q] = (int)ph[o]; });
     }
     cx<T> w[I1][R1];

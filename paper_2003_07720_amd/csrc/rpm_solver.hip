@@ -2,9 +2,10 @@
 //
 // The hot loop follows Algorithm 2 of the paper (Algorithm 1 when no basis is
 // kept): every iteration is one application of F (five pencil passes, see
-// rpm_kernels.h) plus one deterministic reduction and one single-workgroup
-// finalize that evaluates the equilibrium error, tests convergence and takes
-// the Newton step on the unstable subspace.  Everything stays on the device;
+// rpm_pencil.h and rpm_kernels.h), with a basis the recombination before it and
+// the projections after it, and one single-workgroup kernel that sums the
+// partials in fixed order, evaluates the equilibrium error, tests convergence and
+// takes the Newton step on the unstable subspace.  Everything stays on the device;
 // the host reads a 'done' flag every check_every iterations and at the basis
 // growth points (every n_max + 1 iterations), where it needs the QR decision.
 #include <hip/hip_runtime.h>
@@ -524,7 +525,10 @@ void run_F(Ctx<T>& c, const T* xin, int p_corr, T* eps_store, const T* eps_for_i
     // 1115 / 1159; 64^3: 32 107 / 105, 64 173 / 175; 48^3: 64 95 / 93)
     const bool split = sizeof(T) == 4 && (6 * g.N) % kZTile == 0 && p_corr >= 30 && fieldB * p_corr >= 400e6;
     // FP64 on 128-point rows: eps = xin + Z d recombined inside the x pass, which
-    // stores it for the x-inverse (128^3, p = 32: 610 us, as the two passes)
+    // stores it for the x-inverse; rpm_stats then counts the basis stream in the x
+    // class.  20 steps with it / as two passes: 128^3 p = 8 11.2 / 11.5 ms, p = 32 29.5 /
+    // 29.4, p = 64 52.8 / 52.4; small grids lose (128x64x32 p = 16 2.61 / 2.51, 128x32x32
+    // p = 32 2.37 / 2.23, 128^2 p = 16 1.15 / 0.83).
     constexpr bool can_fuse = sizeof(T) == 8;
     const bool fuse = can_fuse && eps_store && g.nx == 128 && !pol;
     if constexpr (can_fuse) {
