@@ -955,10 +955,12 @@ int add_columns(Ctx<T>& c, int& p, double* const* v, int* jvps)
 }
 
 // First part of a basis growth after main-loop F application number it: the last
-// two differences of q and their Gram entries (st->gram).
+// two differences of q and their Gram entries (st->gram).  The growth's timing
+// event begins here (ev) and ends in grow_basis.
 template <typename T>
-void growth_diff(Ctx<T>& c, int it, int nq, int p)
+void growth_diff(Ctx<T>& c, int it, int nq, int p, hipEvent_t& ev)
 {
+    c.mark_begin(RPM_K_GROWTH, ev);
     const long long N = c.sh.g.N;
     double* D1 = c.template at<double>(c.L.D1);
     double* D0 = c.template at<double>(c.L.D0);
@@ -978,7 +980,7 @@ void growth_diff(Ctx<T>& c, int it, int nq, int p)
 // (growth_diff).  Returns the number of columns added, or -1 on HIP error.
 template <typename T>
 int grow_basis(Ctx<T>& c, int nq, const double* gram, int& p, const rpm_options* o, int growth_index, int* want_out,
-               int* jvps)
+               int* jvps, hipEvent_t ev)
 {
     const long long N = c.sh.g.N;
     double* D1 = c.template at<double>(c.L.D1);
@@ -986,8 +988,6 @@ int grow_basis(Ctx<T>& c, int nq, const double* gram, int& p, const rpm_options*
     T* tmp = c.template at<T>(c.L.tmp);
     T* tmp2 = c.template at<T>(c.L.tmp2);
     const bool two = nq >= 3;
-    hipEvent_t ev;
-    c.mark_begin(RPM_K_GROWTH, ev);
     const double T11 = std::sqrt(std::max(gram[0], 0.0));
     double T22 = 0.0;
     int want = 0;
@@ -1152,14 +1152,18 @@ rpm_status run_solve(Ctx<T>& c, const rpm_problem* pr, const rpm_options* o, con
             // at a growth point the differences are formed before the flags are
             // known, so that one wait serves both
             DevHead hd;
-            if (at_growth) growth_diff(c, it, nq, p);
+            hipEvent_t gev = nullptr;
+            if (at_growth) growth_diff(c, it, nq, p, gev);
             if (!sync_read(c, &hd, c.st, offsetof(DevHead, tol))) return RPM_E_HIP;
-            if (hd.done || hd.iters >= o->max_iter) break;
+            if (hd.done || hd.iters >= o->max_iter) {
+                if (gev) c.prof.pool.push_back(gev);
+                break;
+            }
             if (at_growth) {
                 int want = 0;
                 const int p_before = p;
                 store_key(c);
-                const int added = grow_basis(c, nq, hd.gram, p, o, (int)so.decisions.size(), &want, &jvps);
+                const int added = grow_basis(c, nq, hd.gram, p, o, (int)so.decisions.size(), &want, &jvps, gev);
                 if (added < 0) return RPM_E_HIP;
                 so.decisions.push_back(want);
                 ++growth;
@@ -1883,9 +1887,10 @@ rpm_status eff_batched(const rpm_problem* pr, const rpm_options* o, double* C, r
                     if (f != last) k_copy_basis_state<<<1, kThreads, 0, c.s>>>(cx[f].st, cx[last].st);
                     int want = 0;
                     double gram[3];
-                    growth_diff(cx[f], it, nq, p);
+                    hipEvent_t gev = nullptr;
+                    growth_diff(cx[f], it, nq, p, gev);
                     if (!sync_read(cx[f], gram, cx[f].st->gram, sizeof(gram))) return RPM_E_HIP;
-                    const int added = grow_basis(cx[f], nq, gram, p, o, (int)decisions.size(), &want, &jvps);
+                    const int added = grow_basis(cx[f], nq, gram, p, o, (int)decisions.size(), &want, &jvps, gev);
                     if (added < 0) return RPM_E_HIP;
                     decisions.push_back(want);
                     last = f;
