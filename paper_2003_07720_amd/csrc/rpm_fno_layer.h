@@ -7,7 +7,7 @@
 // and written once per layer; as separate batched GEMMs the same layer was 26
 // launches that read h five times and moved every partial sum of a complex
 // product through memory.  Warm start of a 64^3 cell (width 32, 4 layers, 12
-// modes): 1989 -> 303 us; training step on four 32^3 cells: 44.2 -> 0.77 ms, of
+// modes): 1990 -> 305 us; training step on four 32^3 cells: 44.2 -> 0.75 ms, of
 // which the weight gradients (k_wgrad) were most.
 //
 // The arithmetic is that of the batched GEMM (k_gemm_bf16), bit for bit:
